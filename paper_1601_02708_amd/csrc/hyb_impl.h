@@ -176,6 +176,15 @@ hipError_t launch_lbm_step2(const LbmArgs &a, int prec, hipStream_t s, int part 
 // of the patch perimeter.
 hipError_t launch_lbm_stepk(const LbmArgs &a, int prec, int K, hipStream_t s, int part = 0, int depth = 0,
                             int ring = 0);
+// Nodes x0 .. x1, y0 .. y1 of the patch (empty when x1 < x0).
+struct NodeRect {
+    int x0, x1, y0, y1;
+};
+// K = 3 .. 5 fine steps in one launch (stream_kernels.hip; fixed solids, nothing
+// recorded) on a rectangle of nodes at least K from every perimeter node's row
+// and column: a.src holds f*(j) there and K nodes around, a.dst receives
+// f*(j+K).
+hipError_t launch_lbm_stream(const LbmArgs &a, int prec, int K, const NodeRect &nodes, hipStream_t s);
 // Adjoint of one fine step (adjoint_kernels.hip), HYB_FP64 or HYB_FP32:
 // a.src = the step's source state f*(t) (read only with clamped closures),
 // snext = f*(t+1), lam = dJ/df*(t+1); nu is scratch; out = dJ/df*(t);

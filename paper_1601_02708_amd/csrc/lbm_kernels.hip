@@ -12,96 +12,18 @@
 // scaled g of Pop<_Float16>); arithmetic is in Pop<S>::T (double or float),
 // the closures in FP64.
 //
-// Default path: two fine steps per launch (lbm_sweep2_kernel, temporal
-// blocking through LDS).  Single-step kernels serve odd step counts
+// Default path: several fine steps per launch, temporally blocked -- strips of
+// columns for large patches (stream_kernels.hip), else tiles in LDS
+// (lbm_sweep2_kernel .. lbm_sweep5_kernel).  Single-step kernels serve odd step counts
 // (lbm_sweep_kernel, perimeter Dirichlet slots in the same launch) and
 // handles with Neumann slots (lbm_bulk_kernel + lbm_perimeter_kernel, whose
 // FP64 Newton solve would otherwise lower the occupancy of the sweep).
-#include "hyb_impl.h"
+#include "lbm_device.h"
 
 #include <type_traits>
 
 namespace hyb {
 namespace {
-
-// BGK collision with reaction, written as
-//   f*_i = (1 - w) f_i + w_i [ w u (1 + 3 e.v + 9/2 (e.v)^2 - 3/2 v.v) - k u ],
-// w = 1/tau; u = sum_i f_i (eq. LBM_Macro); the bracket's polynomial is the
-// equilibrium of eq. (LBM_feq) with c_s^2 = 1/3 and the quadratic term read
-// as -v.v/(2 c_s^2).  Returns u.
-template <typename T>
-__device__ __forceinline__ T collide(T (&f)[kQ], T vx, T vy, T omega, T k) {
-    const T u = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7])) + f[8];
-    const T A = omega * u;
-    const T base = A * (T(1) - T(1.5) * (vx * vx + vy * vy)) - k * u;
-    const T keep = T(1) - omega;
-    const T c3 = T(3) * A;
-    const T c45 = T(4.5) * A;
-    const T w0 = T(kW[0]), w1 = T(kW[1]), w5 = T(kW[5]);
-    const T dpp = vx + vy, dmp = vy - vx;   // e.v of (+,+) and (-,+)
-    f[0] = keep * f[0] + w0 * base;
-    f[1] = keep * f[1] + w1 * (base + c3 * vx + c45 * vx * vx);
-    f[3] = keep * f[3] + w1 * (base - c3 * vx + c45 * vx * vx);
-    f[2] = keep * f[2] + w1 * (base + c3 * vy + c45 * vy * vy);
-    f[4] = keep * f[4] + w1 * (base - c3 * vy + c45 * vy * vy);
-    f[5] = keep * f[5] + w5 * (base + c3 * dpp + c45 * dpp * dpp);
-    f[7] = keep * f[7] + w5 * (base - c3 * dpp + c45 * dpp * dpp);
-    f[6] = keep * f[6] + w5 * (base + c3 * dmp + c45 * dmp * dmp);
-    f[8] = keep * f[8] + w5 * (base - c3 * dmp + c45 * dmp * dmp);
-    return u;
-}
-
-__device__ __forceinline__ bool finite_val(double x) { return x - x == 0.0; }
-__device__ __forceinline__ bool finite_val(float x) { return x - x == 0.0f; }
-
-// Adds the number of active lanes whose flag is set to *ctr with one atomic
-// per wavefront (the one-node-per-thread kernels).
-__device__ __forceinline__ void count_lanes(unsigned long long *ctr, bool flag) {
-    const unsigned long long lanes = __ballot(flag);
-    if (lanes == 0ull) return;
-    if (__lane_id() == __ffsll(static_cast<long long>(lanes)) - 1) atomicAdd(ctr, static_cast<unsigned long long>(__popcll(lanes)));
-}
-
-// Event counts of one lane over a whole multi-step launch.  At the patch
-// edge a wavefront holds one perimeter node per round, so per-wavefront
-// aggregation still leaves one atomic per event; and device-scope atomics
-// on one address, issued from every XCD, serialise at the memory side and
-// hold up the sweep's own loads and stores there.  The sweeps therefore
-// count in registers and add to the device counters once per workgroup.
-struct Tally {
-    unsigned bad = 0u;          // infeasible closures at owned perimeter nodes
-    unsigned nonfinite = 0u;    // owned nodes whose concentration is not finite
-};
-
-__device__ __forceinline__ unsigned wave_sum(unsigned v) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-    return v;
-}
-
-// Adds a workgroup's tallies to the device counters.  `edge` is uniform
-// over the workgroup (whether the tile with its ring reaches the patch
-// perimeter) and false where no closure ran, so only edge tiles take the
-// extra barrier; a non-finite value is rare enough to count per wavefront.
-template <int NT>
-__device__ __forceinline__ void flush_tally(const LbmArgs &a, const Tally &t, bool edge) {
-    if (__ballot(t.nonfinite != 0u) != 0ull) {
-        const unsigned s = wave_sum(t.nonfinite);
-        if (__lane_id() == 0) atomicAdd(&a.counters[kCntNonfinite], static_cast<unsigned long long>(s));
-    }
-    if (edge) {
-        __shared__ unsigned part[NT / 64];
-        const unsigned s = wave_sum(t.bad);
-        if (__lane_id() == 0) part[threadIdx.x / 64] = s;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            unsigned long long sum = 0ull;
-#pragma unroll
-            for (int w = 0; w < NT / 64; ++w) sum += part[w];
-            if (sum != 0ull) atomicAdd(&a.counters[kCntInfeasible], sum);
-        }
-    }
-}
 
 // Address of the value a node pulls along q from an LDS stage: the upstream
 // slot `pull` or, where the upstream node is solid (flag bit q set), the
@@ -121,66 +43,6 @@ __device__ __forceinline__ const T *pull_or_back(const T *node, unsigned m, int 
                                        __mul24(bit, (back - pull) * sz));
 }
 
-// per-node reaction rate (k field in the arithmetic type) or the uniform one
-template <typename T>
-__device__ __forceinline__ T node_k(const LbmArgs &a, int n) {
-    return a.kfield ? static_cast<const T *>(a.kfield)[n] : T(a.k);
-}
-
-// Perimeter slot of perimeter node (i, j) (inverse of slot_to_node).
-__device__ __forceinline__ int perimeter_slot(int N, int i, int j) {
-    if (j == 0) return i;
-    if (j == N - 1) return N + i;
-    if (i == 0) return 2 * N + j - 1;
-    return 3 * N - 2 + j - 1;
-}
-
-// bit q set: the upstream node x - e_q lies outside the patch
-__device__ __forceinline__ unsigned outside_bits(int N, int i, int j) {
-    unsigned u = 0;
-#pragma unroll
-    for (int q = 1; q < kQ; ++q) {
-        const int si = i - kCx[q], sj = j - kCy[q];
-        if (si < 0 || si >= N || sj < 0 || sj >= N) u |= 1u << q;
-    }
-    return u;
-}
-
-// Dirichlet closure of eq. (LBM_Dir): the unknowns U share the mass deficit
-// R = u^p - sum_known f in proportion to w_i; sums in FP64.  u^p is the
-// eq. (MTS) value (1 - lam) a + lam b of slot p.  R < 0 (no non-negative
-// solution) is reported; with clamp the unknowns become 0, otherwise the
-// closed form is kept.
-template <typename T>
-__device__ __forceinline__ bool dirichlet_close(const LbmArgs &a, T (&f)[kQ], unsigned unknown, int p,
-                                                double lam) {
-    double known = 0.0, wsum = 0.0;
-#pragma unroll
-    for (int q = 0; q < kQ; ++q) {
-        if ((unknown >> q) & 1u) wsum += kW[q];
-        else known += double(f[q]);
-    }
-    double R = (1.0 - lam) * a.bc_a[p] + lam * a.bc_b[p] - known;
-    const bool bad = R < 0.0;
-    if (bad && a.clamp) R = 0.0;
-    const double scale = R / wsum;
-#pragma unroll
-    for (int q = 0; q < kQ; ++q)
-        if ((unknown >> q) & 1u) f[q] = T(kW[q] * scale);
-    return bad;
-}
-
-// Workgroups are handed to the 8 XCDs (each with its own L2) in
-// round-robin order.  Tile t of T is given to workgroup b so that XCD b % 8
-// sweeps one contiguous eighth of the tiles in row-major order: the lines a
-// tile shares with its neighbours (pulls, halos) are then fetched into the
-// same L2.
-__device__ __forceinline__ int xcd_tile(int b, int T) {
-    const int x = b & 7, k = b >> 3;
-    const int q = T >> 3, r = T & 7;
-    return x * q + (x < r ? x : r) + k;
-}
-
 // Whether the region of rows y0 - r .. y0 + h - 1 + r and columns x0 - r ..
 // x0 + w - 1 + r reaches the patch perimeter (uniform across a workgroup:
 // the per-node perimeter test only runs in tiles where it can hold).
@@ -191,15 +53,6 @@ __device__ __forceinline__ bool reaches_perimeter(int N, int x0, int y0, int w, 
 // ---------------------------------------------------------------------------
 // Single fine step
 // ---------------------------------------------------------------------------
-
-// Bounce-back value across a link to a solid node with the surface reaction
-// of dissolving solids: (1 - kappa_s) f + kappa_s w_q c_sat (f itself when
-// the reaction is off).
-template <typename T>
-__device__ __forceinline__ T reactive(const LbmArgs &a, T f, int q) {
-    if (a.kappa_s == 0.0) return f;
-    return T((1.0 - a.kappa_s) * double(f) + a.kappa_s * kW[q] * a.c_sat);
-}
 
 // Solid node n with fluid neighbours (flag bits q): the mass its reactive
 // links move into the fluid during this step, sum over q of
@@ -494,42 +347,6 @@ __global__ void __launch_bounds__(128) lbm_perimeter_kernel(LbmArgs a) {
 // HBM traffic for two steps is one read of the state (the ring-2 halo is
 // mostly served by L2) and one write.
 // ---------------------------------------------------------------------------
-
-// Raw buffer access (gfx9 buffer instructions): the array base and size
-// live in one SGPR resource and each lane supplies a 32-bit byte offset
-// (stores add the plane offset q * plane as the scalar offset), so a pull
-// or a store costs no 64-bit address arithmetic.  Offsets at or past
-// num_records read as 0 without touching memory.
-typedef __amdgpu_buffer_rsrc_t BufRsrc;
-__device__ __forceinline__ BufRsrc buf_rsrc(const void *p, unsigned bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)0, (int)bytes, 0x00020000);
-}
-template <typename S> struct Buf;
-template <> struct Buf<float> {
-    static __device__ __forceinline__ float load(BufRsrc r, unsigned v, unsigned s) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, v, s, 0));
-    }
-    static __device__ __forceinline__ void store_nt(float x, BufRsrc r, unsigned v, unsigned s) {
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), r, v, s, 2);
-    }
-};
-template <> struct Buf<double> {
-    typedef decltype(__builtin_amdgcn_raw_buffer_load_b64(BufRsrc(), 0, 0, 0)) Raw;
-    static __device__ __forceinline__ double load(BufRsrc r, unsigned v, unsigned s) {
-        return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, v, s, 0));
-    }
-    static __device__ __forceinline__ void store_nt(double x, BufRsrc r, unsigned v, unsigned s) {
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(Raw, x), r, v, s, 2);
-    }
-};
-template <> struct Buf<_Float16> {
-    static __device__ __forceinline__ _Float16 load(BufRsrc r, unsigned v, unsigned s) {
-        return __builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r, v, s, 0));
-    }
-    static __device__ __forceinline__ void store_nt(_Float16 x, BufRsrc r, unsigned v, unsigned s) {
-        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, x), r, v, s, 2);
-    }
-};
 
 // Which tiles a two-step launch covers: all of the tiles_x x tiles_y grid
 // (part 0), a rectangle [ix0, ix1] x [iy0, iy1] of tiles (part 1), or the
@@ -1354,8 +1171,19 @@ hipError_t step2_impl(const LbmArgs &a, int part, int depth, int ring, hipStream
 // cut the sweep time per pass by 4.6% against the two-step launches.
 template <typename S> struct Tile3 { static constexpr int TW = 64, TH = 8, NT = 512; };
 
+// Whether the deep rectangle of a K-step launch goes to the strip kernel
+// (stream_kernels.hip) and only the frame of tiles around it to the tile kernel.
+// The strips recompute 2K rows per band and need some 800 workgroups, so small
+// rectangles leave their bands short.  Measured per four-step launch, frame
+// included, tiles against strips: 1200^2 FP64 70.5 / 75.2 us, FP32 45.7 / 50.0,
+// binary16 43.8 / 47.8; 1501^2 FP64 110.6 / 100.7; 1800^2 FP32 87.0 / 76.1;
+// 4096^2 FP64 757 / 582, FP32 455 / 323, binary16 390 / 228.
+bool stream_pays(const NodeRect &r) {
+    return (double)(r.x1 - r.x0 + 1) * (double)(r.y1 - r.y0 + 1) >= 1.5e6;
+}
+
 template <typename S, int K>
-hipError_t stepk_impl(const LbmArgs &a, int part, int depth, int ring, hipStream_t s) {
+hipError_t stepk_impl(const LbmArgs &a, int prec, int part, int depth, int ring, hipStream_t s) {
     constexpr int TW = Tile3<S>::TW, TH = Tile3<S>::TH, NT = Tile3<S>::NT;
     TileMap m{};
     m.tiles_x = (a.N + TW - 1) / TW;
@@ -1382,6 +1210,14 @@ hipError_t stepk_impl(const LbmArgs &a, int part, int depth, int ring, hipStream
     m.count = m.part == 0 ? all : m.part == 1 ? inner : all - inner;
     if (m.count == 0) return hipSuccess;
     if (a.mid) return hipErrorInvalidValue;
+    const NodeRect deep{m.ix0 * TW, (m.ix1 + 1) * TW - 1, m.iy0 * TH, (m.iy1 + 1) * TH - 1};
+    if (m.part != 2 && has_rect && !(a.flux || a.kappa_s != 0.0) && stream_pays(deep)) {
+        const hipError_t e = launch_lbm_stream(a, prec, K, deep, s);
+        if (e != hipSuccess || m.part == 1) return e;
+        m.part = 2;
+        m.count = all - inner;
+        if (m.count == 0) return hipSuccess;
+    }
     if (a.flux || a.kappa_s != 0.0) {
         // dissolving solids: whole-patch launches only
         if (m.part != 0) return hipErrorInvalidValue;
@@ -1405,19 +1241,19 @@ hipError_t stepk_impl(const LbmArgs &a, int part, int depth, int ring, hipStream
 }
 
 template <typename S>
-hipError_t stepk_dispatch(const LbmArgs &a, int K, int part, int depth, int ring, hipStream_t s) {
-    if (K == 3) return stepk_impl<S, 3>(a, part, depth, ring, s);
-    if (K == 4) return stepk_impl<S, 4>(a, part, depth, ring, s);
-    if (K == 5) return stepk_impl<S, 5>(a, part, depth, ring, s);
+hipError_t stepk_dispatch(const LbmArgs &a, int prec, int K, int part, int depth, int ring, hipStream_t s) {
+    if (K == 3) return stepk_impl<S, 3>(a, prec, part, depth, ring, s);
+    if (K == 4) return stepk_impl<S, 4>(a, prec, part, depth, ring, s);
+    if (K == 5) return stepk_impl<S, 5>(a, prec, part, depth, ring, s);
     return hipErrorInvalidValue;
 }
 
 }  // namespace
 
 hipError_t launch_lbm_stepk(const LbmArgs &a, int prec, int K, hipStream_t s, int part, int depth, int ring) {
-    if (prec == HYB_FP32) return stepk_dispatch<float>(a, K, part, depth, ring, s);
-    if (prec == HYB_FP16S) return stepk_dispatch<_Float16>(a, K, part, depth, ring, s);
-    if (prec == HYB_FP64) return stepk_dispatch<double>(a, K, part, depth, ring, s);
+    if (prec == HYB_FP32) return stepk_dispatch<float>(a, prec, K, part, depth, ring, s);
+    if (prec == HYB_FP16S) return stepk_dispatch<_Float16>(a, prec, K, part, depth, ring, s);
+    if (prec == HYB_FP64) return stepk_dispatch<double>(a, prec, K, part, depth, ring, s);
     return hipErrorInvalidValue;
 }
 

@@ -1,0 +1,335 @@
+// K fine steps per launch (K = 3 .. 5) on a rectangle of nodes clear of the
+// patch perimeter, one wavefront per strip of columns.
+//
+// A wavefront owns a strip of 64 - 2K columns (its 64 lanes less K ring
+// columns on each side) and a band of rows, and walks up the rows with all K
+// steps in flight: when row r of the source state has arrived, step 1 finishes
+// row r-1, step 2 row r-2, .. step K row r-K, which is stored.  A pull from a
+// neighbouring column is a lane shift (DPP), one from a neighbouring row reads
+// registers, so the state between the steps needs no LDS and no barrier, and
+// wavefronts never wait for each other.
+//
+// What a step keeps of the rows below (nine values): when row r of its input
+// is there, directions 0, 1, 3 (same row) and 2, 5, 6 (row r-1) of row r can be
+// gathered and bounced back at once; 4, 7, 8 pull from row r+1 and bounce back
+// 2, 5, 6 of row r, which row r+1 pulls anyway.
+//
+// Bound: FP64 by HBM (the state read and written once, 2.6 GB at 4096^2 in
+// about 550 us: 4.7 TB/s of the 4.9 a large copy reaches), FP32 and binary16 by
+// VALU issue (about 80 instructions per node and step; a build without stores
+// took 250 us of FP32's 300).  Per four-step launch at 4096^2, porosity 0.6, with
+// the frame of tiles (about 28 us): FP64 582 us, FP32 323, binary16 228; the
+// LDS tiles, bound by latency at the occupancy their tile allows, took 757, 455
+// and 390.
+#include "lbm_device.h"
+
+#include <type_traits>
+
+namespace hyb {
+namespace {
+
+// dst lane i takes lane i-1 (from_left) or i+1 (from_right); lanes without a
+// source take 0 (ring lanes, whose results are not used)
+__device__ __forceinline__ float lane_from_left(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_from_right(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x130, 0xf, 0xf, true));
+}
+struct TwoWords {
+    int lo, hi;
+};
+__device__ __forceinline__ double lane_from_left(double x) {
+    TwoWords w = __builtin_bit_cast(TwoWords, x);
+    w.lo = __builtin_amdgcn_update_dpp(0, w.lo, 0x138, 0xf, 0xf, true);
+    w.hi = __builtin_amdgcn_update_dpp(0, w.hi, 0x138, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, w);
+}
+__device__ __forceinline__ double lane_from_right(double x) {
+    TwoWords w = __builtin_bit_cast(TwoWords, x);
+    w.lo = __builtin_amdgcn_update_dpp(0, w.lo, 0x130, 0xf, 0xf, true);
+    w.hi = __builtin_amdgcn_update_dpp(0, w.hi, 0x130, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, w);
+}
+
+// back where bit q of m is set, else pull.  The bit is widened to a word mask
+// and the words merged (one v_bfe_i32, one v_bfi_b32 per word); the empty asm
+// keeps the compiler from turning that back into a compare and a select.
+__device__ __forceinline__ int bit_mask(unsigned m, int q) {
+    int s = __builtin_amdgcn_sbfe(static_cast<int>(m), q, 1);
+    asm("" : "+v"(s));
+    return s;
+}
+__device__ __forceinline__ float back_or_pull(unsigned m, int q, float back, float pull) {
+    const int s = bit_mask(m, q);
+    const int b = __builtin_bit_cast(int, back), p = __builtin_bit_cast(int, pull);
+    return __builtin_bit_cast(float, (s & b) | (~s & p));
+}
+__device__ __forceinline__ double back_or_pull(unsigned m, int q, double back, double pull) {
+    const int s = bit_mask(m, q);
+    const TwoWords b = __builtin_bit_cast(TwoWords, back), p = __builtin_bit_cast(TwoWords, pull);
+    const TwoWords o = {(s & b.lo) | (~s & p.lo), (s & b.hi) | (~s & p.hi)};
+    return __builtin_bit_cast(double, o);
+}
+
+// Wavefronts per SIMD the register budget is set for, and rows taken per turn
+// of the row loop.  Two rows a turn spare the copies that return what a step
+// keeps to the registers the loop starts with (a tenth of the instructions) for
+// a quarter more registers: 4096^2, four steps, binary16 236 us against 252
+// with one row and five wavefronts, FP32 329 against 335; FP64 would spill.
+template <typename S, int K>
+constexpr bool two_rows() { return sizeof(S) < 8 && K <= 4; }
+template <typename S, int K>
+constexpr int stream_waves_per_simd() { return sizeof(S) == 8 ? (K <= 4 ? 3 : 2) : 4; }
+
+// The nodes of a launch, cut into strips of 64 - 2K columns and bands of rows;
+// a workgroup is four neighbouring strips of one band.
+struct StreamMap {
+    NodeRect nodes;
+    int strips, groups_x, rows;             // rows per band
+    int count;                              // workgroups
+};
+
+constexpr int kStreamWaves = 4;
+constexpr int kComputeUnits = 256;
+constexpr int kNonTemporal = 2;          // cache policy bit of the buffer store
+typedef unsigned Quad __attribute__((ext_vector_type(4)));
+
+template <typename S, int K, bool KF>
+__global__ void __launch_bounds__(64 * kStreamWaves, (stream_waves_per_simd<S, K>())) lbm_stream_kernel(LbmArgs a, StreamMap map) {
+    typedef typename Pop<S>::T T;
+    constexpr int UNR = two_rows<S, K>() ? 2 : 1;
+    constexpr int OW = 64 - 2 * K;
+    constexpr unsigned sz = sizeof(S), tsz = sizeof(T);
+    const int t = xcd_tile(blockIdx.x, map.count);
+    const int strip = (t % map.groups_x) * kStreamWaves + __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    // wavefronts past the last strip run along (the workgroup's barriers count
+    // on them) on the last strip's columns
+    const int xs = map.nodes.x0 + (strip < map.strips ? strip : map.strips - 1) * OW, y0 = map.nodes.y0 + (t / map.groups_x) * map.rows;
+    const int yend = y0 + map.rows < map.nodes.y1 + 1 ? y0 + map.rows : map.nodes.y1 + 1;
+    const unsigned P = static_cast<unsigned>(a.pitch), SP = static_cast<unsigned>(a.plane);
+    const unsigned NP = static_cast<unsigned>(a.N) * P;
+    const BufRsrc fsrc = buf_rsrc(a.src, kQ * SP * sz);
+    const BufRsrc fdst = buf_rsrc(a.dst, kQ * SP * sz);
+    const BufRsrc mrs = buf_rsrc(a.mask, NP * 2u);
+    const BufRsrc vxr = buf_rsrc(a.vx, NP * 4u);
+    const BufRsrc vyr = buf_rsrc(a.vy, NP * 4u);
+    const BufRsrc kfr = buf_rsrc(KF ? a.kfield : a.vx, NP * tsz);
+    const T omega = T(a.omega);
+    const T kuni = T(a.k);
+    const int lane = __lane_id();
+    // lanes past the rectangle read the row's remainder (or the next row, still
+    // inside the plane) and are not stored
+    const unsigned i = static_cast<unsigned>(xs - K + lane);
+    const bool owned = lane >= K && lane < K + OW && static_cast<int>(i) <= map.nodes.x1 && strip < map.strips;
+    const unsigned long long owned_lanes = __builtin_amdgcn_ballot_w64(owned);
+    const int rend = y0 - K + ((yend - y0 + 2 * K + UNR - 1) / UNR) * UNR;     // rows taken: a multiple of UNR
+    unsigned nonfinite = 0u;
+
+    // A finished row leaves through LDS: the four strips' columns together are
+    // whole 128-byte lines (FP16S: half lines), stored 16 bytes a lane.  (Rows
+    // stored by each wavefront alone begin and end inside lines; full-width
+    // lines half as wide were faster than that.)
+    constexpr int GW = OW * kStreamWaves, NT = 64 * kStreamWaves, CHUNK = 16 / sz, PER = GW / CHUNK;
+    constexpr int ROUNDS_OUT = (kQ * PER + NT - 1) / NT;
+    static_assert(GW % CHUNK == 0, "whole chunks");
+    __shared__ __align__(16) S rows_out[2][kQ * GW];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    unsigned out_at[ROUNDS_OUT];
+    bool out_on[ROUNDS_OUT];
+    {
+        const int gx0 = map.nodes.x0 + (t % map.groups_x) * GW;
+#pragma unroll
+        for (int c = 0; c < ROUNDS_OUT; ++c) {
+            const int chunk = static_cast<int>(threadIdx.x) + NT * c, q = chunk / PER, col = gx0 + (chunk % PER) * CHUNK;
+            out_on[c] = chunk < kQ * PER && col <= map.nodes.x1;
+            out_at[c] = (q * SP + static_cast<unsigned>(col)) * sz;
+        }
+    }
+
+    struct Row {
+        S f[kQ];
+        unsigned m;
+        float vx, vy;
+        T k;
+    };
+    auto fetch = [&](int r, Row &w) {
+        const unsigned at = static_cast<unsigned>(r) * P;
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) w.f[q] = Buf<S>::load(fsrc, i * sz, (q * SP + at) * sz);
+        w.m = __builtin_amdgcn_raw_buffer_load_b16(mrs, i * 2u, at * 2u, 0);
+        w.vx = Buf<float>::load(vxr, i * 4u, at * 4u);
+        w.vy = Buf<float>::load(vyr, i * 4u, at * 4u);
+        if constexpr (KF) w.k = Buf<T>::load(kfr, i * tsz, at * tsz);
+    };
+
+    // per step s+1: gathered directions 0, 1, 3, 2, 5, 6 of the row it works
+    // on, and directions 2, 5, 6 of that row of its input
+    T part[K][6], own[K][3];
+#pragma unroll
+    for (int s = 0; s < K; ++s) {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) part[s][c] = T(0);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) own[s][c] = T(0);
+    }
+    // flag words, owned fluid lanes, velocities and rates of the last K+1 rows
+    unsigned mk[K + 1];
+    unsigned long long live[K + 1];
+    float vx[K + 1], vy[K + 1];
+    T kn[K + 1];
+#pragma unroll
+    for (int d = 0; d <= K; ++d) {
+        mk[d] = kMaskSolid;
+        live[d] = 0ull;
+        vx[d] = vy[d] = 0.f;
+        kn[d] = kuni;
+    }
+
+    Row next;
+    fetch(y0 - K, next);
+    auto row = [&](int r) {
+        __builtin_amdgcn_sched_barrier(0);
+        T g[kQ];
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) g[q] = Pop<S>::ld(next.f[q], q, a);
+        mk[0] = next.m;
+        live[0] = __builtin_amdgcn_ballot_w64(!(next.m & kMaskSolid)) & owned_lanes;
+        vx[0] = next.vx;
+        vy[0] = next.vy;
+        if constexpr (KF) kn[0] = next.k;
+        fetch(r + 1 < rend ? r + 1 : r, next);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < K; ++s) {
+            // finish row r-s-1 of step s+1
+            const unsigned m = mk[s + 1], mn = mk[s];
+            T f[kQ];
+            f[0] = part[s][0];
+            f[1] = part[s][1];
+            f[3] = part[s][2];
+            f[2] = part[s][3];
+            f[5] = part[s][4];
+            f[6] = part[s][5];
+            f[4] = back_or_pull(m, 4, own[s][0], g[4]);
+            f[7] = back_or_pull(m, 7, own[s][1], lane_from_right(g[7]));
+            f[8] = back_or_pull(m, 8, own[s][2], lane_from_left(g[8]));
+            // gather what row r-s has
+            part[s][0] = g[0];
+            part[s][1] = back_or_pull(mn, 1, g[3], lane_from_left(g[1]));
+            part[s][2] = back_or_pull(mn, 3, g[1], lane_from_right(g[3]));
+            part[s][3] = back_or_pull(mn, 2, g[4], own[s][0]);
+            part[s][4] = back_or_pull(mn, 5, g[7], lane_from_left(own[s][1]));
+            part[s][5] = back_or_pull(mn, 6, g[8], lane_from_right(own[s][2]));
+            own[s][0] = g[2];
+            own[s][1] = g[5];
+            own[s][2] = g[6];
+            // made here and now: left to itself the compiler defers these
+            // selects to the end of the row and carries their operands (twice
+            // the registers) through the later steps
+#pragma unroll
+            for (int c = 0; c < 6; ++c) asm volatile("" : "+v"(part[s][c]));
+#pragma unroll
+            for (int c = 0; c < 3; ++c) asm volatile("" : "+v"(own[s][c]));
+            const T u = collide<T>(f, T(vx[s + 1]), T(vy[s + 1]), omega, KF ? kn[s + 1] : kuni);
+            const int j = r - s - 1;
+            const unsigned long long nf = __builtin_amdgcn_ballot_w64(!__builtin_isfinite(u)) & live[s + 1];
+            nonfinite += j >= y0 && j < yend ? static_cast<unsigned>(__popcll(nf)) : 0u;
+#pragma unroll
+            for (int q = 0; q < kQ; ++q) g[q] = f[q];
+            // keep the scheduler from starting every step's selects at once
+            // (their masks alone would take eight registers a step)
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // The next row has to be here before this one is stored: the counter
+        // the loads are waited on also counts stores, so a wait after them
+        // would wait for them too.
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) asm volatile("" : "+v"(next.f[q]));
+        asm volatile("" : "+v"(next.m), "+v"(next.vx), "+v"(next.vy));
+        if constexpr (KF) asm volatile("" : "+v"(next.k));
+        __builtin_amdgcn_sched_barrier(0);
+        // row r-K has taken all K steps
+        const int j = r - K;
+        if (j >= y0 && j < yend) {
+            S *out = rows_out[j & 1];
+            if (lane >= K && lane < K + OW) {
+#pragma unroll
+                for (int q = 0; q < kQ; ++q) out[q * GW + wave * OW + lane - K] = Pop<S>::st(g[q], q, a);
+            }
+            // one barrier a row: a row's buffer is written again two rows on,
+            // after the barrier that follows its last read
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            const unsigned at = static_cast<unsigned>(j) * P * sz;
+#pragma unroll
+            for (int c = 0; c < ROUNDS_OUT; ++c)
+                if (out_on[c]) {
+                    const Quad v = *reinterpret_cast<const Quad *>(out + (threadIdx.x + NT * c) * CHUNK);
+                    __builtin_amdgcn_raw_buffer_store_b128(v, fdst, out_at[c], at, kNonTemporal);
+                }
+        }
+#pragma unroll
+        for (int d = K; d > 0; --d) {
+            mk[d] = mk[d - 1];
+            live[d] = live[d - 1];
+            vx[d] = vx[d - 1];
+            vy[d] = vy[d - 1];
+            kn[d] = kn[d - 1];
+            // (no values derived from these are kept from one step of a node
+            // to its next: they would not fit the registers)
+            asm volatile("" : "+v"(mk[d]), "+v"(vx[d]), "+v"(vy[d]));
+        }
+    };
+#pragma unroll 1
+    for (int r = y0 - K; r < rend; r += UNR) {
+#pragma unroll
+        for (int n = 0; n < UNR; ++n) row(r + n);
+    }
+    if (nonfinite && lane == 0) atomicAdd(&a.counters[kCntNonfinite], static_cast<unsigned long long>(nonfinite));
+}
+
+template <typename S, int K>
+hipError_t stream_impl(const LbmArgs &a, const NodeRect &nodes, hipStream_t s) {
+    constexpr int OW = 64 - 2 * K;
+    StreamMap m{};
+    m.nodes = nodes;
+    m.strips = (nodes.x1 - nodes.x0 + OW) / OW;
+    m.groups_x = (m.strips + kStreamWaves - 1) / kStreamWaves;
+    const int h = nodes.y1 - nodes.y0 + 1;
+    // bands: as many workgroups as are resident at once, so that none starts
+    // late with a whole band before it (4096^2 FP32: 335 us; two rounds of them
+    // 351; bands of 16 rows 357, which recompute 2K rows each)
+    const int slots = kComputeUnits * stream_waves_per_simd<S, K>();
+    const int bands = slots / m.groups_x > 1 ? slots / m.groups_x : 1;
+    m.rows = (h + bands - 1) / bands;
+    if (m.rows < 4) m.rows = 4;
+    m.count = m.groups_x * ((h + m.rows - 1) / m.rows);
+    const dim3 grid(m.count), block(64 * kStreamWaves);
+    if (a.kfield) hipLaunchKernelGGL((lbm_stream_kernel<S, K, true>), grid, block, 0, s, a, m);
+    else hipLaunchKernelGGL((lbm_stream_kernel<S, K, false>), grid, block, 0, s, a, m);
+    return hipGetLastError();
+}
+
+template <typename S>
+hipError_t stream_steps(const LbmArgs &a, int K, const NodeRect &nodes, hipStream_t s) {
+    if (K == 3) return stream_impl<S, 3>(a, nodes, s);
+    if (K == 4) return stream_impl<S, 4>(a, nodes, s);
+    if (K == 5) return stream_impl<S, 5>(a, nodes, s);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+hipError_t launch_lbm_stream(const LbmArgs &a, int prec, int K, const NodeRect &nodes, hipStream_t s) {
+    if (a.flux || a.kappa_s != 0.0 || a.mid || a.u_out) return hipErrorInvalidValue;
+    if (nodes.x1 < nodes.x0 || nodes.y1 < nodes.y0) return hipSuccess;
+    // every pull of every step stays inside the patch and off its perimeter nodes
+    if (nodes.x0 < K || nodes.y0 < K || nodes.x1 > a.N - 1 - K || nodes.y1 > a.N - 1 - K) return hipErrorInvalidValue;
+    if (prec == HYB_FP64) return stream_steps<double>(a, K, nodes, s);
+    if (prec == HYB_FP32) return stream_steps<float>(a, K, nodes, s);
+    return stream_steps<_Float16>(a, K, nodes, s);
+}
+
+}  // namespace hyb
