@@ -181,7 +181,12 @@ int hyb_lbm_substeps(hyb_handle *h, int n_sub, int restart);
 int hyb_commit(hyb_handle *h);
 
 /* Algorithm 1 for one coarse step: max_schwarz times {F2C exchange, coarse
- * step, C2F exchange, eta fine steps from f*(t_n)}, then commit. */
+ * step, C2F exchange, eta fine steps from f*(t_n)}, then commit.  The passes
+ * start from the same state and differ in the interface values only, which eta
+ * fine steps carry eta nodes into the patch; with at most two multi-step
+ * launches a pass (hyb_set_steps_per_launch) the passes after the first sweep
+ * that frame and share the first one's state inside it.  States, counts and
+ * errors are those of the separate calls, bit for bit. */
 int hyb_step(hyb_handle *h, int max_schwarz);
 
 /* Lattice-only use and tests: per-slot closure kind (HYB_BC_*, NULL = all
@@ -336,8 +341,8 @@ int hyb_step_adjoint(hyb_handle *h, const void *tape, const double *lam_f, const
                      double *lam_f_out, double *lam_d_out, double *grad_k, double *grad_outer);
 
 /* Overlap in hyb_step (default HYB_OVERLAP_AUTO): with multi-step
- * launches (hyb_set_steps_per_launch), the deep interior tiles of each
- * Schwarz pass's first `depth` launches run on a second stream owned by the
+ * launches (hyb_set_steps_per_launch), the deep interior tiles of the first
+ * `depth` launches of each Schwarz pass that sweeps the whole patch run on a second stream owned by the
  * handle while the pass's fine-to-coarse transfer, coarse solve and
  * coarse-to-fine transfer run on the caller's stream; the remaining tiles
  * follow on the caller's stream.  Launch j (j = 0 .. depth-1, its fine

@@ -278,6 +278,7 @@ struct hyb_handle {
     int solve_budget = 0, solve_cap = 0;
     long long coarse_steps = 0, fine_steps = 0;
     unsigned long long seen_nonfinite = 0;
+    unsigned long long shared_nonfinite = 0;   // counted in the first pass for later ones too
     // kernel timing (measurement only)
     bool timing = false;
     std::vector<hipEvent_t> ev_pool;       // pairs: [2k] begin, [2k+1] end
@@ -331,6 +332,24 @@ struct hyb_handle {
             timed_launches += ev_launches[k];
         }
         ev_used = 0;
+        return hipSuccess;
+    }
+
+    // the next pair of timing events
+    hipError_t take_event_pair(hipEvent_t *e0, hipEvent_t *e1) {
+        if (2 * (ev_used + 1) > ev_pool.size()) {
+            for (int k = 0; k < 2; ++k) {
+                hipEvent_t e;
+                hipError_t er = hipEventCreate(&e);
+                if (er != hipSuccess) return er;
+                ev_pool.push_back(e);
+            }
+            ev_launches.push_back(0);
+        }
+        *e0 = ev_pool[2 * ev_used];
+        *e1 = ev_pool[2 * ev_used + 1];
+        ev_launches[ev_used] = 0;
+        ev_used += 1;
         return hipSuccess;
     }
 
@@ -811,14 +830,102 @@ int overlap_dmax(const hyb_handle *h) {
 // One multi-step launch of `take` fine steps (2, 3 or 4) from a.src to a.dst,
 // fine steps j0 + 1 .. j0 + take of the pass (interface weights (j0+1)/eta,
 // ...).
-hipError_t launch_fused(const hyb_handle *h, LbmArgs a, int j0, int take, hipStream_t s, int part, int depth) {
+hipError_t launch_fused(const hyb_handle *h, LbmArgs a, int j0, int take, hipStream_t s, int part, int depth,
+                        const NodeRect *hole = nullptr) {
     a.lam = (double)(j0 + 1) / (double)h->eta;
     a.lam2 = (double)(j0 + 2) / (double)h->eta;
     a.lam3 = (double)(j0 + 3) / (double)h->eta;
     a.lam4 = (double)(j0 + 4) / (double)h->eta;
     a.lam5 = (double)(j0 + 5) / (double)h->eta;
-    if (take >= 3) return launch_lbm_stepk(a, h->prec, take, s, part, depth, pass_ring(h));
-    return launch_lbm_step2(a, h->prec, s, part, depth, pass_ring(h));
+    if (take >= 3) return launch_lbm_stepk(a, h->prec, take, s, part, depth, pass_ring(h), hole);
+    return launch_lbm_step2(a, h->prec, s, part, depth, pass_ring(h), hole);
+}
+
+// The nodes a step's Schwarz passes have in common.  Every pass runs the same
+// eta fine steps from the frozen state and only its interface values differ;
+// those reach the nodes less than eta from the perimeter and no other, since a
+// fine step carries values one node further.  A later pass therefore sweeps the
+// frame that they reach and leaves the nodes inside it as the first pass left
+// them.  hole[j]: the nodes that launch j of a later pass need not write, whole
+// tiles -- all of those at the end of the pass, and before it fewer, by the ring
+// that the launches after it read.  Holds for up to two launches a pass: the
+// first of two then writes the buffer that does not hold the first pass's result,
+// the last one that which does.
+struct SharedNodes {
+    int launches = 0;                // 0: every pass sweeps the whole patch
+    int take[2] = {0, 0};
+    NodeRect hole[2] = {{0, -1, 0, -1}, {0, -1, 0, -1}};
+};
+SharedNodes shared_nodes(const hyb_handle *h) {
+    SharedNodes sh;
+    if (!use_two_step(h) || h->dissolve_on) return sh;
+    const int fuse = fuse_steps(h);
+    int n = 0;
+    for (int rem = h->eta; rem > 0; ++n) {
+        const int t = plan_take(fuse, rem);
+        if (n == 2 || t < 2) return sh;
+        sh.take[n] = t;
+        rem -= t;
+    }
+    const int d = h->eta;
+    NodeRect r = whole_tiles(NodeRect{d, h->N - 1 - d, d, h->N - 1 - d});
+    for (int j = n - 1; j >= 0; --j) {
+        if (r.x1 < r.x0 || r.y1 < r.y0) return sh;
+        sh.hole[j] = r;
+        const int k = sh.take[j];
+        r = whole_tiles(NodeRect{r.x0 + k, r.x1 - k, r.y0 + k, r.y1 - k});
+    }
+    sh.launches = n;
+    return sh;
+}
+
+// A later Schwarz pass on the frame: from the frozen state into the buffer that
+// holds the pass before it (h->cur).
+int substeps_frame(hyb_handle *h, const SharedNodes &sh) {
+    const int last = h->cur;
+    int src = h->frozen, j0 = 0;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (h->timing) {
+        HIP_TRY(h, h->take_event_pair(&e0, &e1));
+        h->ev_launches[h->ev_used - 1] = sh.launches;
+        HIP_TRY(h, hipEventRecord(e0, h->stream));
+    }
+    for (int j = 0; j < sh.launches; ++j) {
+        const int dst = j == sh.launches - 1 ? last : h->spare(last);
+        HIP_TRY(h, launch_fused(h, h->lbm_args(src, dst), j0, sh.take[j], h->stream, 2, 0, &sh.hole[j]));
+        src = dst;
+        j0 += sh.take[j];
+    }
+    if (e1) HIP_TRY(h, hipEventRecord(e1, h->stream));
+    h->jsub = h->eta;
+    h->fine_steps += h->eta;
+    return HYB_OK;
+}
+
+// Non-finite concentrations are counted at every node in every pass, so when a
+// step has met one, count those of the shared nodes again for each later pass:
+// sweep a pass as before (its interface values are still in place, so the state
+// stays the same), counting into slots of their own and keeping only the shared
+// nodes' count.  Runs only on the way to HYB_ENONFINITE.
+int count_shared_nonfinite(hyb_handle *h, const SharedNodes &sh, int later) {
+    const int last = h->cur;
+    HIP_TRY(h, hipMemsetAsync(h->counters + kCntRecount, 0, (kCntSlots - kCntRecount) * 8, h->stream));
+    int src = h->frozen, j0 = 0;
+    for (int j = 0; j < sh.launches; ++j) {
+        const int dst = j == sh.launches - 1 ? last : h->spare(last);
+        LbmArgs a = h->lbm_args(src, dst);
+        a.counters = h->counters + kCntThrown;
+        HIP_TRY(h, launch_fused(h, a, j0, sh.take[j], h->stream, 0, 0));
+        a.counters = h->counters + kCntRecount;
+        HIP_TRY(h, launch_fused(h, a, j0, sh.take[j], h->stream, 1, 0, &sh.hole[j]));
+        src = dst;
+        j0 += sh.take[j];
+    }
+    unsigned long long cnt[2];
+    HIP_TRY(h, hipMemcpyAsync(cnt, h->counters + kCntRecount, sizeof(cnt), hipMemcpyDeviceToHost, h->stream));
+    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    h->shared_nonfinite += (unsigned long long)later * cnt[kCntNonfinite];
+    return HYB_OK;
 }
 
 // the host copy of the solid flags after commits that may have converted
@@ -859,22 +966,6 @@ int substeps_impl(hyb_handle *h, int n_sub, int restart, int first_dst, int deep
     const bool timed = h->timing && h->N > 2 && n_sub > 0;
     const bool general = h->any_neumann || h->wall_on;
     const int fuse = fuse_steps(h);
-    auto take_pair = [&](hipEvent_t *e0, hipEvent_t *e1) -> hipError_t {
-        if (2 * (h->ev_used + 1) > h->ev_pool.size()) {
-            for (int k = 0; k < 2; ++k) {
-                hipEvent_t e;
-                hipError_t err = hipEventCreate(&e);
-                if (err != hipSuccess) return err;
-                h->ev_pool.push_back(e);
-            }
-            h->ev_launches.push_back(0);
-        }
-        *e0 = h->ev_pool[2 * h->ev_used];
-        *e1 = h->ev_pool[2 * h->ev_used + 1];
-        h->ev_launches[h->ev_used] = 0;
-        h->ev_used += 1;
-        return hipSuccess;
-    };
     hipEvent_t g0 = nullptr, g1 = nullptr;
     size_t gslot = 0;
     int launch = 0;
@@ -897,7 +988,7 @@ int substeps_impl(hyb_handle *h, int n_sub, int restart, int first_dst, int deep
         if (deep > 0 && launch >= 1 && launch <= deep)
             HIP_TRY(h, hipStreamWaitEvent(h->stream, h->ev_deep[launch - 1], 0));
         if (timed && !general && !g0 && !split_now) {
-            HIP_TRY(h, take_pair(&g0, &g1));
+            HIP_TRY(h, h->take_event_pair(&g0, &g1));
             gslot = h->ev_used - 1;
             HIP_TRY(h, hipEventRecord(g0, h->stream));
         }
@@ -906,7 +997,7 @@ int substeps_impl(hyb_handle *h, int n_sub, int restart, int first_dst, int deep
         } else {
             hipEvent_t e0 = nullptr, e1 = nullptr;
             if (timed && general) {
-                HIP_TRY(h, take_pair(&e0, &e1));
+                HIP_TRY(h, h->take_event_pair(&e0, &e1));
                 h->ev_launches[h->ev_used - 1] = 1;
             }
             HIP_TRY(h, launch_lbm_step(a, h->prec, general, h->stream, e0, e1));
@@ -1065,12 +1156,22 @@ int hyb_step(hyb_handle *h, int max_schwarz) {
     int rc = HYB_OK;
     // a pass of one multi-step launch (eta fine steps in one launch)
     const bool one_launch = fuse_steps(h) >= 2 && plan_take(fuse_steps(h), h->eta) == h->eta;
+    const SharedNodes sh = max_schwarz > 1 ? shared_nodes(h) : SharedNodes();
     for (int attempt = 0; attempt < 2; ++attempt) {
         h->cur = h->frozen;
         h->jsub = 0;
         h->solved_this_step = false;
         const int deep = depth;
         for (int it = 0; it < max_schwarz; ++it) {
+            if (it > 0 && sh.launches > 0) {
+                // the pass before left the shared nodes in h->cur; the transfer
+                // reads it before the frame is swept again
+                if ((rc = hyb_interface_exchange(h, HYB_F2C)) != HYB_OK) return rc;
+                if ((rc = hyb_coarse_step(h, 200)) != HYB_OK) return rc;
+                if ((rc = hyb_interface_exchange(h, HYB_C2F)) != HYB_OK) return rc;
+                if ((rc = substeps_frame(h, sh)) != HYB_OK) return rc;
+                continue;
+            }
             // the pass's first launch writes a buffer that is neither the
             // frozen state nor the one the fine-to-coarse transfer reads
             int first_dst = -1;
@@ -1087,6 +1188,12 @@ int hyb_step(hyb_handle *h, int max_schwarz) {
         }
         if (tuning) HIP_TRY(h, hipEventRecord(h->ev_t1, h->stream));
         rc = hyb_commit(h);
+        if (rc == HYB_ENONFINITE && sh.launches > 0) {
+            const std::string why = h->err;
+            const int again = count_shared_nonfinite(h, sh, max_schwarz - 1);
+            if (again != HYB_OK) return again;
+            h->err = why;
+        }
         // a coarse solve that ran out of its launch budget (not of max_iter)
         // is repeated once from the untouched committed state
         if (rc != HYB_ENOCONV || h->solve_budget >= h->solve_cap) break;
@@ -1294,7 +1401,7 @@ int hyb_stats(hyb_handle *h, hyb_run_stats *out) {
     out->min_f = dg[1];
     out->h_function = dg[2];
     out->infeasible = (int64_t)cnt[kCntInfeasible];
-    out->nonfinite = (int64_t)cnt[kCntNonfinite];
+    out->nonfinite = (int64_t)(cnt[kCntNonfinite] + h->shared_nonfinite);
     out->krylov_iters = kr.iters;
     out->krylov_converged = kr.converged;
     out->krylov_relres = kr.relres;

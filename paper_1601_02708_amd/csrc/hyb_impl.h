@@ -33,8 +33,14 @@ constexpr int kWClasses = 3;
 // fluid end of a link whose population bounces back off this node).
 constexpr uint16_t kMaskSolid = 1u << 15;
 
-// Device error counters (uint64 slots in the workspace).
-enum Counter { kCntInfeasible = 0, kCntNonfinite = 1, kCntSlots = 8 };
+// Nodes x0 .. x1, y0 .. y1 of the patch (empty when x1 < x0).
+struct NodeRect {
+    int x0, x1, y0, y1;
+};
+
+// Device error counters (uint64 slots in the workspace).  kCntRecount: a second
+// set of the first two and a third to throw away (count_shared_nonfinite).
+enum Counter { kCntInfeasible = 0, kCntNonfinite = 1, kCntRecount = 2, kCntThrown = 4, kCntSlots = 8 };
 
 // Scalars of the coarse BiCGSTAB shared between its kernels.
 struct KrylovState {
@@ -166,8 +172,9 @@ hipError_t launch_lbm_step(const LbmArgs &a, int prec, bool general_perimeter, h
 // shrunk by d tiles on every side); part 2: the others.  Parts 1 and 2 of
 // one depth together update every node exactly as part 0.  ring 2 or 3: the
 // rectangles of launch_lbm_stepk (ring K-1, for passes that mix them).
+// hole: part 1 takes the tiles inside it, part 2 the others.
 hipError_t launch_lbm_step2(const LbmArgs &a, int prec, hipStream_t s, int part = 0, int depth = 0,
-                            int ring = 1);
+                            int ring = 1, const NodeRect *hole = nullptr);
 // K = 3, 4 or 5 fine steps in one launch (Dirichlet closure on every slot;
 // with the surface reaction of dissolving solids, and its link fluxes into
 // a.flux, whole-patch launches only): a.src holds f*(j), a.dst receives
@@ -175,11 +182,9 @@ hipError_t launch_lbm_step2(const LbmArgs &a, int prec, hipStream_t s, int part 
 // rectangle being the tiles whose ring of `ring` >= K-1 nodes stays clear
 // of the patch perimeter.
 hipError_t launch_lbm_stepk(const LbmArgs &a, int prec, int K, hipStream_t s, int part = 0, int depth = 0,
-                            int ring = 0);
-// Nodes x0 .. x1, y0 .. y1 of the patch (empty when x1 < x0).
-struct NodeRect {
-    int x0, x1, y0, y1;
-};
+                            int ring = 0, const NodeRect *hole = nullptr);
+// The tiles of the multi-step launches that lie inside r: the nodes they cover.
+NodeRect whole_tiles(const NodeRect &r);
 // K = 3 .. 5 fine steps in one launch (stream_kernels.hip; fixed solids, nothing
 // recorded) on a rectangle of nodes at least K from every perimeter node's row
 // and column: a.src holds f*(j) there and K nodes around, a.dst receives

@@ -1113,8 +1113,17 @@ hipError_t step_impl(const LbmArgs &a, bool general_perimeter, hipStream_t s, hi
 template <typename S> struct Tile2 { static constexpr int TW = SWEEP2_TW32, TH = SWEEP2_TH32, NT = SWEEP2_NT32; };
 template <> struct Tile2<double> { static constexpr int TW = SWEEP2_TW64, TH = SWEEP2_TH64, NT = SWEEP2_NT64; };
 
+// the rectangle of whole tiles inside r
+template <int TW, int TH>
+void tiles_inside(const NodeRect &r, TileMap &m) {
+    m.ix0 = (r.x0 + TW - 1) / TW;
+    m.iy0 = (r.y0 + TH - 1) / TH;
+    m.ix1 = (r.x1 + 1) / TW - 1;
+    m.iy1 = (r.y1 + 1) / TH - 1;
+}
+
 template <typename S>
-hipError_t step2_impl(const LbmArgs &a, int part, int depth, int ring, hipStream_t s) {
+hipError_t step2_impl(const LbmArgs &a, int part, int depth, int ring, const NodeRect *hole, hipStream_t s) {
     constexpr int TW = Tile2<S>::TW, TH = Tile2<S>::TH, NT = Tile2<S>::NT;
     TileMap m{};
     m.tiles_x = (a.N + TW - 1) / TW;
@@ -1132,7 +1141,8 @@ hipError_t step2_impl(const LbmArgs &a, int part, int depth, int ring, hipStream
     m.iy0 = 1 + depth;
     m.ix1 = (fits ? lx / TW : 0) - depth;
     m.iy1 = (fits ? ly / TH : 0) - depth;
-    const bool has_rect = fits && m.ix1 >= m.ix0 && m.iy1 >= m.iy0;
+    if (hole) tiles_inside<TW, TH>(*hole, m);
+    const bool has_rect = (fits || hole) && m.ix1 >= m.ix0 && m.iy1 >= m.iy0;
     const int all = m.tiles_x * m.tiles_y;
     const int inner = has_rect ? (m.ix1 - m.ix0 + 1) * (m.iy1 - m.iy0 + 1) : 0;
     if (part != 0 && !has_rect) {
@@ -1183,7 +1193,7 @@ bool stream_pays(const NodeRect &r) {
 }
 
 template <typename S, int K>
-hipError_t stepk_impl(const LbmArgs &a, int prec, int part, int depth, int ring, hipStream_t s) {
+hipError_t stepk_impl(const LbmArgs &a, int prec, int part, int depth, int ring, const NodeRect *hole, hipStream_t s) {
     constexpr int TW = Tile3<S>::TW, TH = Tile3<S>::TH, NT = Tile3<S>::NT;
     TileMap m{};
     m.tiles_x = (a.N + TW - 1) / TW;
@@ -1200,7 +1210,8 @@ hipError_t stepk_impl(const LbmArgs &a, int prec, int part, int depth, int ring,
     m.iy0 = 1 + depth;
     m.ix1 = (fits ? lx / TW : 0) - depth;
     m.iy1 = (fits ? ly / TH : 0) - depth;
-    const bool has_rect = fits && m.ix1 >= m.ix0 && m.iy1 >= m.iy0;
+    if (hole) tiles_inside<TW, TH>(*hole, m);
+    const bool has_rect = (fits || hole) && m.ix1 >= m.ix0 && m.iy1 >= m.iy0;
     const int all = m.tiles_x * m.tiles_y;
     const int inner = has_rect ? (m.ix1 - m.ix0 + 1) * (m.iy1 - m.iy0 + 1) : 0;
     if (part != 0 && !has_rect) {
@@ -1211,7 +1222,7 @@ hipError_t stepk_impl(const LbmArgs &a, int prec, int part, int depth, int ring,
     if (m.count == 0) return hipSuccess;
     if (a.mid) return hipErrorInvalidValue;
     const NodeRect deep{m.ix0 * TW, (m.ix1 + 1) * TW - 1, m.iy0 * TH, (m.iy1 + 1) * TH - 1};
-    if (m.part != 2 && has_rect && !(a.flux || a.kappa_s != 0.0) && stream_pays(deep)) {
+    if (m.part != 2 && has_rect && !hole && !(a.flux || a.kappa_s != 0.0) && stream_pays(deep)) {
         const hipError_t e = launch_lbm_stream(a, prec, K, deep, s);
         if (e != hipSuccess || m.part == 1) return e;
         m.part = 2;
@@ -1241,27 +1252,40 @@ hipError_t stepk_impl(const LbmArgs &a, int prec, int part, int depth, int ring,
 }
 
 template <typename S>
-hipError_t stepk_dispatch(const LbmArgs &a, int prec, int K, int part, int depth, int ring, hipStream_t s) {
-    if (K == 3) return stepk_impl<S, 3>(a, prec, part, depth, ring, s);
-    if (K == 4) return stepk_impl<S, 4>(a, prec, part, depth, ring, s);
-    if (K == 5) return stepk_impl<S, 5>(a, prec, part, depth, ring, s);
+hipError_t stepk_dispatch(const LbmArgs &a, int prec, int K, int part, int depth, int ring, const NodeRect *hole, hipStream_t s) {
+    if (K == 3) return stepk_impl<S, 3>(a, prec, part, depth, ring, hole, s);
+    if (K == 4) return stepk_impl<S, 4>(a, prec, part, depth, ring, hole, s);
+    if (K == 5) return stepk_impl<S, 5>(a, prec, part, depth, ring, hole, s);
     return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-hipError_t launch_lbm_stepk(const LbmArgs &a, int prec, int K, hipStream_t s, int part, int depth, int ring) {
-    if (prec == HYB_FP32) return stepk_dispatch<float>(a, prec, K, part, depth, ring, s);
-    if (prec == HYB_FP16S) return stepk_dispatch<_Float16>(a, prec, K, part, depth, ring, s);
-    if (prec == HYB_FP64) return stepk_dispatch<double>(a, prec, K, part, depth, ring, s);
+NodeRect whole_tiles(const NodeRect &r) {
+    constexpr int TW = 64, TH = 8;
+    static_assert(Tile2<float>::TW == TW && Tile2<float>::TH == TH && Tile2<double>::TW == TW && Tile2<double>::TH == TH &&
+                      Tile3<float>::TW == TW && Tile3<float>::TH == TH,
+                  "one tile shape for every multi-step launch");
+    TileMap m{};
+    tiles_inside<TW, TH>(r, m);
+    if (m.ix1 < m.ix0 || m.iy1 < m.iy0) return NodeRect{0, -1, 0, -1};
+    return NodeRect{m.ix0 * TW, (m.ix1 + 1) * TW - 1, m.iy0 * TH, (m.iy1 + 1) * TH - 1};
+}
+
+hipError_t launch_lbm_stepk(const LbmArgs &a, int prec, int K, hipStream_t s, int part, int depth, int ring,
+                            const NodeRect *hole) {
+    if (prec == HYB_FP32) return stepk_dispatch<float>(a, prec, K, part, depth, ring, hole, s);
+    if (prec == HYB_FP16S) return stepk_dispatch<_Float16>(a, prec, K, part, depth, ring, hole, s);
+    if (prec == HYB_FP64) return stepk_dispatch<double>(a, prec, K, part, depth, ring, hole, s);
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_lbm_step2(const LbmArgs &a, int prec, hipStream_t s, int part, int depth, int ring) {
+hipError_t launch_lbm_step2(const LbmArgs &a, int prec, hipStream_t s, int part, int depth, int ring,
+                            const NodeRect *hole) {
     if (ring < 1 || ring > 4) return hipErrorInvalidValue;
-    if (prec == HYB_FP64) return step2_impl<double>(a, part, depth, ring, s);
-    if (prec == HYB_FP32) return step2_impl<float>(a, part, depth, ring, s);
-    return step2_impl<_Float16>(a, part, depth, ring, s);
+    if (prec == HYB_FP64) return step2_impl<double>(a, part, depth, ring, hole, s);
+    if (prec == HYB_FP32) return step2_impl<float>(a, part, depth, ring, hole, s);
+    return step2_impl<_Float16>(a, part, depth, ring, hole, s);
 }
 
 hipError_t launch_lbm_step(const LbmArgs &a, int prec, bool general_perimeter, hipStream_t s,

@@ -108,9 +108,9 @@ __global__ void __launch_bounds__(64 * kStreamWaves, (stream_waves_per_simd<S, K
     const int xs = map.nodes.x0 + (strip < map.strips ? strip : map.strips - 1) * OW, y0 = map.nodes.y0 + (t / map.groups_x) * map.rows;
     const int yend = y0 + map.rows < map.nodes.y1 + 1 ? y0 + map.rows : map.nodes.y1 + 1;
     const unsigned P = static_cast<unsigned>(a.pitch), SP = static_cast<unsigned>(a.plane);
-    const unsigned NP = static_cast<unsigned>(a.N) * P;
     const BufRsrc fsrc = buf_rsrc(a.src, kQ * SP * sz);
     const BufRsrc fdst = buf_rsrc(a.dst, kQ * SP * sz);
+    const unsigned NP = static_cast<unsigned>(a.N) * P;
     const BufRsrc mrs = buf_rsrc(a.mask, NP * 2u);
     const BufRsrc vxr = buf_rsrc(a.vx, NP * 4u);
     const BufRsrc vyr = buf_rsrc(a.vy, NP * 4u);
