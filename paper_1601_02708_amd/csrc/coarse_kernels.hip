@@ -12,6 +12,8 @@
 // (a sparse approximate inverse computed on the host) is folded into the
 // operator A P.  One BiCGSTAB iteration is two kernels with one reduction
 // each; device-side flags turn the launches after convergence into no-ops.
+// Meshes of up to 135 elements a side solve in one launch instead
+// (coarse_solve.hip); these kernels take the larger ones.
 #include "hyb_impl.h"
 
 namespace hyb {

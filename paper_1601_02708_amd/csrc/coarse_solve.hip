@@ -1,0 +1,371 @@
+// The coarse solve in one launch: right-preconditioned BiCGSTAB on (A P) y = r0
+// (the recurrences, the shadow residual and the stop test of coarse_kernels.hip)
+// with the mesh cut into tiles of 17 x 17 nodes, one workgroup each, for meshes
+// of up to 64 tiles (M <= 135).
+//
+// Bound: latency.  An iteration is two stencil products of a few hundred
+// thousand multiply-adds and two sums over the mesh; as two kernels (one per
+// sum) it took 11-20 us, nearly all of it launch, drain and first loads, and the
+// host had to enqueue iterations for the worst case.  Here a row's operator
+// coefficients (49 doubles) and its entries of all Krylov vectors stay in the
+// registers of one lane from the first product to the last, neighbours' entries
+// of the one vector a product reads come through LDS, and what crosses
+// workgroups -- three rings of that vector and two to four partial sums -- goes
+// through global memory once per product.  Per solve (seven iterations, kernel
+// trace): M = 16 30 us against 110 us of kernels, M = 64 55 against 135, M = 128
+// beside a sweep 86 against 180.  A product's LDS reads (49 a row, 0.4 us) and
+// the round trip of the sums (about 2.5 us) are what is left.
+//
+// Between workgroups: every double is published as two 64-bit words, each half
+// of it under a 32-bit tag that names the launch and the phase, written and
+// polled with agent-scope relaxed atomics.  A word is one atomic access and
+// carries its own tag, so a reader needs no fence and no flag, and a word left
+// over from an earlier phase or launch is never taken for the expected one.
+// Every workgroup waits for every other's partial sums in every phase, so words
+// may be overwritten two phases later without further ordering.  A wait gives up
+// after kSpin polls (a workgroup that never becomes resident); the launch then
+// ends with converged = 0 and `lost` set, and the host repeats the step with the
+// kernels of coarse_kernels.hip.
+#include "hyb_impl.h"
+
+namespace hyb {
+namespace {
+
+constexpr int kT = kSolveTile, kF = kT + 2 * kCoarseHalo, kRows = kT * kT, kRing = kF * kF - kRows;
+constexpr int kLanes = 384, kWaves = kLanes / 64;
+constexpr int kSumWave = kWaves - 1;       // polls the partial sums (no ring node of its own)
+constexpr int kSpin = 1 << 22;
+static_assert(kRows <= kLanes && kRing <= kSumWave * 64 && kSolveTiles <= 64, "one row, one ring node, one tile a lane");
+static_assert(kCoarseHalo == kApW / 2, "ring of the operator's radius");
+
+typedef unsigned long long Word;
+
+__device__ __forceinline__ void publish(Word *at, double x, unsigned tag) {
+    const Word b = __builtin_bit_cast(Word, x), t = static_cast<Word>(tag) << 32;
+    __hip_atomic_store(at, t | (b & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(at + 1, t | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// the NV doubles at `at` once all carry the tag; false: given up
+template <int NV>
+__device__ __forceinline__ bool collect(const Word *at, unsigned tag, double (&x)[NV]) {
+    for (int n = 0; n < kSpin; ++n) {
+        Word w[2 * NV];
+#pragma unroll
+        for (int k = 0; k < 2 * NV; ++k) w[k] = __hip_atomic_load(at + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bool all = true;
+#pragma unroll
+        for (int k = 0; k < 2 * NV; ++k) all = all && static_cast<unsigned>(w[k] >> 32) == tag;
+        if (all) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+                x[v] = __builtin_bit_cast(double, (w[2 * v] & 0xffffffffull) | (w[2 * v + 1] << 32));
+            return true;
+        }
+        __builtin_amdgcn_s_sleep(1);
+    }
+    return false;
+}
+
+// Sum over the wavefront, in lane 63: lane shifts within rows of sixteen, then
+// the row totals (no LDS round trips, which cost ds_bpermute ~100 cycles each).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double add_lanes(double x) {
+    struct Two {
+        int lo, hi;
+    };
+    Two w = __builtin_bit_cast(Two, x);
+    w.lo = __builtin_amdgcn_update_dpp(0, w.lo, CTRL, ROWS, 0xf, true);
+    w.hi = __builtin_amdgcn_update_dpp(0, w.hi, CTRL, ROWS, 0xf, true);
+    return x + __builtin_bit_cast(double, w);
+}
+__device__ __forceinline__ double wave_total(double x) {
+    x = add_lanes<0x111, 0xf>(x);          // row_shr:1, 2, 4, 8: lane 15 of a row has its total
+    x = add_lanes<0x112, 0xf>(x);
+    x = add_lanes<0x114, 0xf>(x);
+    x = add_lanes<0x118, 0xf>(x);
+    x = add_lanes<0x142, 0xa>(x);          // row_bcast:15 into rows 1 and 3
+    return add_lanes<0x143, 0xc>(x);       // row_bcast:31 into rows 2 and 3
+}
+
+// Dense part of the shadow residual: the MurmurHash3 32-bit finaliser of the
+// node index, mapped to [-1, 1).
+__device__ __forceinline__ double shadow_hash(int node) {
+    unsigned x = static_cast<unsigned>(node) * 0x9E3779B9u + 0x7F4A7C15u;
+    x ^= x >> 16;
+    x *= 0x85EBCA6Bu;
+    x ^= x >> 13;
+    x *= 0xC2B2AE35u;
+    x ^= x >> 16;
+    return double(x) * (2.0 / 4294967296.0) - 1.0;
+}
+
+// GIVEN: r0 is a given vector, the guess 0 and the result y itself (a solve
+// with c.AP); else r0 = b - A guess of the trapezoidal step, and the result
+// guess + P y.
+template <bool GIVEN>
+__global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const double *__restrict__ given,
+                                                              double *__restrict__ out, int tiles_x, int extrapolate,
+                                                              int max_iter, double tol) {
+    __shared__ double X[kF * kF];
+    __shared__ double red[kWaves][4];
+    __shared__ double tot[4];
+    __shared__ int lost;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int m1 = c.M + 1, nb = gridDim.x;
+    const int k0 = (blockIdx.x % tiles_x) * kT, l0 = (blockIdx.x / tiles_x) * kT;
+    // this lane's row
+    const int dk = tid % kT, dl = tid / kT;
+    const bool row = tid < kRows && k0 + dk < m1 && l0 + dl < m1;
+    const int node = row ? (l0 + dl) * m1 + k0 + dk : 0;
+    const int pi = (node / m1 + kCoarseHalo) * c.S + (node % m1 + kCoarseHalo);
+    const int xi = (dl + kCoarseHalo) * kF + dk + kCoarseHalo;
+    const bool shown = row && nb > 1 && (dk < kCoarseHalo || dl < kCoarseHalo || dk >= kT - kCoarseHalo || dl >= kT - kCoarseHalo);
+    // and its ring node
+    int rk, rl;
+    if (tid < 2 * kCoarseHalo * kF) {
+        rk = tid % kF;
+        rl = tid / kF;
+        if (rl >= kCoarseHalo) rl += kT;
+    } else {
+        const int e = tid - 2 * kCoarseHalo * kF, w = e % (2 * kCoarseHalo);
+        rk = w < kCoarseHalo ? w : w + kT;
+        rl = kCoarseHalo + e / (2 * kCoarseHalo);
+    }
+    const int gk = k0 + rk - kCoarseHalo, gl = l0 + rl - kCoarseHalo;
+    const bool ring = tid < kRing && nb > 1 && gk >= 0 && gl >= 0 && gk < m1 && gl < m1;
+    const int rnode = ring ? gl * m1 + gk : 0, ri = ring ? rl * kF + rk : 0;
+
+    // words: the tag base, the partial sums of both phases, two published vectors
+    Word *const base_at = c.words;
+    Word *const sums_at[2] = {c.words + 16, c.words + 16 + kSolveTiles * 8};
+    Word *const vec_at[2] = {c.words + 16 + kSolveTiles * 16, c.words + 16 + kSolveTiles * 16 + (size_t)4 * c.n};
+    unsigned tag = static_cast<unsigned>(__hip_atomic_load(base_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) + 1u;
+
+    if (tid == 0) lost = 0;
+    for (int e = tid; e < kF * kF; e += kLanes) X[e] = 0.0;
+    double ap[kApW * kApW];
+#pragma unroll
+    for (int o = 0; o < kApW * kApW; ++o) ap[o] = c.AP[(size_t)node * (kApW * kApW) + o];
+
+    auto product = [&]() {
+        double s[kApW];
+#pragma unroll
+        for (int a = 0; a < kApW; ++a) {
+            s[a] = 0.0;
+#pragma unroll
+            for (int b = 0; b < kApW; ++b)
+                s[a] += ap[a * kApW + b] * X[(dl + a) * kF + dk + b];
+            // two stencil rows of reads in flight: more would not fit the
+            // registers beside the coefficients
+            if (a & 1) __builtin_amdgcn_sched_barrier(0);
+        }
+        return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + s[6]);
+    };
+    // Partial sums of this workgroup into red (and to the others); ends behind a barrier.
+    auto give_sums = [&](auto &v, Word *at) {
+        constexpr int NV = sizeof(v) / sizeof(double);
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const double x = wave_total(v[k]);
+            if (lane == 63) red[wave][k] = x;
+        }
+        __syncthreads();
+        if (nb > 1 && tid < NV) {
+            double x = 0.0;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) x += red[w][tid];
+            publish(at + (size_t)blockIdx.x * 8 + 2 * tid, x, tag);
+        }
+    };
+    // Sums over the mesh into tot: the same operations in every workgroup.
+    // Complete after the caller's next barrier.
+    auto take_sums = [&](auto &v, const Word *at) {
+        constexpr int NV = sizeof(v) / sizeof(double);
+        if (nb > 1) {
+            if (wave == kSumWave) {
+                double x[NV];
+#pragma unroll
+                for (int k = 0; k < NV; ++k) x[k] = 0.0;
+                if (lane < nb && !collect<NV>(at + (size_t)lane * 8, tag, x)) lost = 1;
+#pragma unroll
+                for (int k = 0; k < NV; ++k) {
+                    const double y = wave_total(x[k]);
+                    if (lane == 63) tot[k] = y;
+                }
+            }
+        } else if (tid < NV) {
+            double x = 0.0;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) x += red[w][tid];
+            tot[tid] = x;
+        }
+    };
+
+    // ---- r0 --------------------------------------------------------------
+    double r = 0.0, guess = 0.0;
+    double first[3] = {0.0, 0.0, 0.0};
+    if (row) {
+        double b;
+        if constexpr (GIVEN) {
+            r = given[pi];
+            b = r;
+        } else {
+            // the guess: x1 as it stands, or 2 xn - xprev
+            auto at = [&](int p) { return extrapolate ? 2.0 * c.xn[p] - c.xprev[p] : c.x1[p]; };
+            const int kind = c.dkind[node];
+            double sa = 0.0, sb = 0.0;
+#pragma unroll
+            for (int o = 0; o < 9; ++o) {
+                const int p = pi + (o / 3 - 1) * c.S + (o % 3 - 1);
+                const double x = at(p);
+                if (o == 4) guess = x;
+                sa += c.A9[(size_t)o * c.n + node] * x;
+                sb += c.B9[(size_t)o * c.n + node] * c.xn[p];
+            }
+            b = kind == -1 ? sb : c.A9[(size_t)4 * c.n + node] * (kind == -2 ? c.outer_value : c.ufc[kind]);
+            r = b - sa;
+        }
+        first[0] = b * b;
+        first[1] = r * r;
+        first[2] = shadow_hash(node) * r;
+        if (shown) publish(vec_at[0] + (size_t)4 * node, r, tag);
+    }
+    give_sums(first, sums_at[0]);
+
+    double p = 0.0, v = 0.0, s = 0.0, t = 0.0, w = 0.0, z = 0.0, y = 0.0, rh = 0.0;
+    double rho = 1.0, inv_rho = 1.0, alpha = 1.0, bnorm = 0.0, rnorm = 0.0;
+    int iters = 0;
+    bool converged = false;
+    for (int k = 0;; ++k) {
+        // ---- A(k): finish iteration k-1, w = A P r, p, v = A P p ----------
+        bool breakdown = false;
+        double omega = 0.0, beta = 0.0, ring_x[2] = {0.0, 0.0};
+        if (k == 0) {
+            double one[1] = {0.0};
+            if (ring && !collect<1>(vec_at[0] + (size_t)4 * rnode, tag, one)) lost = 1;
+            take_sums(first, sums_at[0]);
+            if (row) X[xi] = r;
+            if (ring) X[ri] = one[0];
+            __syncthreads();
+            bnorm = sqrt(tot[0]);
+            const double gamma = sqrt(tot[1] / c.n);
+            rho = tot[1] + gamma * tot[2];
+            rh = r + gamma * shadow_hash(node);
+        } else {
+            double four[4];
+            if (ring && !collect<2>(vec_at[0] + (size_t)4 * rnode, tag, ring_x)) lost = 1;
+            take_sums(four, sums_at[0]);
+            __syncthreads();
+            // (1 / omega and 1 / rho_{k-1} on their own: one division deep)
+            omega = tot[1] > 0.0 ? tot[0] / tot[1] : 0.0;
+            const double inv_omega = tot[1] / tot[0];
+            const double next = tot[2] - omega * tot[3];
+            breakdown = omega == 0.0 || next == 0.0;
+            beta = breakdown ? 0.0 : (next * inv_rho) * (alpha * inv_omega);
+            rho = next;
+            r = s - omega * t;
+            y += alpha * p + omega * s;
+            if (row) X[xi] = r;
+            if (ring) X[ri] = ring_x[0] - omega * ring_x[1];
+            __syncthreads();
+        }
+        if (lost) break;
+        ++tag;
+        double two[2] = {0.0, 0.0};
+        if (row) {
+            w = product();
+            p = r + beta * (p - omega * v);
+            v = w + beta * (v - omega * z);
+            two[0] = rh * v;
+            two[1] = r * r;
+            if (shown) publish(vec_at[1] + (size_t)4 * node, v, tag);
+        }
+        give_sums(two, sums_at[1]);
+        // ---- B(k): stop test, z = A P v, s, t ------------------------------
+        double one[1] = {0.0};
+        if (ring && !collect<1>(vec_at[1] + (size_t)4 * rnode, tag, one)) lost = 1;
+        take_sums(two, sums_at[1]);
+        if (row) X[xi] = v;
+        if (ring) X[ri] = one[0];
+        __syncthreads();
+        if (lost) break;
+        rnorm = sqrt(tot[1]);
+        iters = k;
+        converged = rnorm <= tol * (bnorm > 0.0 ? bnorm : 1.0);
+        if (converged || breakdown || k >= max_iter || !(rnorm == rnorm)) break;
+        alpha = rho / tot[0];
+        inv_rho = 1.0 / rho;
+        ++tag;
+        double four[4] = {0.0, 0.0, 0.0, 0.0};
+        if (row) {
+            z = product();
+            s = r - alpha * v;
+            t = w - alpha * z;
+            four[0] = t * s;
+            four[1] = t * t;
+            four[2] = rh * s;
+            four[3] = rh * t;
+            if (shown) {
+                publish(vec_at[0] + (size_t)4 * node, s, tag);
+                publish(vec_at[0] + (size_t)4 * node + 2, t, tag);
+            }
+        }
+        give_sums(four, sums_at[0]);
+    }
+
+    // ---- the result ---------------------------------------------------------
+    ++tag;
+    if constexpr (GIVEN) {
+        if (row) out[pi] = y;
+    } else {
+        double one[1] = {0.0};
+        if (shown) publish(vec_at[1] + (size_t)4 * node, y, tag);
+        if (ring && !lost && !collect<1>(vec_at[1] + (size_t)4 * rnode, tag, one)) lost = 1;
+        __syncthreads();                   // every product's reads are done
+        if (row) X[xi] = y;
+        if (ring) X[ri] = one[0];
+        __syncthreads();
+        if (row) {
+            double acc = 0.0;
+#pragma unroll
+            for (int o = 0; o < kSpaiW * kSpaiW; ++o)
+                acc += c.P[(size_t)o * c.n + node] *
+                       X[xi + (o / kSpaiW - kSpaiRadius) * kF + (o % kSpaiW - kSpaiRadius)];
+            out[pi] = guess + acc;
+        }
+    }
+    if (blockIdx.x == 0 && tid == 0) {
+        c.result->iters = iters;
+        c.result->converged = converged && !lost ? 1 : 0;
+        c.result->relres = bnorm > 0.0 ? rnorm / bnorm : rnorm;
+        if (lost) c.result->lost = 1;      // sticks: a step has several solves
+        // (every workgroup has read the base: it took part in a later phase)
+        __hip_atomic_store(base_at, static_cast<Word>(tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+}  // namespace
+
+size_t coarse_solve_words(int n) { return 16 + (size_t)kSolveTiles * 16 + (size_t)8 * n; }
+
+bool coarse_solve_fits(int M) {
+    const int t = (M + 1 + kSolveTile - 1) / kSolveTile;
+    return t * t <= kSolveTiles;
+}
+
+hipError_t launch_coarse_solve_one(const CoarseDev &c, bool extrapolate, int max_iter, double tol, hipStream_t s) {
+    const int t = (c.M + 1 + kSolveTile - 1) / kSolveTile;
+    hipLaunchKernelGGL((coarse_solve_kernel<false>), dim3(t * t), dim3(kLanes), 0, s, c, nullptr, c.x1, t,
+                       extrapolate ? 1 : 0, max_iter, tol);
+    return hipGetLastError();
+}
+
+hipError_t launch_coarse_solve_given_one(const CoarseDev &c, const double *rhs, double *out, int max_iter, double tol,
+                                         hipStream_t s) {
+    const int t = (c.M + 1 + kSolveTile - 1) / kSolveTile;
+    hipLaunchKernelGGL((coarse_solve_kernel<true>), dim3(t * t), dim3(kLanes), 0, s, c, rhs, out, t, 0, max_iter, tol);
+    return hipGetLastError();
+}
+
+}  // namespace hyb

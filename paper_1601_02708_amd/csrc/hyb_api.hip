@@ -106,7 +106,7 @@ struct Layout {
     size_t u_bytes = 0;     // one plane of the arithmetic type (recorded u of a fine step)
     size_t mask = 0, vx = 0, vy = 0, kfield = 0, bc_kind = 0, bc_a = 0, bc_b = 0, c2f_idx = 0, c2f_w = 0;
     size_t fc_idx = 0, fc_w = 0, ufc = 0, A9 = 0, B9 = 0, AP = 0, P = 0, dkind = 0, vec = 0, partials = 0;
-    size_t counters = 0, barrier = 0, kres = 0, diag = 0, total = 0;
+    size_t counters = 0, barrier = 0, words = 0, kres = 0, diag = 0, total = 0;
     size_t APT = 0, PT = 0, c2fT_ptr = 0, c2fT_slot = 0, c2fT_w = 0, f2cT_node = 0, f2cT_ptr = 0, f2cT_c = 0;
     size_t f2cT_w = 0, fc_row = 0;
     // dissolving solids (hyb_lattice.dissolution): per-node mass, link flux
@@ -178,6 +178,7 @@ Layout make_layout(const hyb_mesh *mesh, const hyb_lattice *lat, bool has_kfield
         L.vec = take(12 * align_up(L.vec_len * 8, kAlign));
         L.partials = take((size_t)4 * kPartialValues * coarse_grid8(L.n) * 8);
         L.barrier = take(sizeof(KrylovState));
+        L.words = take(coarse_solve_words(L.n) * 8);
         // reverse mode: transposed stencils and transfer lists (at most 4
         // lattice nodes per Gamma_{f->c} node, at most n such nodes)
         L.APT = take((size_t)L.n * kApW * kApW * 8);
@@ -276,6 +277,7 @@ struct hyb_handle {
     bool solved_this_step = false;
     int last_krylov_iters = 8;          // sizes the launch budget of the next solve
     int solve_budget = 0, solve_cap = 0;
+    bool solve_one = false;             // one-launch coarse solve (coarse_solve.hip)
     long long coarse_steps = 0, fine_steps = 0;
     unsigned long long seen_nonfinite = 0;
     unsigned long long shared_nonfinite = 0;   // counted in the first pass for later ones too
@@ -656,6 +658,8 @@ int hyb_create(const hyb_mesh *mesh, const hyb_lattice *lat, double D, const hyb
         c.xprev = vec[11];
         c.partials = reinterpret_cast<double *>(h->ws + L.partials);
         c.state = reinterpret_cast<KrylovState *>(h->ws + L.barrier);
+        c.words = reinterpret_cast<unsigned long long *>(h->ws + L.words);
+        h->solve_one = coarse_solve_fits(mesh->M);
         c.result = h->kres;
         const std::vector<double> A9t = offset_major(ch.A9, L.n, 9), B9t = offset_major(ch.B9, L.n, 9);
         const std::vector<double> Pt = offset_major(ch.P, L.n, kSpaiW * kSpaiW);
@@ -763,14 +767,20 @@ int hyb_coarse_step(hyb_handle *h, int max_iter) {
     // first solve of a coarse step starts from the extrapolation
     // 2 d(t_n) - d(t_{n-1}) (d(t_n) itself at the first step); later Schwarz
     // passes start from the previous pass's solution
-    if (!h->solved_this_step) HIP_TRY(h, launch_coarse_extrapolate(h->cd, h->stream));
-    const double *guess = h->cd.x1;
-    // iterations enqueued: a few more than the last solve needed (launches
-    // after convergence are no-ops); hyb_commit reports a solve that ran out
-    // of this budget and hyb_step then repeats the step with max_iter
-    const int budget = std::min(max_iter, std::max(4, h->last_krylov_iters + 2));
-    HIP_TRY(h, launch_coarse_rhs(h->cd, guess, h->stream));
-    HIP_TRY(h, launch_coarse_solve(h->cd, guess, budget, max_iter, 1e-14, h->stream));
+    const bool extrapolate = !h->solved_this_step;
+    int budget = max_iter;
+    if (h->solve_one) {
+        HIP_TRY(h, launch_coarse_solve_one(h->cd, extrapolate, max_iter, 1e-14, h->stream));
+    } else {
+        if (extrapolate) HIP_TRY(h, launch_coarse_extrapolate(h->cd, h->stream));
+        const double *guess = h->cd.x1;
+        // iterations enqueued: a few more than the last solve needed (launches
+        // after convergence are no-ops); hyb_commit reports a solve that ran out
+        // of this budget and hyb_step then repeats the step with max_iter
+        budget = std::min(max_iter, std::max(4, h->last_krylov_iters + 2));
+        HIP_TRY(h, launch_coarse_rhs(h->cd, guess, h->stream));
+        HIP_TRY(h, launch_coarse_solve(h->cd, guess, budget, max_iter, 1e-14, h->stream));
+    }
     h->solved_this_step = true;
     h->solve_budget = budget;
     h->solve_cap = max_iter;
@@ -1110,6 +1120,13 @@ int hyb_commit(hyb_handle *h) {
         return h->fail(HYB_ENONFINITE, "non-finite concentration in the fine subdomain; state not committed");
     }
     if (h->solved_this_step) h->last_krylov_iters = kr.iters;
+    if (h->solved_this_step && h->solve_one && kr.lost) {
+        // (never again on this handle: see coarse_solve.hip)
+        h->solve_one = false;
+        h->last_krylov_iters = h->solve_cap;
+        h->solve_budget = 0;
+        return h->fail(HYB_ENOCONV, "coarse solve: a workgroup did not become resident");
+    }
     if (h->solved_this_step && !kr.converged) {
         char buf[160];
         std::snprintf(buf, sizeof buf, "coarse solve did not converge (%d iterations, relres %.3e)", kr.iters,
@@ -1807,7 +1824,8 @@ int hyb_step_adjoint(hyb_handle *h, const void *tape, const double *lam_f, const
                                         p == passes - 1 ? lam_d : nullptr, lam_dn, lam_d1, h->stream));
         HIP_TRY(h, launch_coarse_stencil(h->cd, h->pt, kSpaiW, lam_d1, rhs_t, h->stream));
         ct.result = kr + p;
-        HIP_TRY(h, launch_coarse_solve_given(ct, rhs_t, mu, budget, 200, 1e-14, h->stream));
+        if (h->solve_one) HIP_TRY(h, launch_coarse_solve_given_one(ct, rhs_t, mu, 200, 1e-14, h->stream));
+        else HIP_TRY(h, launch_coarse_solve_given(ct, rhs_t, mu, budget, 200, 1e-14, h->stream));
         HIP_TRY(h, launch_coarse_rhs_transpose(h->cd, h->fc_row, h->nfc, mu, lam_dn, lam_ufc, grad_outer, h->stream));
         // fine-to-coarse transposed onto the state the pass's transfer read
         const void *read = p == 0 ? state(0, 0) : state(p - 1, h->eta);
@@ -1828,6 +1846,7 @@ int hyb_step_adjoint(hyb_handle *h, const void *tape, const double *lam_f, const
     HIP_TRY(h, hipStreamSynchronize(h->stream));
     for (int p = 0; p < passes; ++p)
         if (!res[p].converged) {
+            h->solve_one = false;
             char buf[160];
             std::snprintf(buf, sizeof buf, "transposed coarse solve of pass %d did not converge (%d iterations, relres %.3e)",
                           p, res[p].iters, res[p].relres);
@@ -2118,7 +2137,7 @@ int hyb_dissolution_state(hyb_handle *h, uint8_t *solid, double *mass, int64_t *
 namespace {
 
 struct GroupLayout {
-    size_t A9 = 0, B9 = 0, AP = 0, P = 0, dkind = 0, vec = 0, partials = 0, state = 0, kres = 0, ufc = 0;
+    size_t A9 = 0, B9 = 0, AP = 0, P = 0, dkind = 0, vec = 0, partials = 0, state = 0, words = 0, kres = 0, ufc = 0;
     std::vector<size_t> c2f_idx, c2f_w, fc_idx, fc_w;
     size_t total = 0;
     int n = 0, S = 0, grid = 0;
@@ -2145,6 +2164,7 @@ GroupLayout group_layout(int M, const std::vector<int> &patch_N) {
     G.vec = take(12 * align_up(G.vec_len * 8, kAlign));
     G.partials = take((size_t)4 * kPartialValues * coarse_grid8(G.n) * 8);
     G.state = take(sizeof(KrylovState));
+    G.words = take(coarse_solve_words(G.n) * 8);
     G.kres = take(sizeof(KrylovResult));
     G.ufc = take((size_t)G.n * 8);
     for (int N : patch_N) {
@@ -2174,6 +2194,7 @@ struct hyb_group {
     int M = 0, eta = 1;
     bool solved = false;
     int last_iters = 8, budget = 0, cap = 0;
+    bool solve_one = false;
     int fail(int code, const std::string &msg) {
         err = msg;
         return code;
@@ -2297,6 +2318,8 @@ int hyb_group_create(const hyb_mesh *mesh, int n, hyb_handle *const *patches, do
     c.xprev = vec[11];
     c.partials = reinterpret_cast<double *>(ws + L.partials);
     c.state = reinterpret_cast<KrylovState *>(ws + L.state);
+    c.words = reinterpret_cast<unsigned long long *>(ws + L.words);
+    g->solve_one = coarse_solve_fits(mesh->M);
     g->kres = reinterpret_cast<KrylovResult *>(ws + L.kres);
     c.result = g->kres;
     const std::vector<double> A9t = offset_major(ch.A9, L.n, 9), B9t = offset_major(ch.B9, L.n, 9);
@@ -2345,14 +2368,21 @@ int hyb_group_step(hyb_group *g, int max_schwarz) {
                     return rc;
             }
             // the shared coarse step
-            if (!g->solved && (rc = hip(launch_coarse_extrapolate(g->cd, g->stream), "extrapolate")) != HYB_OK)
-                return rc;
-            g->budget = std::min(200, std::max(4, g->last_iters + 2));
             g->cap = 200;
-            if ((rc = hip(launch_coarse_rhs(g->cd, g->cd.x1, g->stream), "coarse rhs")) != HYB_OK) return rc;
-            if ((rc = hip(launch_coarse_solve(g->cd, g->cd.x1, g->budget, 200, 1e-14, g->stream), "coarse solve")) !=
-                HYB_OK)
-                return rc;
+            if (g->solve_one) {
+                g->budget = g->cap;
+                if ((rc = hip(launch_coarse_solve_one(g->cd, !g->solved, 200, 1e-14, g->stream), "coarse solve")) !=
+                    HYB_OK)
+                    return rc;
+            } else {
+                if (!g->solved && (rc = hip(launch_coarse_extrapolate(g->cd, g->stream), "extrapolate")) != HYB_OK)
+                    return rc;
+                g->budget = std::min(200, std::max(4, g->last_iters + 2));
+                if ((rc = hip(launch_coarse_rhs(g->cd, g->cd.x1, g->stream), "coarse rhs")) != HYB_OK) return rc;
+                if ((rc = hip(launch_coarse_solve(g->cd, g->cd.x1, g->budget, 200, 1e-14, g->stream),
+                              "coarse solve")) != HYB_OK)
+                    return rc;
+            }
             g->solved = true;
             // every patch's perimeter values and fine steps
             for (int p = 0; p < np; ++p) {
@@ -2369,7 +2399,11 @@ int hyb_group_step(hyb_group *g, int max_schwarz) {
             return rc;
         if ((rc = hip(hipStreamSynchronize(g->stream), "synchronise")) != HYB_OK) return rc;
         g->last_iters = kr.iters;
-        if (kr.converged) break;
+        if (kr.converged && !(g->solve_one && kr.lost)) break;
+        if (g->solve_one && kr.lost) {
+            g->solve_one = false;
+            g->budget = 0;
+        }
         if (g->budget >= g->cap || attempt == 1) {
             char buf[160];
             std::snprintf(buf, sizeof buf, "coarse solve did not converge (%d iterations, relres %.3e)", kr.iters,

@@ -58,7 +58,7 @@ struct KrylovResult {
     int iters;
     int converged;
     double relres;
-    unsigned pad0;
+    int lost;                // a workgroup of the one-launch solve never showed up
     unsigned pad1;
 };
 
@@ -252,7 +252,18 @@ struct CoarseDev {
     double *partials;        // [4 slots][kPartialValues][pstride] reduction partials
     KrylovState *state;
     KrylovResult *result;
+    unsigned long long *words;   // coarse_solve_words(n) words of the one-launch solve
 };
+
+// The whole solve in one launch (coarse_solve.hip), for meshes that fit: from
+// c.x1 or, with extrapolate, from 2 xn - xprev; the solution in c.x1.
+constexpr int kSolveTile = 17, kSolveTiles = 64;
+bool coarse_solve_fits(int M);
+size_t coarse_solve_words(int n);
+hipError_t launch_coarse_solve_one(const CoarseDev &c, bool extrapolate, int max_iter, double tol, hipStream_t s);
+// launch_coarse_solve_given in one launch
+hipError_t launch_coarse_solve_given_one(const CoarseDev &c, const double *rhs, double *out, int max_iter, double tol,
+                                         hipStream_t s);
 
 hipError_t launch_coarse_rhs(const CoarseDev &c, const double *guess, hipStream_t s);
 // x1 = 2 xn - xprev over the padded grid (the halo stays zero)
