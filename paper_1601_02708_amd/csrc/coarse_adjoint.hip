@@ -96,10 +96,25 @@ __global__ void rhs_transpose_kernel(CoarseDev c, const int *__restrict__ fc_row
 }
 
 template <typename T>
+__device__ __forceinline__ double node_sum(const T *__restrict__ g, int plane, int n) {
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) s += double(g[q * plane + n]);
+    return s;
+}
+
+template <typename T>
+__global__ void f2c_sums_kernel(LbmArgs lat, const int *__restrict__ node, int ntouched, const T *__restrict__ g,
+                                double *__restrict__ sums) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < ntouched) sums[t] = node_sum(g, static_cast<int>(lat.plane), node[t]);
+}
+
+template <typename T>
 __global__ void f2c_transpose_kernel(LbmArgs lat, const int *__restrict__ node, const int *__restrict__ ptr,
                                      const int *__restrict__ cidx, const double *__restrict__ w, int ntouched,
                                      const double *__restrict__ lam_ufc, const T *__restrict__ g,
-                                     T *__restrict__ lam_pitched, double *__restrict__ lam_dense,
+                                     const double *__restrict__ sums, T *__restrict__ lam_pitched, double *__restrict__ lam_dense,
                                      double *__restrict__ grad_k) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= ntouched) return;
@@ -118,9 +133,7 @@ __global__ void f2c_transpose_kernel(LbmArgs lat, const int *__restrict__ node, 
         for (int q = 0; q < kQ; ++q) lam_dense[((size_t)q * lat.N + j) * lat.N + i] += lam_u * inv;
     }
     if (grad_k) {
-        double s = 0.0;
-#pragma unroll
-        for (int q = 0; q < kQ; ++q) s += double(g[q * plane + n]);
+        const double s = g ? node_sum(g, plane, n) : sums[t];
         grad_k[(size_t)j * lat.N + i] += lam_u * s * inv * inv;
     }
 }
@@ -159,17 +172,32 @@ hipError_t launch_coarse_rhs_transpose(const CoarseDev &c, const int *fc_row, in
     return hipGetLastError();
 }
 
+hipError_t launch_f2c_sums(const LbmArgs &lat, int prec, const int *node, int ntouched, const void *g_state,
+                           double *sums, hipStream_t s) {
+    if (ntouched == 0) return hipSuccess;
+    const dim3 grid(blocks_for(ntouched)), block(kBlock);
+    if (prec == HYB_FP64)
+        hipLaunchKernelGGL(f2c_sums_kernel<double>, grid, block, 0, s, lat, node, ntouched,
+                           static_cast<const double *>(g_state), sums);
+    else if (prec == HYB_FP32)
+        hipLaunchKernelGGL(f2c_sums_kernel<float>, grid, block, 0, s, lat, node, ntouched,
+                           static_cast<const float *>(g_state), sums);
+    else
+        return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
 hipError_t launch_f2c_transpose(const LbmArgs &lat, int prec, const int *node, const int *ptr, const int *cidx,
                                 const double *w, int ntouched, const double *lam_ufc, const void *g_state,
-                                void *lam_pitched, double *lam_dense, double *grad_k, hipStream_t s) {
+                                const double *sums, void *lam_pitched, double *lam_dense, double *grad_k, hipStream_t s) {
     if (ntouched == 0) return hipSuccess;
     if (prec == HYB_FP64)
         hipLaunchKernelGGL(f2c_transpose_kernel<double>, dim3(blocks_for(ntouched)), dim3(kBlock), 0, s, lat, node,
-                           ptr, cidx, w, ntouched, lam_ufc, static_cast<const double *>(g_state),
+                           ptr, cidx, w, ntouched, lam_ufc, static_cast<const double *>(g_state), sums,
                            static_cast<double *>(lam_pitched), lam_dense, grad_k);
     else if (prec == HYB_FP32)
         hipLaunchKernelGGL(f2c_transpose_kernel<float>, dim3(blocks_for(ntouched)), dim3(kBlock), 0, s, lat, node,
-                           ptr, cidx, w, ntouched, lam_ufc, static_cast<const float *>(g_state),
+                           ptr, cidx, w, ntouched, lam_ufc, static_cast<const float *>(g_state), sums,
                            static_cast<float *>(lam_pitched), lam_dense, grad_k);
     else
         return hipErrorInvalidValue;

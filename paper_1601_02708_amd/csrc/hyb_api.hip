@@ -818,6 +818,11 @@ int plan_take(int fuse, int rem) {
     return rem == 6 ? 3 : rem == 7 || rem == 8 ? 4 : rem >= 5 ? 5 : rem;
 }
 
+// Whether the reversed steps read u of each collision and nothing else of the
+// states between a sweep's ends: closures clamped at 0 read the states near the
+// perimeter (dissolving solids, which read all, are the callers' matter).
+bool reverse_reads_u_only(const hyb_handle *h) { return use_two_step(h) && !h->clamp; }
+
 // Ring of the overlap rectangles of a pass: a K-step kernel reads K-1 nodes
 // beyond its tile, and every launch of a pass uses the widest ring so that
 // the rectangles of successive launches nest.
@@ -847,8 +852,29 @@ hipError_t launch_fused(const hyb_handle *h, LbmArgs a, int j0, int take, hipStr
     a.lam3 = (double)(j0 + 3) / (double)h->eta;
     a.lam4 = (double)(j0 + 4) / (double)h->eta;
     a.lam5 = (double)(j0 + 5) / (double)h->eta;
-    if (take >= 3) return launch_lbm_stepk(a, h->prec, take, s, part, depth, pass_ring(h), hole);
+    if (take >= 3 || a.u_out) return launch_lbm_stepk(a, h->prec, take, s, part, depth, pass_ring(h), hole);
     return launch_lbm_step2(a, h->prec, s, part, depth, pass_ring(h), hole);
+}
+
+// n fine steps from src to dst by the handle's launch plan, u of each step's
+// collision stored at u, u + u_bytes, ..; scratch: two states.
+hipError_t record_steps(const hyb_handle *h, int n, const void *src, void *dst, char *scratch, void *u) {
+    LbmArgs a = h->lbm_args(h->frozen, -1);
+    a.u_step = h->lay.u_bytes;
+    a.src = src;
+    int launch = 0;
+    for (int j = 0; j < n; ++launch) {
+        const int take = plan_take(fuse_steps(h), n - j);
+        a.dst = j + take == n ? dst : scratch + (launch & 1) * h->lay.f_bytes;
+        a.u_out = static_cast<char *>(u) + (size_t)j * h->lay.u_bytes;
+        a.lam = (double)(j + 1) / (double)h->eta;
+        const hipError_t e = take == 1 ? launch_lbm_step(a, h->prec, false, h->stream)
+                                       : launch_fused(h, a, j, take, h->stream, 0, 0);
+        if (e != hipSuccess) return e;
+        a.src = a.dst;
+        j += take;
+    }
+    return hipSuccess;
 }
 
 // The nodes a step's Schwarz passes have in common.  Every pass runs the same
@@ -1464,11 +1490,16 @@ int hyb_lbm_substeps_record(hyb_handle *h, int n_sub, void *tape) {
         if (h->dissolve_on) return nullptr;
         return static_cast<char *>(tape) + (size_t)(n_sub + 4) * fb + (size_t)(t - 1) * h->lay.u_bytes;
     };
-    // pairs of fine steps in one launch that also stores the state between
+    // reversed steps that read no state: the plan's multi-step launches (the
+    // states between two of them in the tape's scratch buffers)
+    if (reverse_reads_u_only(h) && !h->dissolve_on)
+        HIP_TRY(h, record_steps(h, n_sub, state(0), state(n_sub), static_cast<char *>(tape) + (size_t)(n_sub + 1) * fb,
+                                uplane(1)));
+    // else pairs of fine steps in one launch that also stores the state between
     // them, while the two-step sweep serves (with dissolving solids the pair
     // also sums both steps' link fluxes)
     const bool pairs = use_two_step(h);
-    for (int t = 0; t < n_sub;) {
+    for (int t = reverse_reads_u_only(h) && !h->dissolve_on ? n_sub : 0; t < n_sub;) {
         LbmArgs a = h->lbm_args(h->frozen, -1);
         a.src = state(t);
         a.lam = (double)(t + 1) / (double)h->eta;
@@ -1637,13 +1668,14 @@ int hyb_step_record(hyb_handle *h, int passes, void *tape) {
     const size_t fb = h->lay.f_bytes;
     const size_t nslots = 4 * (size_t)(h->N - 1);
     char *base = static_cast<char *>(tape);
-    // f*(t_n) stays in the committed buffer and the last pass's end state
-    // is written straight to the buffer the commit makes current; the other
-    // fine states go to the tape
+    // f*(t_n) stays in the committed buffer and a pass's end state is written
+    // straight to the buffer the commit makes current (with dissolving solids
+    // the last pass's: their reversed passes read the others' too); the states
+    // between go to the tape where the reversed steps read them
     const int f0 = h->frozen, out = h->spare(-1);
     auto state = [&](int p, int t) -> char * {
         if (t == 0) return static_cast<char *>(h->f[f0]);
-        if (p == passes - 1 && t == h->eta) return static_cast<char *>(h->f[out]);
+        if (t == h->eta && (p == passes - 1 || !h->dissolve_ws)) return static_cast<char *>(h->f[out]);
         return base + T.states + (1 + (size_t)p * h->eta + t - 1) * fb;
     };
     // u of fine step t of pass p (t = 1 .. eta; not with dissolving solids,
@@ -1663,12 +1695,21 @@ int hyb_step_record(hyb_handle *h, int passes, void *tape) {
                                       h->stream));
         for (int p = 0; p < passes; ++p) {
             if ((rc = hyb_interface_exchange(h, HYB_F2C)) != HYB_OK) return rc;
+            // what the reversed transfer needs of the pass before's end state,
+            // in the slot that state would have taken
+            if (p > 0 && !h->dissolve_ws)
+                HIP_TRY(h, launch_f2c_sums(h->lbm_args(h->frozen, -1), h->prec, h->f2cT_node, h->f2cT_n, h->f[out],
+                                           reinterpret_cast<double *>(base + T.states + (size_t)p * h->eta * fb),
+                                           h->stream));
             if ((rc = hyb_coarse_step(h, 200)) != HYB_OK) return rc;
             if ((rc = hyb_interface_exchange(h, HYB_C2F)) != HYB_OK) return rc;
             if (p == 0) HIP_TRY(h, hipMemcpyAsync(bc, h->bc_a, nslots * 8, hipMemcpyDeviceToDevice, h->stream));
             HIP_TRY(h, hipMemcpyAsync(bc + (1 + p) * nslots, h->bc_b, nslots * 8, hipMemcpyDeviceToDevice, h->stream));
+            const bool u_only = reverse_reads_u_only(h) && !h->dissolve_ws;
+            if (u_only)
+                HIP_TRY(h, record_steps(h, h->eta, state(p, 0), state(p, h->eta), base + T.scratch, uplane(p, 1)));
             const bool pairs = use_two_step(h);
-            for (int t = 1; t <= h->eta;) {
+            for (int t = u_only ? h->eta + 1 : 1; t <= h->eta;) {
                 LbmArgs a = h->lbm_args(h->frozen, -1);
                 a.src = state(p, t - 1);
                 a.lam = (double)t / (double)h->eta;
@@ -1693,7 +1734,7 @@ int hyb_step_record(hyb_handle *h, int passes, void *tape) {
                 t += 1;
             }
             // the next pass's fine-to-coarse transfer reads the current buffer
-            if (p < passes - 1)
+            if (state(p, h->eta) != h->f[out])
                 HIP_TRY(h, hipMemcpyAsync(h->f[out], state(p, h->eta), fb, hipMemcpyDeviceToDevice, h->stream));
             h->cur = out;
             h->jsub = h->eta;
@@ -1733,12 +1774,15 @@ int hyb_step_adjoint(hyb_handle *h, const void *tape, const double *lam_f, const
     char *base = static_cast<char *>(const_cast<void *>(tape));
     auto state = [&](int p, int t) -> char * {
         if (t == 0) return static_cast<char *>(h->f[h->rec_step_f0]);
-        if (p == passes - 1 && t == h->eta) return static_cast<char *>(h->f[h->rec_step_out]);
+        if (t == h->eta && (p == passes - 1 || !h->dissolve_ws)) return static_cast<char *>(h->f[h->rec_step_out]);
         return base + T.states + (1 + (size_t)p * h->eta + t - 1) * fb;
     };
     auto uplane = [&](int p, int t) -> const void * {
         if (h->dissolve_ws) return nullptr;
         return base + T.u + ((size_t)p * h->eta + t - 1) * h->lay.u_bytes;
+    };
+    auto sums = [&](int p) -> const double * {
+        return p == 0 ? nullptr : reinterpret_cast<const double *>(base + T.states + (size_t)p * h->eta * fb);
     };
     void *lcur = base + T.scratch, *nu = base + T.scratch + fb, *lnext = base + T.scratch + 2 * fb;
     double *bc = reinterpret_cast<double *>(base + T.bc);
@@ -1828,7 +1872,9 @@ int hyb_step_adjoint(hyb_handle *h, const void *tape, const double *lam_f, const
         else HIP_TRY(h, launch_coarse_solve_given(ct, rhs_t, mu, budget, 200, 1e-14, h->stream));
         HIP_TRY(h, launch_coarse_rhs_transpose(h->cd, h->fc_row, h->nfc, mu, lam_dn, lam_ufc, grad_outer, h->stream));
         // fine-to-coarse transposed onto the state the pass's transfer read
-        const void *read = p == 0 ? state(0, 0) : state(p - 1, h->eta);
+        // (from the second pass on its sums over q at the nodes read, which the
+        // record kept; with dissolving solids the state itself)
+        const void *read = p == 0 ? state(0, 0) : dissolving ? state(p - 1, h->eta) : nullptr;
         if (p > 0) HIP_TRY(h, hipMemsetAsync(lcur, 0, fb, h->stream));
         void *to_pitched = p == 0 ? nullptr : lcur;
         double *to_dense = p == 0 ? lam_f_out : nullptr;
@@ -1838,7 +1884,7 @@ int hyb_step_adjoint(hyb_handle *h, const void *tape, const double *lam_f, const
                                                     to_dense, grad_k, h->stream));
         else
             HIP_TRY(h, launch_f2c_transpose(a, h->prec, h->f2cT_node, h->f2cT_ptr, h->f2cT_c, h->f2cT_w, h->f2cT_n,
-                                            lam_ufc, read, to_pitched, to_dense, grad_k, h->stream));
+                                            lam_ufc, read, sums(p), to_pitched, to_dense, grad_k, h->stream));
     }
     HIP_TRY(h, launch_coarse_repad(h->cd, lam_dn, lam_d_out, true, h->stream));
     std::vector<KrylovResult> res(passes);

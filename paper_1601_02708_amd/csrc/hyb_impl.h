@@ -122,12 +122,14 @@ struct LbmArgs {
     // reverse mode: a recording forward also stores u of each fine step's
     // collision at the fluid nodes, a plane of the arithmetic type pitched
     // like a population plane (u_out: the launch's first step; u_out2: the
-    // second step of a two-step launch); a reversed step reads the recorded u
-    // of the collision it transposes from u_rec (for dJ/dk) instead of
-    // summing the next state's nine populations.  nullptr: not stored / from
-    // the state.
+    // second step of a two-step launch that stores the state between as well,
+    // which a multi-step launch does not: its step s (0-based) stores at
+    // u_out + s * u_step bytes); a reversed step reads the recorded u of the
+    // collision it transposes from u_rec (for dJ/dk) instead of summing the
+    // next state's nine populations.  nullptr: not stored / from the state.
     void *u_out;
     void *u_out2;
+    size_t u_step;
     const void *u_rec;
 };
 
@@ -178,15 +180,16 @@ hipError_t launch_lbm_step2(const LbmArgs &a, int prec, hipStream_t s, int part 
 // K = 3, 4 or 5 fine steps in one launch (Dirichlet closure on every slot;
 // with the surface reaction of dissolving solids, and its link fluxes into
 // a.flux, whole-patch launches only): a.src holds f*(j), a.dst receives
-// f*(j+K); u^p at a.lam .. a.lam5.  Parts as launch_lbm_step2, the depth-0
+// f*(j+K); u^p at a.lam .. a.lam5.  With a.u_out (FP64 and FP32, whole-patch
+// launches, K = 2 too) every step's u is stored a.u_step bytes apart.  Parts as launch_lbm_step2, the depth-0
 // rectangle being the tiles whose ring of `ring` >= K-1 nodes stays clear
 // of the patch perimeter.
 hipError_t launch_lbm_stepk(const LbmArgs &a, int prec, int K, hipStream_t s, int part = 0, int depth = 0,
                             int ring = 0, const NodeRect *hole = nullptr);
 // The tiles of the multi-step launches that lie inside r: the nodes they cover.
 NodeRect whole_tiles(const NodeRect &r);
-// K = 3 .. 5 fine steps in one launch (stream_kernels.hip; fixed solids, nothing
-// recorded) on a rectangle of nodes at least K from every perimeter node's row
+// K = 3 .. 5 fine steps in one launch (stream_kernels.hip; fixed solids, u of
+// every step recorded when a.u_out is set) on a rectangle of nodes at least K from every perimeter node's row
 // and column: a.src holds f*(j) there and K nodes around, a.dst receives
 // f*(j+K).
 hipError_t launch_lbm_stream(const LbmArgs &a, int prec, int K, const NodeRect &nodes, hipStream_t s);
@@ -308,9 +311,13 @@ hipError_t launch_coarse_rhs_transpose(const CoarseDev &c, const int *fc_row, in
 // population of the node receives lam_u / (1 - k), added to lam_pitched
 // (storage T planes) or, when that is null, to lam_dense (FP64 [9][N][N]);
 // grad_k (dense [N][N], or null) += lam_u sum_q g_q / (1 - k)^2 for the
-// state g the forward transfer read.  HYB_FP64 or HYB_FP32 storage.
+// state g the forward transfer read (g null: from the sums over q that
+// launch_f2c_sums kept at the ntouched nodes).  HYB_FP64 or HYB_FP32 storage.
+hipError_t launch_f2c_sums(const LbmArgs &lat, int prec, const int *node, int ntouched, const void *g_state,
+                           double *sums, hipStream_t s);
 hipError_t launch_f2c_transpose(const LbmArgs &lat, int prec, const int *node, const int *ptr, const int *cidx,
                                 const double *w, int ntouched, const double *lam_ufc, const void *g_state,
+                                const double *sums,
                                 void *lam_pitched, double *lam_dense, double *grad_k, hipStream_t s);
 // Dissolving solids (dissolve_kernels.hip), HYB_FP64 / FP32 / FP16S storage;
 // per-node arrays are pitched like the flag words.

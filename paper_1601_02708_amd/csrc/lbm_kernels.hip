@@ -681,6 +681,12 @@ __device__ __forceinline__ double stage_lam(const LbmArgs &a, int s) {
     return s == 1 ? a.lam : s == 2 ? a.lam2 : s == 3 ? a.lam3 : s == 4 ? a.lam4 : a.lam5;
 }
 
+// plane that a recording launch stores u of its step s (0-based) in
+template <typename T>
+__device__ __forceinline__ T *recorded_u(const LbmArgs &a, int s) {
+    return reinterpret_cast<T *>(static_cast<char *>(a.u_out) + s * a.u_step);
+}
+
 // Row and column of each round's node in a W-wide region of R nodes, NT
 // lanes per round, stepped without divisions.
 template <int W, int NT, int ROUNDS>
@@ -732,7 +738,7 @@ __device__ __forceinline__ void region_fields(int N, int P, int x0, int y0, cons
 // results to registers, the next region's fields fetched, barrier, results
 // written back in place, barrier, next stage.  RING = 0: the owned nodes,
 // stored to HBM.
-template <typename S, int TW, int TH, int NT, int G, int RING, bool FLUX, bool EDGE>
+template <typename S, int TW, int TH, int NT, int G, int RING, bool FLUX, bool REC, bool EDGE>
 __device__ __forceinline__ void later_stages(const LbmArgs &a, typename Pop<S>::T *L0, int x0, int y0,
                                              const BufRsrc &fdst, const BufRsrc &mrs, const BufRsrc &vxr,
                                              const BufRsrc &vyr,
@@ -784,6 +790,9 @@ __device__ __forceinline__ void later_stages(const LbmArgs &a, typename Pop<S>::
         }
         const T u = collide<T>(h[k], T(vx[k]), T(vy[k]), omega, node_k<T>(a, static_cast<int>(n)));
         tally.nonfinite += owned && !finite_val(u);
+        if constexpr (REC) {
+            if (owned) recorded_u<T>(a, STAGE - 1)[n] = u;
+        }
         if constexpr (RING == 0) {
 #pragma unroll
             for (int q = 0; q < kQ; ++q) Buf<S>::store_nt(Pop<S>::st(h[k][q], q, a), fdst, n * sz, q * SP * sz);
@@ -824,15 +833,15 @@ __device__ __forceinline__ void later_stages(const LbmArgs &a, typename Pop<S>::
             for (int q = 0; q < kQ; ++q) L0[q * PL + (rr[k] + OFF) * W0 + (cc[k] + OFF)] = h[k][q];
         }
         __syncthreads();
-        later_stages<S, TW, TH, NT, G, RING - 1, FLUX, EDGE>(a, L0, x0, y0, fdst, mrs, vxr, vyr, m2, vx2, vy2, rr2,
-                                                            cc2, mo, acc, tally);
+        later_stages<S, TW, TH, NT, G, RING - 1, FLUX, REC, EDGE>(a, L0, x0, y0, fdst, mrs, vxr, vyr, m2, vx2, vy2,
+                                                                 rr2, cc2, mo, acc, tally);
     }
 }
 
-template <typename S, int TW, int TH, int NT, int PART, int K, bool FLUX = false>
+template <typename S, int TW, int TH, int NT, int PART, int K, bool FLUX = false, bool REC = false>
 __device__ __forceinline__ void sweepk_body(const LbmArgs &a, const TileMap &map) {
     typedef typename Pop<S>::T T;
-    static_assert(K >= 3, "two-step launches use sweep2_body");
+    static_assert(K >= 3 || REC, "other two-step launches use sweep2_body");
     static_assert((TW * TH) % NT == 0 && NT % TW == 0, "last stage: whole rows per round");
     constexpr int G = K - 1;
     typedef Region<TW, TH, NT, G> R0;
@@ -967,6 +976,9 @@ __device__ __forceinline__ void sweepk_body(const LbmArgs &a, const TileMap &map
             }
             const T u = collide<T>(f, T(vx1[k]), T(vy1[k]), omega, node_k<T>(a, static_cast<int>(n)));
             tally.nonfinite += owned && !finite_val(u);
+            if constexpr (REC) {
+                if (owned) recorded_u<T>(a, 0)[n] = u;
+            }
 #pragma unroll
             for (int q = 0; q < kQ; ++q) lds[q][r][c] = f[q];
         }
@@ -978,8 +990,8 @@ __device__ __forceinline__ void sweepk_body(const LbmArgs &a, const TileMap &map
         int r1[R1::ROUNDS], c1[R1::ROUNDS];
         region_fields<TW, TH, NT, G - 1>(N, P, x0, y0, mrs, vxr, vyr, m1, vx2, vy2, r1, c1);
         __syncthreads();
-        later_stages<S, TW, TH, NT, G, G - 1, FLUX, EDGE>(a, &lds[0][0][0], x0, y0, fdst, mrs, vxr, vyr, m1, vx2,
-                                                          vy2, r1, c1, mo, acc, tally);
+        later_stages<S, TW, TH, NT, G, G - 1, FLUX, REC, EDGE>(a, &lds[0][0][0], x0, y0, fdst, mrs, vxr, vyr, m1, vx2,
+                                                               vy2, r1, c1, mo, acc, tally);
     };
     if (edge) stages(std::true_type{});
     else stages(std::false_type{});
@@ -1005,6 +1017,16 @@ __global__ void __launch_bounds__(NT) lbm_sweep5_kernel(LbmArgs a, TileMap map) 
 template <typename S, int TW, int TH, int NT, int K>
 __global__ void __launch_bounds__(NT) lbm_sweepk_flux_kernel(LbmArgs a, TileMap map) {
     sweepk_body<S, TW, TH, NT, 0, K, true>(a, map);
+}
+
+// K steps (2 .. 5) that also store every step's u for the reverse mode, whose
+// reversed steps need nothing else of the states between: one value a node and
+// step instead of nine.  777^2 FP64, seven steps: 79 us (4 + 3) against 148 for
+// pairs that store the states; 2048^2 FP32, ten steps: 269 us (5 + 5, strips
+// inside a frame of these tiles) against 804.
+template <typename S, int TW, int TH, int NT, int PART, int K>
+__global__ void __launch_bounds__(NT) lbm_sweepk_rec_kernel(LbmArgs a, TileMap map) {
+    sweepk_body<S, TW, TH, NT, PART, K, false, true>(a, map);
 }
 
 // ---------------------------------------------------------------------------
@@ -1220,9 +1242,9 @@ hipError_t stepk_impl(const LbmArgs &a, int prec, int part, int depth, int ring,
     }
     m.count = m.part == 0 ? all : m.part == 1 ? inner : all - inner;
     if (m.count == 0) return hipSuccess;
-    if (a.mid) return hipErrorInvalidValue;
+    if (a.mid || (a.u_out && (a.flux || a.kappa_s != 0.0))) return hipErrorInvalidValue;
     const NodeRect deep{m.ix0 * TW, (m.ix1 + 1) * TW - 1, m.iy0 * TH, (m.iy1 + 1) * TH - 1};
-    if (m.part != 2 && has_rect && !hole && !(a.flux || a.kappa_s != 0.0) && stream_pays(deep)) {
+    if (K >= 3 && m.part != 2 && has_rect && !hole && !(a.flux || a.kappa_s != 0.0) && stream_pays(deep)) {
         const hipError_t e = launch_lbm_stream(a, prec, K, deep, s);
         if (e != hipSuccess || m.part == 1) return e;
         m.part = 2;
@@ -1232,10 +1254,23 @@ hipError_t stepk_impl(const LbmArgs &a, int prec, int part, int depth, int ring,
     if (a.flux || a.kappa_s != 0.0) {
         // dissolving solids: whole-patch launches only
         if (m.part != 0) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((lbm_sweepk_flux_kernel<S, TW, TH, NT, K>), dim3(m.count), dim3(NT), 0, s, a, m);
+        if constexpr (K >= 3)
+            hipLaunchKernelGGL((lbm_sweepk_flux_kernel<S, TW, TH, NT, K>), dim3(m.count), dim3(NT), 0, s, a, m);
+        else return hipErrorInvalidValue;
         return hipGetLastError();
     }
-    if constexpr (K == 3) {
+    if (a.u_out) {
+        if constexpr (sizeof(S) >= 4) {
+            if (m.part == 0) hipLaunchKernelGGL((lbm_sweepk_rec_kernel<S, TW, TH, NT, 0, K>), dim3(m.count), dim3(NT), 0, s, a, m);
+            else if (m.part == 2) hipLaunchKernelGGL((lbm_sweepk_rec_kernel<S, TW, TH, NT, 2, K>), dim3(m.count), dim3(NT), 0, s, a, m);
+            else return hipErrorInvalidValue;
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
+    }
+    if constexpr (K == 2) {
+        return hipErrorInvalidValue;         // step2_impl's
+    } else if constexpr (K == 3) {
         if (m.part == 0) hipLaunchKernelGGL((lbm_sweep3_kernel<S, TW, TH, NT, 0>), dim3(m.count), dim3(NT), 0, s, a, m);
         else if (m.part == 1) hipLaunchKernelGGL((lbm_sweep3_kernel<S, TW, TH, NT, 1>), dim3(m.count), dim3(NT), 0, s, a, m);
         else hipLaunchKernelGGL((lbm_sweep3_kernel<S, TW, TH, NT, 2>), dim3(m.count), dim3(NT), 0, s, a, m);
@@ -1253,6 +1288,7 @@ hipError_t stepk_impl(const LbmArgs &a, int prec, int part, int depth, int ring,
 
 template <typename S>
 hipError_t stepk_dispatch(const LbmArgs &a, int prec, int K, int part, int depth, int ring, const NodeRect *hole, hipStream_t s) {
+    if (K == 2 && a.u_out) return stepk_impl<S, 2>(a, prec, part, depth, ring, hole, s);
     if (K == 3) return stepk_impl<S, 3>(a, prec, part, depth, ring, hole, s);
     if (K == 4) return stepk_impl<S, 4>(a, prec, part, depth, ring, hole, s);
     if (K == 5) return stepk_impl<S, 5>(a, prec, part, depth, ring, hole, s);

@@ -95,7 +95,7 @@ constexpr int kComputeUnits = 256;
 constexpr int kNonTemporal = 2;          // cache policy bit of the buffer store
 typedef unsigned Quad __attribute__((ext_vector_type(4)));
 
-template <typename S, int K, bool KF>
+template <typename S, int K, bool KF, bool REC>
 __global__ void __launch_bounds__(64 * kStreamWaves, (stream_waves_per_simd<S, K>())) lbm_stream_kernel(LbmArgs a, StreamMap map) {
     typedef typename Pop<S>::T T;
     constexpr int UNR = two_rows<S, K>() ? 2 : 1;
@@ -134,6 +134,13 @@ __global__ void __launch_bounds__(64 * kStreamWaves, (stream_waves_per_simd<S, K
     constexpr int ROUNDS_OUT = (kQ * PER + NT - 1) / NT;
     static_assert(GW % CHUNK == 0, "whole chunks");
     __shared__ __align__(16) S rows_out[2][kQ * GW];
+    // a recording launch sends u of each step's row the same way: step s+1's
+    // is K-1-s rows above the finished row
+    constexpr int ROUNDS_U = REC ? (K * PER + NT - 1) / NT : 1;
+    __shared__ __align__(16) T rows_u[REC ? 2 : 1][REC ? K * GW : 4];
+    const BufRsrc urs = buf_rsrc(REC ? a.u_out : a.dst, static_cast<unsigned>(K * a.u_step));
+    unsigned u_at[ROUNDS_U];
+    int u_row[ROUNDS_U];                     // rows above row r - K
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     unsigned out_at[ROUNDS_OUT];
     bool out_on[ROUNDS_OUT];
@@ -144,6 +151,14 @@ __global__ void __launch_bounds__(64 * kStreamWaves, (stream_waves_per_simd<S, K
             const int chunk = static_cast<int>(threadIdx.x) + NT * c, q = chunk / PER, col = gx0 + (chunk % PER) * CHUNK;
             out_on[c] = chunk < kQ * PER && col <= map.nodes.x1;
             out_at[c] = (q * SP + static_cast<unsigned>(col)) * sz;
+        }
+        if constexpr (REC) {
+#pragma unroll
+            for (int c = 0; c < ROUNDS_U; ++c) {
+                const int chunk = static_cast<int>(threadIdx.x) + NT * c, s = chunk / PER, col = gx0 + (chunk % PER) * CHUNK;
+                u_row[c] = chunk < K * PER && col <= map.nodes.x1 ? K - 1 - s : -(1 << 30);
+                u_at[c] = static_cast<unsigned>(s * a.u_step) + (static_cast<unsigned>(K - 1 - s) * P + static_cast<unsigned>(col)) * tsz;
+            }
         }
     }
 
@@ -232,6 +247,9 @@ __global__ void __launch_bounds__(64 * kStreamWaves, (stream_waves_per_simd<S, K
 #pragma unroll
             for (int c = 0; c < 3; ++c) asm volatile("" : "+v"(own[s][c]));
             const T u = collide<T>(f, T(vx[s + 1]), T(vy[s + 1]), omega, KF ? kn[s + 1] : kuni);
+            if constexpr (REC) {
+                if (lane >= K && lane < K + OW) rows_u[r & 1][s * GW + wave * OW + lane - K] = u;
+            }
             const int j = r - s - 1;
             const unsigned long long nf = __builtin_amdgcn_ballot_w64(!__builtin_isfinite(u)) & live[s + 1];
             nonfinite += j >= y0 && j < yend ? static_cast<unsigned>(__popcll(nf)) : 0u;
@@ -251,7 +269,7 @@ __global__ void __launch_bounds__(64 * kStreamWaves, (stream_waves_per_simd<S, K
         __builtin_amdgcn_sched_barrier(0);
         // row r-K has taken all K steps
         const int j = r - K;
-        if (j >= y0 && j < yend) {
+        if (REC || (j >= y0 && j < yend)) {
             S *out = rows_out[j & 1];
             if (lane >= K && lane < K + OW) {
 #pragma unroll
@@ -265,10 +283,18 @@ __global__ void __launch_bounds__(64 * kStreamWaves, (stream_waves_per_simd<S, K
             const unsigned at = static_cast<unsigned>(j) * P * sz;
 #pragma unroll
             for (int c = 0; c < ROUNDS_OUT; ++c)
-                if (out_on[c]) {
+                if (out_on[c] && (!REC || (j >= y0 && j < yend))) {
                     const Quad v = *reinterpret_cast<const Quad *>(out + (threadIdx.x + NT * c) * CHUNK);
                     __builtin_amdgcn_raw_buffer_store_b128(v, fdst, out_at[c], at, kNonTemporal);
                 }
+            if constexpr (REC) {
+#pragma unroll
+                for (int c = 0; c < ROUNDS_U; ++c)
+                    if (j + u_row[c] >= y0 && j + u_row[c] < yend) {
+                        const Quad v = *reinterpret_cast<const Quad *>(&rows_u[r & 1][(threadIdx.x + NT * c) * CHUNK]);
+                        __builtin_amdgcn_raw_buffer_store_b128(v, urs, u_at[c] + static_cast<unsigned>(j) * P * tsz, 0, kNonTemporal);
+                    }
+            }
         }
 #pragma unroll
         for (int d = K; d > 0; --d) {
@@ -307,8 +333,16 @@ hipError_t stream_impl(const LbmArgs &a, const NodeRect &nodes, hipStream_t s) {
     if (m.rows < 4) m.rows = 4;
     m.count = m.groups_x * ((h + m.rows - 1) / m.rows);
     const dim3 grid(m.count), block(64 * kStreamWaves);
-    if (a.kfield) hipLaunchKernelGGL((lbm_stream_kernel<S, K, true>), grid, block, 0, s, a, m);
-    else hipLaunchKernelGGL((lbm_stream_kernel<S, K, false>), grid, block, 0, s, a, m);
+    if (a.u_out) {
+        if constexpr (sizeof(S) >= 4) {
+            if (a.kfield) hipLaunchKernelGGL((lbm_stream_kernel<S, K, true, true>), grid, block, 0, s, a, m);
+            else hipLaunchKernelGGL((lbm_stream_kernel<S, K, false, true>), grid, block, 0, s, a, m);
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
+    }
+    if (a.kfield) hipLaunchKernelGGL((lbm_stream_kernel<S, K, true, false>), grid, block, 0, s, a, m);
+    else hipLaunchKernelGGL((lbm_stream_kernel<S, K, false, false>), grid, block, 0, s, a, m);
     return hipGetLastError();
 }
 
@@ -323,7 +357,7 @@ hipError_t stream_steps(const LbmArgs &a, int K, const NodeRect &nodes, hipStrea
 }  // namespace
 
 hipError_t launch_lbm_stream(const LbmArgs &a, int prec, int K, const NodeRect &nodes, hipStream_t s) {
-    if (a.flux || a.kappa_s != 0.0 || a.mid || a.u_out) return hipErrorInvalidValue;
+    if (a.flux || a.kappa_s != 0.0 || a.mid) return hipErrorInvalidValue;
     if (nodes.x1 < nodes.x0 || nodes.y1 < nodes.y0) return hipSuccess;
     // every pull of every step stays inside the patch and off its perimeter nodes
     if (nodes.x0 < K || nodes.y0 < K || nodes.x1 > a.N - 1 - K || nodes.y1 > a.N - 1 - K) return hipErrorInvalidValue;

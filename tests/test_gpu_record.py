@@ -1,0 +1,52 @@
+"""Recording sweeps of several fine steps per launch against single-step ones:
+a node takes the same operations with the same roundings in each, so the state
+and the recorded u of every step, and with them the gradients that one reversed
+sweep makes of each record, are equal bit for bit."""
+import numpy as np
+import pytest
+
+from paper_1601_02708_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+# 9: one tile, all perimeter; 200: interior and edge tiles; 1409: strips inside
+# the frame.  n_sub 2 .. 7: launches of every length and of two lengths
+@pytest.mark.parametrize("N,n_sub", [(9, 2), (9, 5), (200, 3), (200, 4), (200, 6), (200, 7), (1409, 3), (1409, 4),
+                                     (1409, 5)])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_record_equals_single_steps(precision, N, n_sub):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1601_02708_amd import hyb
+    rng = np.random.default_rng(N + n_sub)
+    j, i = np.mgrid[0:N, 0:N]
+    solid = ((i + j // 7) % 37 - 18) ** 2 + ((j + i // 11) % 41 - 20) ** 2 <= 120
+    solid[:3], solid[-3:], solid[:, :3], solid[:, -3:] = False, False, False, False
+    v = rng.uniform(-0.05, 0.05, (2, N, N)).astype(np.float32) * ~solid
+    kf = rng.uniform(0, 2e-3, (N, N)) if n_sub % 2 else None
+    f0 = inputs.random_populations(N, 7, lo=0.03, hi=0.06)
+    f0[:, solid] = 0.0
+    a, b = rng.uniform(0.2, 0.6, (2, 4 * (N - 1)))
+    got = {}
+    for spl in (1, 2, 5):
+        g = hyb.Hybrid(N=N, x0=0, y0=0, u0=np.full((N, N), 0.4), vx=v[0], vy=v[1], D=0.02, eta=n_sub,
+                       precision=precision, solid=solid.astype(np.uint8), k=1e-3 if kf is None else 0.0, k_field=kf)
+        g.set_steps_per_launch(spl)
+        g.set_populations(f0)
+        g.set_boundary(a, b)
+        tape = g.adjoint_tape(n_sub)
+        g.substeps_record(n_sub, tape)
+        g.set_steps_per_launch(1)
+        lam = torch.from_numpy(np.random.default_rng(1).standard_normal((9, N, N)) * ~solid).to(g.dev)
+        out = torch.empty_like(lam)
+        ga, gb = torch.zeros((2, 4 * (N - 1)), dtype=torch.float64, device=g.dev)
+        gk = torch.zeros((N, N), dtype=torch.float64, device=g.dev)
+        g.adjoint(n_sub, tape, lam, out, ga, gb, gk)
+        g.commit()
+        got[spl] = [g.get_populations()] + [x.cpu().numpy() for x in (out, ga, gb, gk)] + [g.stats()["infeasible"]]
+        g.close()
+    for spl in (2, 5):
+        for x, y in zip(got[1], got[spl]):
+            assert np.array_equal(x, y)
