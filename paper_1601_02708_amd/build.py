@@ -6,7 +6,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
-SOURCES = ["lbm_kernels.hip", "stream_kernels.hip", "adjoint_kernels.hip", "coarse_kernels.hip", "coarse_solve.hip", "coarse_adjoint.hip", "coarse_setup.hip",
+SOURCES = ["lbm_kernels.hip", "stream_kernels.hip", "adjoint_kernels.hip", "adjoint_stream.hip", "coarse_kernels.hip", "coarse_solve.hip", "coarse_adjoint.hip", "coarse_setup.hip",
            "dissolve_kernels.hip", "diag_kernels.hip", "hyb1d.hip",
            "hyb_api.hip"]
 LIB = os.path.join(HERE, "libhyb.so")

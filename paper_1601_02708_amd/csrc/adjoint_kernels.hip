@@ -19,18 +19,35 @@
 // and then gathers the tile's outputs from there, so nu never goes to HBM.
 // The forward states of the step come from the tape recorded by the forward
 // sweep.
-#include "hyb_impl.h"
+#include "lbm_device.h"
 
 #include <type_traits>
 
 namespace hyb {
 namespace {
 
-__device__ __forceinline__ int slot_of(int N, int i, int j) {
-    if (j == 0) return i;
-    if (j == N - 1) return N + i;
-    if (i == 0) return 2 * N + j - 1;
-    return 3 * N - 2 + j - 1;
+// Closure transposed at perimeter slot p (unknown: the directions it sets),
+// interface weight lam; active false: the closure was clamped at 0.
+template <typename T>
+__device__ __forceinline__ void close_transposed(T (&nu)[kQ], unsigned unknown, bool active, double lam, bool owner,
+                                                 int p, double *__restrict__ grad_a, double *__restrict__ grad_b) {
+    double G = 0.0;
+    if (active) {
+        double wsum = 0.0;
+#pragma unroll
+        for (int q = 0; q < kQ; ++q)
+            if ((unknown >> q) & 1u) {
+                G += kW[q] * double(nu[q]);
+                wsum += kW[q];
+            }
+        G /= wsum;
+    }
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) nu[q] = ((unknown >> q) & 1u) ? T(0) : T(double(nu[q]) - G);
+    if (owner) {
+        grad_a[p] += (1.0 - lam) * G;
+        grad_b[p] += lam * G;
+    }
 }
 
 // Dense FP64 ends of a reversed sweep, folded into its first and last
@@ -71,18 +88,9 @@ __device__ __forceinline__ void adj_nu_of(const LbmArgs &a, int i, int j, const 
     }
     const T vx = T(a.vx[n]), vy = T(a.vy[n]);
     const T k = a.kfield ? static_cast<const T *>(a.kfield)[n] : T(a.k);
-    const T omega = T(a.omega);
-    const T vv = T(1.5) * (vx * vx + vy * vy);
-    T S = T(0), wl = T(0);
 #pragma unroll
-    for (int q = 0; q < kQ; ++q) {
-        const T ev = T(kCx[q]) * vx + T(kCy[q]) * vy;
-        const T Pq = T(1) + T(3) * ev + T(4.5) * ev * ev - vv;
-        S += l[q] * T(kW[q]) * (omega * Pq - k);
-        wl += T(kW[q]) * l[q];
-    }
-#pragma unroll
-    for (int q = 0; q < kQ; ++q) nu[q] = (T(1) - omega) * l[q] + S;
+    for (int q = 0; q < kQ; ++q) nu[q] = l[q];
+    const T wl = collide_transposed<T>(nu, vx, vy, T(a.omega), k);
     if (grad_k && owner) {
         // u at the step's collision: recorded by the forward, or from the
         // next state, sum f*(t+1) = (1 - k) u
@@ -104,13 +112,8 @@ __device__ __forceinline__ void adj_nu_of(const LbmArgs &a, int i, int j, const 
         }
     }
     if (EDGE && (i == 0 || j == 0 || i == N - 1 || j == N - 1)) {
-        unsigned unknown = 0;
-#pragma unroll
-        for (int q = 1; q < kQ; ++q) {
-            const int si = i - kCx[q], sj = j - kCy[q];
-            if (si < 0 || si >= N || sj < 0 || sj >= N) unknown |= 1u << q;
-        }
-        const int p = slot_of(N, i, j);
+        const unsigned unknown = outside_bits(N, i, j);
+        const int p = perimeter_slot(N, i, j);
         bool active = true;
         if (a.clamp) {
             // the forward closure's R from the step's source state
@@ -129,23 +132,7 @@ __device__ __forceinline__ void adj_nu_of(const LbmArgs &a, int i, int j, const 
             }
             active = !((1.0 - a.lam) * a.bc_a[p] + a.lam * a.bc_b[p] - known < 0.0);
         }
-        double G = 0.0;
-        if (active) {
-            double wsum = 0.0;
-#pragma unroll
-            for (int q = 0; q < kQ; ++q)
-                if ((unknown >> q) & 1u) {
-                    G += kW[q] * double(nu[q]);
-                    wsum += kW[q];
-                }
-            G /= wsum;
-        }
-#pragma unroll
-        for (int q = 0; q < kQ; ++q) nu[q] = ((unknown >> q) & 1u) ? T(0) : T(double(nu[q]) - G);
-        if (owner) {
-            grad_a[p] += (1.0 - a.lam) * G;
-            grad_b[p] += a.lam * G;
-        }
+        close_transposed<T>(nu, unknown, active, a.lam, owner, p, grad_a, grad_b);
     }
 }
 
@@ -370,6 +357,220 @@ __global__ void __launch_bounds__(NT) adj_step2_kernel(LbmArgs a1, LbmArgs a2, c
     else phases(std::false_type{});
 }
 
+// ---------------------------------------------------------------------------
+// K reversed fine steps per launch
+// ---------------------------------------------------------------------------
+// As adj_step2_kernel, K steps deep: the first step's nu on the tile and K rings
+// from HBM into LDS, each later one's on a region one ring narrower, in place
+// across a barrier, and the owned nodes' cotangents from the last.  Reads u of
+// each step and no state, so it serves where no closure was clamped and solids
+// stay.  Every node takes the single reversed step's operations.  The owned
+// nodes' dJ/dk terms add up in LDS over the launch, in FP64.
+//
+// 64 x 8 tiles, 512 lanes.  LDS: FP64 K = 3 74.6 KB (two workgroups per CU), FP32
+// K = 5 52.0 KB (three).  Bound by latency at that occupancy.  512^2 FP64, ten
+// steps 82 us (3 + 3 + 2 + 2) against 100 in pairs that read states and flags
+// anew; 777^2 FP64, seven steps 121 against 165; 2048^2 FP32, ten steps 609
+// against 1075.
+template <typename T, int TW, int TH, int NT, int K, int RING, bool EDGE>
+__device__ __forceinline__ void reversed_stages(const AdjSteps &A, T *L0, double *kst, int x0, int y0, bool adds) {
+    constexpr int W0 = TW + 2 * K, PL = W0 * (TH + 2 * K), OFF = K - RING;
+    constexpr int W = TW + 2 * RING, H = TH + 2 * RING, ROUNDS = (W * H + NT - 1) / NT;
+    constexpr int S = K - RING;                 // steps reversed before this one
+    const LbmArgs &a = A.a;
+    const int N = a.N, P = a.pitch;
+    const int plane = static_cast<int>(a.plane);
+    T l[ROUNDS][kQ];
+    unsigned m[ROUNDS];
+    // cotangents of this step's result: from HBM, or gathered from the nu before
+#pragma unroll
+    for (int k = 0; k < ROUNDS; ++k) {
+        const int r = threadIdx.x + NT * k;
+        const int c = r % W, row = r / W;
+        const int i = x0 - RING + c, j = y0 - RING + row;
+        m[k] = kMaskSolid;
+        if (r < W * H && (!EDGE || (i >= 0 && j >= 0 && i < N && j < N))) m[k] = a.mask[j * P + i];
+    }
+#pragma unroll
+    for (int k = 0; k < ROUNDS; ++k) {
+        const int r = threadIdx.x + NT * k;
+        const int c = r % W, row = r / W;
+        const int i = x0 - RING + c, j = y0 - RING + row;
+        const int n = j * P + i;
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) l[k][q] = T(0);
+        if (m[k] & kMaskSolid) continue;
+        if constexpr (RING == K) {
+            if (A.lam_dense) {
+#pragma unroll
+                for (int q = 0; q < kQ; ++q) l[k][q] = T(A.lam_dense[dense_at(N, q, i, j)]);
+            } else {
+#pragma unroll
+                for (int q = 0; q < kQ; ++q) l[k][q] = static_cast<const T *>(A.lam)[q * plane + n];
+            }
+        } else {
+            const T *at = L0 + (row + OFF) * W0 + c + OFF;
+#pragma unroll
+            for (int p = 0; p < kQ; ++p) {
+                T acc = at[p * PL + kCy[p] * W0 + kCx[p]];
+                if ((m[k] >> kOpp[p]) & 1u) acc += at[kOpp[p] * PL];
+                l[k][p] = acc;
+            }
+            if (A.inj && (RING > 0 || A.inj_out)) {
+#pragma unroll
+                for (int p = 0; p < kQ; ++p) l[k][p] += static_cast<const T *>(A.inj)[p * plane + n];
+            }
+        }
+    }
+    if constexpr (RING > 0) {
+        const T omega = T(a.omega);
+#pragma unroll
+        for (int k = 0; k < ROUNDS; ++k) {
+            if (m[k] & kMaskSolid) continue;
+            const int r = threadIdx.x + NT * k;
+            const int c = r % W, row = r / W;
+            const int i = x0 - RING + c, j = y0 - RING + row;
+            const int n = j * P + i;
+            const bool owner = adds && c >= RING && c < RING + TW && row >= RING && row < RING + TH;
+            const T wl = collide_transposed<T>(l[k], T(a.vx[n]), T(a.vy[n]), omega, node_k<T>(a, n));
+            if (A.grad_k && owner) {
+                const T u = reinterpret_cast<const T *>(static_cast<const char *>(a.u_rec) - S * a.u_step)[n];
+                double &sum = kst[(row - RING) * TW + c - RING];
+                const double term = double(u) * double(wl);
+                const double total = S == 0 ? term : sum + term;
+                if constexpr (RING > 1) sum = total;
+                else A.grad_k[(size_t)j * N + i] -= total;
+            }
+            if (EDGE && (i == 0 || j == 0 || i == N - 1 || j == N - 1)) {
+                const double lam = S == 0 ? a.lam : S == 1 ? a.lam2 : S == 2 ? a.lam3 : S == 3 ? a.lam4 : a.lam5;
+                close_transposed<T>(l[k], outside_bits(N, i, j), true, lam, owner, perimeter_slot(N, i, j), A.grad_a,
+                                    A.grad_b);
+            }
+        }
+        if constexpr (RING < K) __syncthreads();             // every read of the nu before is done
+#pragma unroll
+        for (int k = 0; k < ROUNDS; ++k) {
+            const int r = threadIdx.x + NT * k;
+            if (r >= W * H) continue;
+#pragma unroll
+            for (int q = 0; q < kQ; ++q) L0[q * PL + (r / W + OFF) * W0 + r % W + OFF] = l[k][q];
+        }
+        __syncthreads();
+        reversed_stages<T, TW, TH, NT, K, RING - 1, EDGE>(A, L0, kst, x0, y0, adds);
+    } else {
+#pragma unroll
+        for (int k = 0; k < ROUNDS; ++k) {
+            const int r = threadIdx.x + NT * k;
+            const int i = x0 + r % W, j = y0 + r / W;
+            if (EDGE && (i >= N || j >= N)) continue;
+            if (A.out_dense) {
+#pragma unroll
+                for (int q = 0; q < kQ; ++q) {
+                    const size_t d = dense_at(N, q, i, j);
+                    if (!A.accumulate) A.out_dense[d] = double(l[k][q]);
+                    else if (!(m[k] & kMaskSolid)) A.out_dense[d] += double(l[k][q]);
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < kQ; ++q) static_cast<T *>(A.out)[q * plane + j * P + i] = l[k][q];
+            }
+        }
+    }
+}
+
+// Tiles of the patch that lie inside a rectangle of whole tiles are left out
+// (all of them are taken where it is empty); those inside `quiet` add no
+// gradients.
+struct FrameMap {
+    int tiles_x, rx0, rx1, ry0, ry1;      // the rectangle, in tiles, inclusive
+    int qx0, qx1, qy0, qy1;
+    int count;
+};
+
+__device__ __forceinline__ void frame_tile(const FrameMap &m, int t, int &tx, int &ty) {
+    const int w = m.rx1 - m.rx0 + 1, h = m.ry1 - m.ry0 + 1;
+    if (w <= 0 || h <= 0) {
+        tx = t % m.tiles_x;
+        ty = t / m.tiles_x;
+        return;
+    }
+    const int below = m.ry0 * m.tiles_x, side = m.tiles_x - w;
+    if (t < below) {
+        tx = t % m.tiles_x;
+        ty = t / m.tiles_x;
+    } else if (t < below + h * side) {
+        const int s = t - below;
+        ty = m.ry0 + s / side;
+        tx = s % side;
+        if (tx >= m.rx0) tx += w;
+    } else {
+        const int s = t - below - h * side;
+        ty = m.ry1 + 1 + s / m.tiles_x;
+        tx = s % m.tiles_x;
+    }
+}
+
+template <typename T, int TW, int TH, int NT, int K>
+__global__ void __launch_bounds__(NT) adj_stepk_kernel(AdjSteps A, FrameMap map) {
+    __shared__ T nus[kQ * (TH + 2 * K) * (TW + 2 * K)];
+    __shared__ double kst[K > 1 ? TH * TW : 1];
+    int tx, ty;
+    frame_tile(map, xcd_tile(blockIdx.x, map.count), tx, ty);
+    const int x0 = tx * TW, y0 = ty * TH, N = A.a.N;
+    const bool adds = !(tx >= map.qx0 && tx <= map.qx1 && ty >= map.qy0 && ty <= map.qy1);
+    const bool edge = x0 - K <= 0 || y0 - K <= 0 || x0 + TW + K - 1 >= N - 1 || y0 + TH + K - 1 >= N - 1;
+    if (edge) reversed_stages<T, TW, TH, NT, K, K, true>(A, nus, kst, x0, y0, adds);
+    else reversed_stages<T, TW, TH, NT, K, K, false>(A, nus, kst, x0, y0, adds);
+}
+
+template <typename T, int TW, int TH>
+__global__ void __launch_bounds__(TW * TH) clear_tiles_kernel(LbmArgs a, T *__restrict__ out, FrameMap map) {
+    int tx, ty;
+    frame_tile(map, blockIdx.x, tx, ty);
+    const int i = tx * TW + threadIdx.x % TW, j = ty * TH + threadIdx.x / TW;
+    if (i >= a.N || j >= a.N) return;
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) out[q * static_cast<int>(a.plane) + j * a.pitch + i] = T(0);
+}
+
+constexpr int kAdjTW = 64, kAdjTH = 8, kAdjNT = 512;
+
+FrameMap frame_map(int N, const NodeRect &hole, const NodeRect &quiet) {
+    FrameMap m{};
+    m.tiles_x = (N + kAdjTW - 1) / kAdjTW;
+    const int tiles_y = (N + kAdjTH - 1) / kAdjTH;
+    auto inside = [](const NodeRect &r, int &x0, int &x1, int &y0, int &y1) {
+        x0 = (r.x0 + kAdjTW - 1) / kAdjTW;
+        y0 = (r.y0 + kAdjTH - 1) / kAdjTH;
+        x1 = (r.x1 + 1) / kAdjTW - 1;
+        y1 = (r.y1 + 1) / kAdjTH - 1;
+    };
+    inside(hole, m.rx0, m.rx1, m.ry0, m.ry1);
+    inside(quiet, m.qx0, m.qx1, m.qy0, m.qy1);
+    const int w = m.rx1 - m.rx0 + 1, h = m.ry1 - m.ry0 + 1;
+    m.count = m.tiles_x * tiles_y - (w > 0 && h > 0 ? w * h : 0);
+    return m;
+}
+
+template <typename T, int K>
+hipError_t adjoint_stepk_impl(const AdjSteps &A, hipStream_t s) {
+    const FrameMap m = frame_map(A.a.N, A.hole, A.quiet);
+    if (m.count <= 0) return hipSuccess;
+    hipLaunchKernelGGL((adj_stepk_kernel<T, kAdjTW, kAdjTH, kAdjNT, K>), dim3(m.count), dim3(kAdjNT), 0, s, A, m);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t adjoint_steps_dispatch(const AdjSteps &A, hipStream_t s) {
+    if (A.K == 1) return adjoint_stepk_impl<T, 1>(A, s);
+    if (A.K == 2) return adjoint_stepk_impl<T, 2>(A, s);
+    if (A.K == 3) return adjoint_stepk_impl<T, 3>(A, s);
+    if (A.K == 4) return adjoint_stepk_impl<T, 4>(A, s);
+    if constexpr (sizeof(T) == 4)
+        if (A.K == 5) return adjoint_stepk_impl<T, 5>(A, s);
+    return hipErrorInvalidValue;
+}
+
 // dense FP64 [9][N][N] <-> pitched planes of T
 template <typename T>
 __global__ void __launch_bounds__(256) adj_pack_kernel(LbmArgs a, const double *__restrict__ dense, T *__restrict__ pitched,
@@ -430,6 +631,24 @@ hipError_t adjoint_step2_impl(const LbmArgs &a1, const LbmArgs &a2, const void *
 }
 
 }  // namespace
+
+hipError_t launch_adjoint_steps(const AdjSteps &A, int prec, hipStream_t s) {
+    if (A.a.clamp || A.a.kappa_s != 0.0 || (A.grad_k && !A.a.u_rec)) return hipErrorInvalidValue;
+    if (prec == HYB_FP64) return adjoint_steps_dispatch<double>(A, s);
+    if (prec == HYB_FP32) return adjoint_steps_dispatch<float>(A, s);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_clear_tiles(const LbmArgs &a, int prec, void *out, const NodeRect &hole, hipStream_t s) {
+    const FrameMap m = frame_map(a.N, hole, NodeRect{0, -1, 0, -1});
+    if (m.count <= 0) return hipSuccess;
+    const dim3 grid(m.count), block(kAdjTW * kAdjTH);
+    if (prec == HYB_FP64)
+        hipLaunchKernelGGL((clear_tiles_kernel<double, kAdjTW, kAdjTH>), grid, block, 0, s, a, static_cast<double *>(out), m);
+    else
+        hipLaunchKernelGGL((clear_tiles_kernel<float, kAdjTW, kAdjTH>), grid, block, 0, s, a, static_cast<float *>(out), m);
+    return hipGetLastError();
+}
 
 hipError_t launch_adjoint_step2(const LbmArgs &a1, const LbmArgs &a2, int prec, const void *snext1,
                                 const void *snext2, const void *lam, void *out, double *grad_a, double *grad_b,

@@ -114,7 +114,8 @@ template <typename T>
 __global__ void f2c_transpose_kernel(LbmArgs lat, const int *__restrict__ node, const int *__restrict__ ptr,
                                      const int *__restrict__ cidx, const double *__restrict__ w, int ntouched,
                                      const double *__restrict__ lam_ufc, const T *__restrict__ g,
-                                     const double *__restrict__ sums, T *__restrict__ lam_pitched, double *__restrict__ lam_dense,
+                                     const double *__restrict__ sums, T *__restrict__ also,
+                                     T *__restrict__ lam_pitched, double *__restrict__ lam_dense,
                                      double *__restrict__ grad_k) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= ntouched) return;
@@ -131,6 +132,10 @@ __global__ void f2c_transpose_kernel(LbmArgs lat, const int *__restrict__ node, 
     } else {
 #pragma unroll
         for (int q = 0; q < kQ; ++q) lam_dense[((size_t)q * lat.N + j) * lat.N + i] += lam_u * inv;
+    }
+    if (also) {
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) also[q * plane + n] += T(lam_u * inv);
     }
     if (grad_k) {
         const double s = g ? node_sum(g, plane, n) : sums[t];
@@ -189,15 +194,15 @@ hipError_t launch_f2c_sums(const LbmArgs &lat, int prec, const int *node, int nt
 
 hipError_t launch_f2c_transpose(const LbmArgs &lat, int prec, const int *node, const int *ptr, const int *cidx,
                                 const double *w, int ntouched, const double *lam_ufc, const void *g_state,
-                                const double *sums, void *lam_pitched, double *lam_dense, double *grad_k, hipStream_t s) {
+                                const double *sums, void *also, void *lam_pitched, double *lam_dense, double *grad_k, hipStream_t s) {
     if (ntouched == 0) return hipSuccess;
     if (prec == HYB_FP64)
         hipLaunchKernelGGL(f2c_transpose_kernel<double>, dim3(blocks_for(ntouched)), dim3(kBlock), 0, s, lat, node,
-                           ptr, cidx, w, ntouched, lam_ufc, static_cast<const double *>(g_state), sums,
+                           ptr, cidx, w, ntouched, lam_ufc, static_cast<const double *>(g_state), sums, static_cast<double *>(also),
                            static_cast<double *>(lam_pitched), lam_dense, grad_k);
     else if (prec == HYB_FP32)
         hipLaunchKernelGGL(f2c_transpose_kernel<float>, dim3(blocks_for(ntouched)), dim3(kBlock), 0, s, lat, node,
-                           ptr, cidx, w, ntouched, lam_ufc, static_cast<const float *>(g_state), sums,
+                           ptr, cidx, w, ntouched, lam_ufc, static_cast<const float *>(g_state), sums, static_cast<float *>(also),
                            static_cast<float *>(lam_pitched), lam_dense, grad_k);
     else
         return hipErrorInvalidValue;

@@ -823,6 +823,71 @@ int plan_take(int fuse, int rem) {
 // perimeter (dissolving solids, which read all, are the callers' matter).
 bool reverse_reads_u_only(const hyb_handle *h) { return use_two_step(h) && !h->clamp; }
 
+// Fewest nodes that the strips of the reversed steps take.  Ten reversed steps,
+// tiles alone against strips in a frame: 1000^2 FP64 266 / 300 us, FP32 155 / 192;
+// 1300^2 446 / 422 and 256 / 259; 1600^2 666 / 562 and 383 / 323; 2048^2
+// 1062 / 873 and 609 / 491.
+constexpr double kReverseStripNodes = 1.5e6;
+// Most steps a launch of the FP64 tiles: three leave room for two workgroups a
+// CU, four for one (ten steps at 777^2: 160 us, four 176, pairs 171).
+constexpr int kReverseTileSteps64 = 3;
+
+// The nodes of a reversed sweep of n steps that go to the strip kernel: whole
+// tiles that no launch's halo connects with the perimeter (n + 4: the strips'
+// first column is rounded down to 16 bytes).  Every Schwarz pass has the same
+// reversed steps there, u of the collisions included, so the passes' cotangents
+// are added up and swept once.  Around them a frame of tiles, pass by pass.
+NodeRect reverse_deep(const hyb_handle *h, int n) {
+    const NodeRect none{0, -1, 0, -1};
+    // (pairs leave an odd count's last step alone, and strips take two or more)
+    if (h->steps_per_launch < 2 || n < 2 || (h->steps_per_launch == 2 && n % 2)) return none;
+    const int d = n + 4;
+    const NodeRect r = whole_tiles(NodeRect{d, h->N - 1 - d, d, h->N - 1 - d});
+    const bool pays = (double)(r.x1 - r.x0 + 1) * (double)(r.y1 - r.y0 + 1) >= kReverseStripNodes;
+    return r.x1 >= r.x0 && r.y1 >= r.y0 && pays ? r : none;
+}
+
+// n reversed fine steps from A.lam or A.lam_dense to A.out or A.out_dense
+// through buf0 and buf1 (A.lam may be buf0); u1: u of the first fine step's
+// collision.  strips: the nodes of *deep; else the tiles that are not inside it
+// (all, if null).  A launch also covers what the ones after it read.
+hipError_t reverse_steps(const hyb_handle *h, const AdjSteps &A, int n, const void *u1, void *buf0, void *buf1,
+                         const NodeRect *deep, bool strips) {
+    const int most = h->prec == HYB_FP64 ? (strips ? 4 : kReverseTileSteps64) : 5;
+    const int fuse = std::min(h->steps_per_launch, most);
+    AdjSteps s = A;
+    for (int t = n, k = 0; t > 0; ++k) {
+        s.K = plan_take(fuse, t);
+        const int rest = t - s.K;
+        s.a.lam = (double)t / (double)h->eta;
+        s.a.lam2 = (double)(t - 1) / (double)h->eta;
+        s.a.lam3 = (double)(t - 2) / (double)h->eta;
+        s.a.lam4 = (double)(t - 3) / (double)h->eta;
+        s.a.lam5 = (double)(t - 4) / (double)h->eta;
+        s.a.u_step = h->lay.u_bytes;
+        s.a.u_rec = static_cast<const char *>(u1) + (size_t)(t - 1) * h->lay.u_bytes;
+        s.out = rest ? (k & 1 ? buf0 : buf1) : A.out;
+        s.out_dense = rest ? nullptr : A.out_dense;
+        s.accumulate = rest ? false : A.accumulate;
+        s.inj_out = rest > 0;
+        hipError_t e;
+        if (strips) {
+            const NodeRect r{(deep->x0 - rest) & ~3, deep->x1 + rest, deep->y0 - rest, deep->y1 + rest};
+            e = launch_adjoint_strips(s, h->prec, r, *deep, h->stream);
+        } else {
+            s.hole = deep ? NodeRect{deep->x0 + rest, deep->x1 - rest, deep->y0 + rest, deep->y1 - rest}
+                          : NodeRect{0, -1, 0, -1};
+            s.quiet = deep ? *deep : NodeRect{0, -1, 0, -1};
+            e = launch_adjoint_steps(s, h->prec, h->stream);
+        }
+        if (e != hipSuccess) return e;
+        s.lam = s.out;
+        s.lam_dense = nullptr;
+        t = rest;
+    }
+    return hipSuccess;
+}
+
 // Ring of the overlap rectangles of a pass: a K-step kernel reads K-1 nodes
 // beyond its tile, and every launch of a pass uses the widest ring so that
 // the rectangles of successive launches nest.
@@ -854,27 +919,6 @@ hipError_t launch_fused(const hyb_handle *h, LbmArgs a, int j0, int take, hipStr
     a.lam5 = (double)(j0 + 5) / (double)h->eta;
     if (take >= 3 || a.u_out) return launch_lbm_stepk(a, h->prec, take, s, part, depth, pass_ring(h), hole);
     return launch_lbm_step2(a, h->prec, s, part, depth, pass_ring(h), hole);
-}
-
-// n fine steps from src to dst by the handle's launch plan, u of each step's
-// collision stored at u, u + u_bytes, ..; scratch: two states.
-hipError_t record_steps(const hyb_handle *h, int n, const void *src, void *dst, char *scratch, void *u) {
-    LbmArgs a = h->lbm_args(h->frozen, -1);
-    a.u_step = h->lay.u_bytes;
-    a.src = src;
-    int launch = 0;
-    for (int j = 0; j < n; ++launch) {
-        const int take = plan_take(fuse_steps(h), n - j);
-        a.dst = j + take == n ? dst : scratch + (launch & 1) * h->lay.f_bytes;
-        a.u_out = static_cast<char *>(u) + (size_t)j * h->lay.u_bytes;
-        a.lam = (double)(j + 1) / (double)h->eta;
-        const hipError_t e = take == 1 ? launch_lbm_step(a, h->prec, false, h->stream)
-                                       : launch_fused(h, a, j, take, h->stream, 0, 0);
-        if (e != hipSuccess) return e;
-        a.src = a.dst;
-        j += take;
-    }
-    return hipSuccess;
 }
 
 // The nodes a step's Schwarz passes have in common.  Every pass runs the same
@@ -913,6 +957,27 @@ SharedNodes shared_nodes(const hyb_handle *h) {
     }
     sh.launches = n;
     return sh;
+}
+
+// n fine steps from src to dst by the handle's launch plan, u of each step's
+// collision stored at u, u + u_bytes, ..; scratch: two states.
+hipError_t record_steps(const hyb_handle *h, int n, const void *src, void *dst, char *scratch, void *u) {
+    LbmArgs a = h->lbm_args(h->frozen, -1);
+    a.u_step = h->lay.u_bytes;
+    a.src = src;
+    int launch = 0;
+    for (int j = 0; j < n; ++launch) {
+        const int take = plan_take(fuse_steps(h), n - j);
+        a.dst = j + take == n ? dst : scratch + (launch & 1) * h->lay.f_bytes;
+        a.u_out = static_cast<char *>(u) + (size_t)j * h->lay.u_bytes;
+        a.lam = (double)(j + 1) / (double)h->eta;
+        const hipError_t e = take == 1 ? launch_lbm_step(a, h->prec, false, h->stream)
+                                       : launch_fused(h, a, j, take, h->stream, 0, 0);
+        if (e != hipSuccess) return e;
+        a.src = a.dst;
+        j += take;
+    }
+    return hipSuccess;
 }
 
 // A later Schwarz pass on the frame: from the frozen state into the buffer that
@@ -1555,6 +1620,32 @@ int hyb_lbm_adjoint(hyb_handle *h, int n_sub, const void *tape, const double *la
     };
     void *lcur = slot(n_sub + 1), *nu = slot(n_sub + 2), *lnext = slot(n_sub + 3);
     LbmArgs a = h->lbm_args(h->frozen, -1);
+    if (reverse_reads_u_only(h) && !h->dissolve_on) {
+        AdjSteps A{};
+        A.a = a;
+        A.grad_a = grad_a;
+        A.grad_b = grad_b;
+        A.grad_k = grad_k;
+        A.lam_dense = lam_in;
+        A.out_dense = lam_out;
+        const NodeRect deep = reverse_deep(h, n_sub);
+        if (deep.x1 >= deep.x0 && lam_in != lam_out) {
+            HIP_TRY(h, launch_adjoint_pack(a, h->prec, lam_in, slot(0), true, h->stream));
+            HIP_TRY(h, reverse_steps(h, A, n_sub, uplane(1), lcur, lnext, &deep, false));
+            A.lam_dense = nullptr;
+            A.lam = slot(0);
+            HIP_TRY(h, reverse_steps(h, A, n_sub, uplane(1), slot(0), nu, &deep, true));
+            return HYB_OK;
+        }
+        // (a first launch that is the last must not read and write one array)
+        if (lam_in == lam_out) {
+            HIP_TRY(h, launch_adjoint_pack(a, h->prec, lam_in, lcur, true, h->stream));
+            A.lam_dense = nullptr;
+            A.lam = lcur;
+        }
+        HIP_TRY(h, reverse_steps(h, A, n_sub, uplane(1), lcur, lnext, nullptr, false));
+        return HYB_OK;
+    }
     // reversed steps in pairs (one launch each) unless single-step launches
     // were asked for (hyb_set_steps_per_launch(1))
     const bool pairs = h->steps_per_launch >= 2;
@@ -1823,6 +1914,14 @@ int hyb_step_adjoint(hyb_handle *h, const void *tape, const double *lam_f, const
     CoarseDev ct = h->cd;
     ct.AP = h->apt;
     const int budget = std::min(200, std::max(16, 2 * h->last_krylov_iters + 6));
+    // reversed steps that read no state: several a launch; on a large patch the
+    // inner nodes of all passes in one sweep of strips, from the sum of the
+    // passes' cotangents (deep_lam)
+    const bool u_only = reverse_reads_u_only(h) && !dissolving;
+    const NodeRect deep = u_only && !inj && dense_in ? reverse_deep(h, h->eta) : NodeRect{0, -1, 0, -1};
+    const bool split = deep.x1 >= deep.x0;
+    void *deep_lam = split ? base + T.states : nullptr;
+    if (split) HIP_TRY(h, launch_adjoint_pack(a, h->prec, lam_f, deep_lam, true, h->stream));
     for (int p = passes - 1; p >= 0; --p) {
         // fine steps of pass p, reversed (interface values of the pass)
         HIP_TRY(h, hipMemsetAsync(ga, 0, 2 * nslots * 8, h->stream));
@@ -1832,10 +1931,29 @@ int hyb_step_adjoint(hyb_handle *h, const void *tape, const double *lam_f, const
         // substep cotangent (state eta takes lam_f, state 0 belongs to the
         // previous coarse step)
         const void *inj_p = p == passes - 1 ? inj : nullptr;
+        if (u_only) {
+            AdjSteps A{};
+            A.a = a;
+            A.grad_a = ga;
+            A.grad_b = gb;
+            A.grad_k = grad_k;
+            A.inj = inj_p;
+            A.lam = lcur;
+            A.lam_dense = dense_in && p == passes - 1 ? lam_f : nullptr;
+            A.out_dense = lam_f_out;
+            A.accumulate = p != passes - 1;
+            HIP_TRY(h, reverse_steps(h, A, h->eta, uplane(p, 1), lcur, lnext, split ? &deep : nullptr, false));
+            if (split && p == 0) {
+                A.lam = deep_lam;
+                A.lam_dense = nullptr;
+                A.accumulate = false;
+                HIP_TRY(h, reverse_steps(h, A, h->eta, uplane(0, 1), deep_lam, nu, &deep, true));
+            }
+        }
         int launches = 0;
         for (int t = h->eta; t >= 1; ++launches) t -= (h->steps_per_launch >= 2 && t >= 2) ? 2 : 1;
         int k = 0;
-        for (int t = h->eta; t >= 1; ++k) {
+        for (int t = u_only ? 0 : h->eta; t >= 1; ++k) {
             // the pass's last launch adds its output to lam_f_out directly
             const double *din = dense_in && p == passes - 1 && k == 0 ? lam_f : nullptr;
             double *dout = k == launches - 1 ? lam_f_out : nullptr;
@@ -1875,7 +1993,10 @@ int hyb_step_adjoint(hyb_handle *h, const void *tape, const double *lam_f, const
         // (from the second pass on its sums over q at the nodes read, which the
         // record kept; with dissolving solids the state itself)
         const void *read = p == 0 ? state(0, 0) : dissolving ? state(p - 1, h->eta) : nullptr;
-        if (p > 0) HIP_TRY(h, hipMemsetAsync(lcur, 0, fb, h->stream));
+        if (p > 0 && split)
+            HIP_TRY(h, launch_clear_tiles(a, h->prec, lcur, NodeRect{deep.x0 + h->eta, deep.x1 - h->eta, deep.y0 + h->eta,
+                                                                     deep.y1 - h->eta}, h->stream));
+        else if (p > 0) HIP_TRY(h, hipMemsetAsync(lcur, 0, fb, h->stream));
         void *to_pitched = p == 0 ? nullptr : lcur;
         double *to_dense = p == 0 ? lam_f_out : nullptr;
         if (dissolving)
@@ -1884,7 +2005,7 @@ int hyb_step_adjoint(hyb_handle *h, const void *tape, const double *lam_f, const
                                                     to_dense, grad_k, h->stream));
         else
             HIP_TRY(h, launch_f2c_transpose(a, h->prec, h->f2cT_node, h->f2cT_ptr, h->f2cT_c, h->f2cT_w, h->f2cT_n,
-                                            lam_ufc, read, sums(p), to_pitched, to_dense, grad_k, h->stream));
+                                            lam_ufc, read, sums(p), p > 0 ? deep_lam : nullptr, to_pitched, to_dense, grad_k, h->stream));
     }
     HIP_TRY(h, launch_coarse_repad(h->cd, lam_dn, lam_d_out, true, h->stream));
     std::vector<KrylovResult> res(passes);

@@ -219,6 +219,32 @@ hipError_t launch_adjoint_step2(const LbmArgs &a1, const LbmArgs &a2, int prec, 
                                 double *out_dense = nullptr, bool accumulate = false);
 // dense FP64 [9][N][N] to pitched planes (to_pitched) or back; back with
 // accumulate adds to the dense array instead of overwriting it
+// A sweep of reversed fine steps: K of them in one launch, where no closure is
+// clamped and no solid dissolves (the reversed steps then read no state).
+struct AdjSteps {
+    LbmArgs a;                    // lam .. lam5: interface weights of the steps as reversed; u_rec: u of the
+                                  // first one's collision, the next ones' u_step bytes below each
+    int K;                        // 1 .. 5 (FP64: 1 .. 4)
+    const void *lam;              // the cotangent, pitched, or
+    const double *lam_dense;      // dense FP64 [9][N][N]
+    void *out;                    // its image, pitched, or
+    double *out_dense;            // dense (accumulate: added)
+    bool accumulate;
+    double *grad_a, *grad_b;
+    double *grad_k;               // or null
+    const void *inj;              // or null: added to the cotangents between the steps and, with
+    bool inj_out;                 // inj_out, to the image
+    NodeRect hole;                // whole 64 x 8 tiles inside it are left out
+    NodeRect quiet;               // whole tiles inside it add no gradients
+};
+hipError_t launch_adjoint_steps(const AdjSteps &A, int prec, hipStream_t s);
+// The same, K = 2 .. 5 (FP64: 2 .. 4), on a rectangle of nodes more than K from
+// the perimeter, x0 a multiple of 16 bytes (adjoint_stream.hip): pitched cotangent,
+// no injection, no accumulation; gradients of the nodes inside `own` only.
+hipError_t launch_adjoint_strips(const AdjSteps &A, int prec, const NodeRect &nodes, const NodeRect &own,
+                                 hipStream_t s);
+// zero populations in the tiles that do not lie inside hole
+hipError_t launch_clear_tiles(const LbmArgs &a, int prec, void *out, const NodeRect &hole, hipStream_t s);
 hipError_t launch_adjoint_pack(const LbmArgs &a, int prec, const double *dense, void *pitched, bool to_pitched,
                                hipStream_t s, bool accumulate = false);
 hipError_t launch_lbm_init(const LbmArgs &a, const double *u0, int prec, hipStream_t s);
@@ -312,12 +338,13 @@ hipError_t launch_coarse_rhs_transpose(const CoarseDev &c, const int *fc_row, in
 // (storage T planes) or, when that is null, to lam_dense (FP64 [9][N][N]);
 // grad_k (dense [N][N], or null) += lam_u sum_q g_q / (1 - k)^2 for the
 // state g the forward transfer read (g null: from the sums over q that
-// launch_f2c_sums kept at the ntouched nodes).  HYB_FP64 or HYB_FP32 storage.
+// launch_f2c_sums kept at the ntouched nodes).  also (or null): pitched planes
+// that receive the same.    HYB_FP64 or HYB_FP32 storage.
 hipError_t launch_f2c_sums(const LbmArgs &lat, int prec, const int *node, int ntouched, const void *g_state,
                            double *sums, hipStream_t s);
 hipError_t launch_f2c_transpose(const LbmArgs &lat, int prec, const int *node, const int *ptr, const int *cidx,
                                 const double *w, int ntouched, const double *lam_ufc, const void *g_state,
-                                const double *sums,
+                                const double *sums, void *also,
                                 void *lam_pitched, double *lam_dense, double *grad_k, hipStream_t s);
 // Dissolving solids (dissolve_kernels.hip), HYB_FP64 / FP32 / FP16S storage;
 // per-node arrays are pitched like the flag words.

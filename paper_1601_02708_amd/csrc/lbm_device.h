@@ -50,6 +50,31 @@ __device__ __forceinline__ T collide(T (&f)[kQ], T vx, T vy, T omega, T k) {
     return u;
 }
 
+// Transpose of the collision: l = dJ/df* after it becomes dJ/df before it,
+//   l_p <- (1 - w) l_p + sum_q l_q w_q (w P_q(v) - k),
+// P_q = 1 + 3 e.v + 9/2 (e.v)^2 - 3/2 v.v.  Returns sum_q w_q l_q (dJ/dk of the
+// node is -u times that).  Written out as the collision, for the same reason;
+// taking e and -e (or v and -v) for each other changes no bit of the result.
+template <typename T>
+__device__ __forceinline__ T collide_transposed(T (&l)[kQ], T vx, T vy, T omega, T k) {
+#pragma clang fp contract(off)
+    const T s1 = l[1] + l[3], s2 = l[2] + l[4], s5 = l[5] + l[7], s6 = l[6] + l[8];
+    const T wl = fma_t(T(kW[5]), s5 + s6, fma_t(T(kW[1]), s1 + s2, T(kW[0]) * l[0]));
+    const T vv = fma_t(vx, vx, vy * vy);
+    const T even = fma_t(omega, fma_t(T(-1.5), vv, T(1)), -k);
+    auto pair = [](T s, T d, T ev) {
+#pragma clang fp contract(off)
+        return ev * fma_t(T(1.5) * ev, s, d);
+    };
+    const T q1 = pair(s1, l[1] - l[3], vx) + pair(s2, l[2] - l[4], vy);
+    const T q5 = pair(s5, l[5] - l[7], vx + vy) + pair(s6, l[6] - l[8], vy - vx);
+    const T S = fma_t(wl, even, omega * fma_t(T(3.0 * kW[1]), q1, T(3.0 * kW[5]) * q5));
+    const T keep = T(1) - omega;
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) l[q] = fma_t(keep, l[q], S);
+    return wl;
+}
+
 __device__ __forceinline__ bool finite_val(double x) { return x - x == 0.0; }
 __device__ __forceinline__ bool finite_val(float x) { return x - x == 0.0f; }
 
