@@ -373,7 +373,8 @@ __global__ void __launch_bounds__(NT) adj_step2_kernel(LbmArgs a1, LbmArgs a2, c
 // anew; 777^2 FP64, seven steps 121 against 165; 2048^2 FP32, ten steps 609
 // against 1075.
 template <typename T, int TW, int TH, int NT, int K, int RING, bool EDGE>
-__device__ __forceinline__ void reversed_stages(const AdjSteps &A, T *L0, double *kst, int x0, int y0, bool adds) {
+__device__ __forceinline__ void reversed_stages(const AdjSteps &A, const char *u_rec, T *L0, double *kst, int x0, int y0,
+                                                bool adds) {
     constexpr int W0 = TW + 2 * K, PL = W0 * (TH + 2 * K), OFF = K - RING;
     constexpr int W = TW + 2 * RING, H = TH + 2 * RING, ROUNDS = (W * H + NT - 1) / NT;
     constexpr int S = K - RING;                 // steps reversed before this one
@@ -434,7 +435,7 @@ __device__ __forceinline__ void reversed_stages(const AdjSteps &A, T *L0, double
             const bool owner = adds && c >= RING && c < RING + TW && row >= RING && row < RING + TH;
             const T wl = collide_transposed<T>(l[k], T(a.vx[n]), T(a.vy[n]), omega, node_k<T>(a, n));
             if (A.grad_k && owner) {
-                const T u = reinterpret_cast<const T *>(static_cast<const char *>(a.u_rec) - S * a.u_step)[n];
+                const T u = reinterpret_cast<const T *>(u_rec - S * a.u_step)[n];
                 double &sum = kst[(row - RING) * TW + c - RING];
                 const double term = double(u) * double(wl);
                 const double total = S == 0 ? term : sum + term;
@@ -456,7 +457,7 @@ __device__ __forceinline__ void reversed_stages(const AdjSteps &A, T *L0, double
             for (int q = 0; q < kQ; ++q) L0[q * PL + (r / W + OFF) * W0 + r % W + OFF] = l[k][q];
         }
         __syncthreads();
-        reversed_stages<T, TW, TH, NT, K, RING - 1, EDGE>(A, L0, kst, x0, y0, adds);
+        reversed_stages<T, TW, TH, NT, K, RING - 1, EDGE>(A, u_rec, L0, kst, x0, y0, adds);
     } else {
 #pragma unroll
         for (int k = 0; k < ROUNDS; ++k) {
@@ -519,8 +520,11 @@ __global__ void __launch_bounds__(NT) adj_stepk_kernel(AdjSteps A, FrameMap map)
     const int x0 = tx * TW, y0 = ty * TH, N = A.a.N;
     const bool adds = !(tx >= map.qx0 && tx <= map.qx1 && ty >= map.qy0 && ty <= map.qy1);
     const bool edge = x0 - K <= 0 || y0 - K <= 0 || x0 + TW + K - 1 >= N - 1 || y0 + TH + K - 1 >= N - 1;
-    if (edge) reversed_stages<T, TW, TH, NT, K, K, true>(A, nus, kst, x0, y0, adds);
-    else reversed_stages<T, TW, TH, NT, K, K, false>(A, nus, kst, x0, y0, adds);
+    const NodeRect &in = A.inner;
+    const bool inner = x0 >= in.x0 && x0 + TW - 1 <= in.x1 && y0 >= in.y0 && y0 + TH - 1 <= in.y1;
+    const char *u_rec = static_cast<const char *>(inner ? A.u_inner : A.a.u_rec);
+    if (edge) reversed_stages<T, TW, TH, NT, K, K, true>(A, u_rec, nus, kst, x0, y0, adds);
+    else reversed_stages<T, TW, TH, NT, K, K, false>(A, u_rec, nus, kst, x0, y0, adds);
 }
 
 template <typename T, int TW, int TH>

@@ -254,6 +254,7 @@ struct hyb_handle {
     const void *rec_step_tape = nullptr;    // last hyb_step_record
     // the record's start and end states stay in these buffers (checked by gen)
     int rec_step_f0 = -1, rec_step_out = -1;
+    NodeRect rec_step_inner{0, -1, 0, -1};   // nodes whose u the first pass alone recorded
     unsigned long long rec_step_gen = 0;
     int rec_step_passes = 0;
     // dissolving solids: workspace reserved (dissolve_ws), reaction on
@@ -849,10 +850,10 @@ NodeRect reverse_deep(const hyb_handle *h, int n) {
 
 // n reversed fine steps from A.lam or A.lam_dense to A.out or A.out_dense
 // through buf0 and buf1 (A.lam may be buf0); u1: u of the first fine step's
-// collision.  strips: the nodes of *deep; else the tiles that are not inside it
+// collision, u1_inner the same for the nodes of A.inner.  strips: the nodes of *deep; else the tiles that are not inside it
 // (all, if null).  A launch also covers what the ones after it read.
-hipError_t reverse_steps(const hyb_handle *h, const AdjSteps &A, int n, const void *u1, void *buf0, void *buf1,
-                         const NodeRect *deep, bool strips) {
+hipError_t reverse_steps(const hyb_handle *h, const AdjSteps &A, int n, const void *u1, const void *u1_inner, void *buf0,
+                         void *buf1, const NodeRect *deep, bool strips) {
     const int most = h->prec == HYB_FP64 ? (strips ? 4 : kReverseTileSteps64) : 5;
     const int fuse = std::min(h->steps_per_launch, most);
     AdjSteps s = A;
@@ -866,6 +867,7 @@ hipError_t reverse_steps(const hyb_handle *h, const AdjSteps &A, int n, const vo
         s.a.lam5 = (double)(t - 4) / (double)h->eta;
         s.a.u_step = h->lay.u_bytes;
         s.a.u_rec = static_cast<const char *>(u1) + (size_t)(t - 1) * h->lay.u_bytes;
+        s.u_inner = static_cast<const char *>(u1_inner) + (size_t)(t - 1) * h->lay.u_bytes;
         s.out = rest ? (k & 1 ? buf0 : buf1) : A.out;
         s.out_dense = rest ? nullptr : A.out_dense;
         s.accumulate = rest ? false : A.accumulate;
@@ -960,8 +962,10 @@ SharedNodes shared_nodes(const hyb_handle *h) {
 }
 
 // n fine steps from src to dst by the handle's launch plan, u of each step's
-// collision stored at u, u + u_bytes, ..; scratch: two states.
-hipError_t record_steps(const hyb_handle *h, int n, const void *src, void *dst, char *scratch, void *u) {
+// collision stored at u, u + u_bytes, ..; scratch: two states.  shared (or
+// null): a later pass, on the frame around the shared nodes.
+hipError_t record_steps(const hyb_handle *h, int n, const void *src, void *dst, char *scratch, void *u,
+                        const SharedNodes *shared = nullptr) {
     LbmArgs a = h->lbm_args(h->frozen, -1);
     a.u_step = h->lay.u_bytes;
     a.src = src;
@@ -972,7 +976,8 @@ hipError_t record_steps(const hyb_handle *h, int n, const void *src, void *dst, 
         a.u_out = static_cast<char *>(u) + (size_t)j * h->lay.u_bytes;
         a.lam = (double)(j + 1) / (double)h->eta;
         const hipError_t e = take == 1 ? launch_lbm_step(a, h->prec, false, h->stream)
-                                       : launch_fused(h, a, j, take, h->stream, 0, 0);
+                                       : launch_fused(h, a, j, take, h->stream, shared ? 2 : 0, 0,
+                                                      shared ? &shared->hole[launch] : nullptr);
         if (e != hipSuccess) return e;
         a.src = a.dst;
         j += take;
@@ -1631,10 +1636,10 @@ int hyb_lbm_adjoint(hyb_handle *h, int n_sub, const void *tape, const double *la
         const NodeRect deep = reverse_deep(h, n_sub);
         if (deep.x1 >= deep.x0 && lam_in != lam_out) {
             HIP_TRY(h, launch_adjoint_pack(a, h->prec, lam_in, slot(0), true, h->stream));
-            HIP_TRY(h, reverse_steps(h, A, n_sub, uplane(1), lcur, lnext, &deep, false));
+            HIP_TRY(h, reverse_steps(h, A, n_sub, uplane(1), uplane(1), lcur, lnext, &deep, false));
             A.lam_dense = nullptr;
             A.lam = slot(0);
-            HIP_TRY(h, reverse_steps(h, A, n_sub, uplane(1), slot(0), nu, &deep, true));
+            HIP_TRY(h, reverse_steps(h, A, n_sub, uplane(1), uplane(1), slot(0), nu, &deep, true));
             return HYB_OK;
         }
         // (a first launch that is the last must not read and write one array)
@@ -1643,7 +1648,7 @@ int hyb_lbm_adjoint(hyb_handle *h, int n_sub, const void *tape, const double *la
             A.lam_dense = nullptr;
             A.lam = lcur;
         }
-        HIP_TRY(h, reverse_steps(h, A, n_sub, uplane(1), lcur, lnext, nullptr, false));
+        HIP_TRY(h, reverse_steps(h, A, n_sub, uplane(1), uplane(1), lcur, lnext, nullptr, false));
         return HYB_OK;
     }
     // reversed steps in pairs (one launch each) unless single-step launches
@@ -1777,6 +1782,10 @@ int hyb_step_record(hyb_handle *h, int passes, void *tape) {
     };
     double *bc = reinterpret_cast<double *>(base + T.bc);
     h->rec_step_tape = nullptr;
+    // the passes after the first record the frame that their interface values
+    // reach; u of the nodes inside it is the first pass's
+    const SharedNodes sh =
+        passes > 1 && reverse_reads_u_only(h) && !h->dissolve_ws ? shared_nodes(h) : SharedNodes();
     for (int attempt = 0; attempt < 2; ++attempt) {
         h->cur = h->frozen;
         h->jsub = 0;
@@ -1798,7 +1807,8 @@ int hyb_step_record(hyb_handle *h, int passes, void *tape) {
             HIP_TRY(h, hipMemcpyAsync(bc + (1 + p) * nslots, h->bc_b, nslots * 8, hipMemcpyDeviceToDevice, h->stream));
             const bool u_only = reverse_reads_u_only(h) && !h->dissolve_ws;
             if (u_only)
-                HIP_TRY(h, record_steps(h, h->eta, state(p, 0), state(p, h->eta), base + T.scratch, uplane(p, 1)));
+                HIP_TRY(h, record_steps(h, h->eta, state(p, 0), state(p, h->eta), base + T.scratch, uplane(p, 1),
+                                        p > 0 && sh.launches > 0 ? &sh : nullptr));
             const bool pairs = use_two_step(h);
             for (int t = u_only ? h->eta + 1 : 1; t <= h->eta;) {
                 LbmArgs a = h->lbm_args(h->frozen, -1);
@@ -1832,10 +1842,17 @@ int hyb_step_record(hyb_handle *h, int passes, void *tape) {
             h->fine_steps += h->eta;
         }
         rc = hyb_commit(h);
+        if (rc == HYB_ENONFINITE && sh.launches > 0) {
+            const std::string why = h->err;
+            const int again = count_shared_nonfinite(h, sh, passes - 1);
+            if (again != HYB_OK) return again;
+            h->err = why;
+        }
         if (rc != HYB_ENOCONV || h->solve_budget >= h->solve_cap) break;
         h->last_krylov_iters = h->solve_cap;
     }
     if (rc == HYB_OK) {
+        h->rec_step_inner = sh.launches > 0 ? sh.hole[sh.launches - 1] : NodeRect{0, -1, 0, -1};
         // the solid flags the commit left (the converted nodes are those
         // solid before and fluid after)
         if (h->dissolve_ws)
@@ -1942,12 +1959,14 @@ int hyb_step_adjoint(hyb_handle *h, const void *tape, const double *lam_f, const
             A.lam_dense = dense_in && p == passes - 1 ? lam_f : nullptr;
             A.out_dense = lam_f_out;
             A.accumulate = p != passes - 1;
-            HIP_TRY(h, reverse_steps(h, A, h->eta, uplane(p, 1), lcur, lnext, split ? &deep : nullptr, false));
+            A.inner = p > 0 ? h->rec_step_inner : NodeRect{0, -1, 0, -1};
+            HIP_TRY(h, reverse_steps(h, A, h->eta, uplane(p, 1), uplane(0, 1), lcur, lnext, split ? &deep : nullptr,
+                                     false));
             if (split && p == 0) {
                 A.lam = deep_lam;
                 A.lam_dense = nullptr;
                 A.accumulate = false;
-                HIP_TRY(h, reverse_steps(h, A, h->eta, uplane(0, 1), deep_lam, nu, &deep, true));
+                HIP_TRY(h, reverse_steps(h, A, h->eta, uplane(0, 1), uplane(0, 1), deep_lam, nu, &deep, true));
             }
         }
         int launches = 0;

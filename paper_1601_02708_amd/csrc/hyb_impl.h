@@ -224,6 +224,8 @@ hipError_t launch_adjoint_step2(const LbmArgs &a1, const LbmArgs &a2, int prec, 
 struct AdjSteps {
     LbmArgs a;                    // lam .. lam5: interface weights of the steps as reversed; u_rec: u of the
                                   // first one's collision, the next ones' u_step bytes below each
+    NodeRect inner;               // tiles inside it read u from u_inner instead (whole tiles)
+    const void *u_inner;
     int K;                        // 1 .. 5 (FP64: 1 .. 4)
     const void *lam;              // the cotangent, pitched, or
     const double *lam_dense;      // dense FP64 [9][N][N]
@@ -235,7 +237,7 @@ struct AdjSteps {
     const void *inj;              // or null: added to the cotangents between the steps and, with
     bool inj_out;                 // inj_out, to the image
     NodeRect hole;                // whole 64 x 8 tiles inside it are left out
-    NodeRect quiet;               // whole tiles inside it add no gradients
+    NodeRect quiet;               // whole 64 x 8 tiles inside it add no gradients
 };
 hipError_t launch_adjoint_steps(const AdjSteps &A, int prec, hipStream_t s);
 // The same, K = 2 .. 5 (FP64: 2 .. 4), on a rectangle of nodes more than K from

@@ -50,3 +50,48 @@ def test_record_equals_single_steps(precision, N, n_sub):
     for spl in (2, 5):
         for x, y in zip(got[1], got[spl]):
             assert np.array_equal(x, y)
+
+
+# no shared nodes (N = 100), holes of one and two launches, ragged right and top
+# tiles, three passes, a patch whose inner reversed sweep goes to strips
+@pytest.mark.parametrize("precision,N,eta,spl,passes", [("fp64", 100, 4, 4, 2), ("fp64", 201, 4, 4, 2),
+                                                        ("fp64", 261, 7, 4, 3), ("fp32", 330, 10, 5, 2),
+                                                        ("fp32", 395, 9, 5, 3), ("fp32", 1450, 10, 5, 2)])
+def test_recorded_passes_share_the_inner_nodes(precision, N, eta, spl, passes):
+    """Passes after the first record the frame their interface values reach;
+    with one fine step a launch every pass records the whole patch."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1601_02708_amd import configs, hyb
+    p = configs.build_problem(configs.PORE2048.replace(N=N, M=16, eta=eta, max_iter=passes, k=1e-3,
+                                                       porosity=0.8 if N < 1000 else 0.6))
+    rng = np.random.default_rng(N)
+    lam_f = rng.standard_normal((9, N, N)) * (p.solid == 0)
+    lam_d = rng.standard_normal(17 ** 2)
+    got = []
+    for s in (spl, 1):
+        g = hyb.Hybrid.from_problem(p, precision=precision)
+        tape = g.step_tape(passes)
+        res = []
+        g.set_steps_per_launch(s)
+        g.step_record(passes, tape)
+        g.set_steps_per_launch(2)
+        for sub in (None, torch.zeros((9, N, N), dtype=torch.float64, device=g.dev)):
+            lf, ld = torch.from_numpy(lam_f).to(g.dev), torch.from_numpy(lam_d).to(g.dev)
+            of, od, gk = torch.empty_like(lf), torch.empty_like(ld), torch.zeros_like(lf[0])
+            g.step_adjoint(tape, lf, ld, of, od, gk, lam_sub=sub)
+            res += [x.cpu().numpy() for x in (of, od, gk)]
+        st = g.stats()
+        got.append(res + [g.get_populations(), g.concentration(hyb.HYB_COARSE), st["infeasible"], st["fine_steps"]])
+        f = g.get_populations()
+        i = N // 2 + int(np.flatnonzero(p.solid[N // 2, N // 2:] == 0)[0])       # a fluid node
+        f[0, N // 2, i] = np.nan
+        g.set_populations(f)
+        with pytest.raises(hyb.HybError):
+            g.set_steps_per_launch(s)
+            g.step_record(passes, tape)
+        got[-1].append(g.stats()["nonfinite"])
+        g.close()
+    for x, y in zip(*got):
+        assert np.array_equal(x, y)
