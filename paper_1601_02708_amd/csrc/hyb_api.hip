@@ -118,9 +118,16 @@ struct Layout {
     bool wall = false;
     size_t wall_nx = 0, wall_ny = 0;
     size_t f2cD_node = 0, f2cD_ptr = 0, f2cD_c = 0, f2cD_m = 0;
+    bool extra_state = false;           // a fourth population state (f_extra)
+    size_t f_extra = 0;
     int n = 0, S = 0, grid = 0;
     size_t vec_len = 0;
 };
+
+int plan_take(int fuse, int rem);
+
+// most fine steps a launch takes unless the user sets it
+int default_steps(int prec) { return prec == HYB_FP32 ? 5 : 4; }
 
 Layout make_layout(const hyb_mesh *mesh, const hyb_lattice *lat, bool has_kfield) {
     Layout L;
@@ -201,6 +208,12 @@ Layout make_layout(const hyb_mesh *mesh, const hyb_lattice *lat, bool has_kfield
             L.f2cD_c = take((size_t)L.n * 5 * 4);
             L.f2cD_m = take((size_t)L.n * 5 * 4);
         }
+        // passes of more than three launches share nodes by way of a fourth
+        // state (shared_nodes), where the patch is large enough to have any
+        int launches = 0;
+        for (int rem = lat->eta; rem > 0; ++launches) rem -= plan_take(default_steps(lat->precision), rem);
+        L.extra_state = launches > 3 && launches <= 8 && N >= 4 * lat->eta + 128 && !lat->wall_closure;
+        if (L.extra_state) L.f_extra = take(L.f_bytes);
     }
     L.total = off;
     return L;
@@ -222,6 +235,7 @@ struct hyb_handle {
     hipStream_t stream = nullptr;
     Layout lay;
     void *f[3] = {nullptr, nullptr, nullptr};
+    void *f_extra = nullptr;            // a fourth state, where a pass takes more than three launches
     char *ws = nullptr;
     // workspace views
     uint16_t *mask = nullptr;
@@ -390,6 +404,7 @@ struct hyb_handle {
         a.c_sat = c_sat;
         a.flux = nullptr;
         a.flux_first = 0;
+        a.flux_kept = NodeRect{0, -1, 0, -1};
         a.mid = nullptr;
         a.wall_nx = wall_on ? wall_nx : nullptr;
         a.wall_ny = wall_on ? wall_ny : nullptr;
@@ -464,7 +479,7 @@ int hyb_create(const hyb_mesh *mesh, const hyb_lattice *lat, double D, const hyb
     // leave one 83 KB workgroup per CU: 52), FP16 shifted storage 4 (its
     // launches keep FP32 intermediates on chip: 82.4, 83.7, 88.9, 87.2 GLUPS
     // at 2, 3, 4, 5)
-    h->steps_per_launch = lat->precision == HYB_FP16S ? 4 : lat->precision == HYB_FP64 ? 4 : 5;
+    h->steps_per_launch = default_steps(lat->precision);
     h->fp64 = lat->precision == HYB_FP64;
     h->tau = tau;
     h->omega = 1.0 / tau;
@@ -566,6 +581,7 @@ int hyb_create(const hyb_mesh *mesh, const hyb_lattice *lat, double D, const hyb
         h->wall_nx = reinterpret_cast<float *>(h->ws + L.wall_nx);
         h->wall_ny = reinterpret_cast<float *>(h->ws + L.wall_ny);
     }
+    if (L.extra_state) h->f_extra = h->ws + L.f_extra;
     if (L.dissolve) {
         h->dissolve_ws = true;
         h->mass = reinterpret_cast<double *>(h->ws + L.mass);
@@ -927,36 +943,50 @@ hipError_t launch_fused(const hyb_handle *h, LbmArgs a, int j0, int take, hipStr
 // eta fine steps from the frozen state and only its interface values differ;
 // those reach the nodes less than eta from the perimeter and no other, since a
 // fine step carries values one node further.  A later pass therefore sweeps the
-// frame that they reach and leaves the nodes inside it as the first pass left
-// them.  hole[j]: the nodes that launch j of a later pass need not write, whole
-// tiles -- all of those at the end of the pass, and before it fewer, by the ring
-// that the launches after it read.  Holds for up to two launches a pass: the
-// first of two then writes the buffer that does not hold the first pass's result,
-// the last one that which does.
+// frame that they reach and leaves the nodes inside it (`common`) as the first
+// pass left them.  hole[j]: the nodes that launch j of a later pass need not
+// write, whole tiles -- `common` in the last launch, and before it fewer, by the
+// ring that the launches after it read.
+//
+// Buffers of a later pass (the frozen state, `last`, which holds the result of
+// the pass before, and one more): two launches go through the third buffer.
+// Of three, the first writes `last` and the second the third buffer, which held
+// the first pass's second state at every node and so still does outside the
+// frame; the last launch can then put back all that the first one overwrote
+// (hole[2] = hole[0]).  More need the workspace's extra state.
+//
+// Dissolving solids at 2048^2 FP32, two passes of four five-step launches: 2083 us
+// a step with whole passes, 1391 with a frame for the second.
 struct SharedNodes {
+    static constexpr int kMost = 8;
     int launches = 0;                // 0: every pass sweeps the whole patch
-    int take[2] = {0, 0};
-    NodeRect hole[2] = {{0, -1, 0, -1}, {0, -1, 0, -1}};
+    int take[kMost] = {};
+    NodeRect hole[kMost] = {};
+    NodeRect common{0, -1, 0, -1};
 };
-SharedNodes shared_nodes(const hyb_handle *h) {
+// own_buffers: the launches have buffers of their own, two beside the result
+SharedNodes shared_nodes(const hyb_handle *h, bool own_buffers = false) {
     SharedNodes sh;
-    if (!use_two_step(h) || h->dissolve_on) return sh;
+    if (!use_two_step(h)) return sh;
     const int fuse = fuse_steps(h);
     int n = 0;
     for (int rem = h->eta; rem > 0; ++n) {
         const int t = plan_take(fuse, rem);
-        if (n == 2 || t < 2) return sh;
+        if (n == SharedNodes::kMost || t < 2) return sh;
         sh.take[n] = t;
         rem -= t;
     }
+    if (n > 3 && !own_buffers && !h->f_extra) return sh;
     const int d = h->eta;
     NodeRect r = whole_tiles(NodeRect{d, h->N - 1 - d, d, h->N - 1 - d});
+    sh.common = r;
     for (int j = n - 1; j >= 0; --j) {
         if (r.x1 < r.x0 || r.y1 < r.y0) return sh;
         sh.hole[j] = r;
         const int k = sh.take[j];
         r = whole_tiles(NodeRect{r.x0 + k, r.x1 - k, r.y0 + k, r.y1 - k});
     }
+    if (n == 3) sh.hole[2] = sh.hole[0];
     sh.launches = n;
     return sh;
 }
@@ -988,18 +1018,31 @@ hipError_t record_steps(const hyb_handle *h, int n, const void *src, void *dst, 
 // A later Schwarz pass on the frame: from the frozen state into the buffer that
 // holds the pass before it (h->cur).
 int substeps_frame(hyb_handle *h, const SharedNodes &sh) {
-    const int last = h->cur;
-    int src = h->frozen, j0 = 0;
+    const int last = h->cur, n = sh.launches;
+    void *const third = h->f[h->spare(last)];
+    auto dst = [&](int j) -> void * {
+        if (j == n - 1) return h->f[last];
+        if (n == 3) return j == 0 ? h->f[last] : third;
+        return j & 1 ? h->f_extra : third;
+    };
+    int j0 = 0;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (h->timing) {
         HIP_TRY(h, h->take_event_pair(&e0, &e1));
-        h->ev_launches[h->ev_used - 1] = sh.launches;
+        h->ev_launches[h->ev_used - 1] = n;
         HIP_TRY(h, hipEventRecord(e0, h->stream));
     }
-    for (int j = 0; j < sh.launches; ++j) {
-        const int dst = j == sh.launches - 1 ? last : h->spare(last);
-        HIP_TRY(h, launch_fused(h, h->lbm_args(src, dst), j0, sh.take[j], h->stream, 2, 0, &sh.hole[j]));
-        src = dst;
+    for (int j = 0; j < n; ++j) {
+        LbmArgs a = h->lbm_args(h->frozen, last);
+        if (j > 0) a.src = dst(j - 1);
+        a.dst = dst(j);
+        if (h->dissolve_on) {
+            // (the common nodes' sums are the first pass's)
+            a.flux = h->flux;
+            a.flux_first = j == 0;
+            a.flux_kept = sh.common;
+        }
+        HIP_TRY(h, launch_fused(h, a, j0, sh.take[j], h->stream, 2, 0, &sh.hole[j]));
         j0 += sh.take[j];
     }
     if (e1) HIP_TRY(h, hipEventRecord(e1, h->stream));
@@ -1011,26 +1054,27 @@ int substeps_frame(hyb_handle *h, const SharedNodes &sh) {
 // Non-finite concentrations are counted at every node in every pass, so when a
 // step has met one, count those of the shared nodes again for each later pass:
 // sweep a pass as before (its interface values are still in place, so the state
-// stays the same), counting into slots of their own and keeping only the shared
-// nodes' count.  Runs only on the way to HYB_ENONFINITE.
+// stays the same) and then its frames, counting each into slots of their own;
+// the difference is the shared nodes' count.  Runs only on the way to
+// HYB_ENONFINITE.
 int count_shared_nonfinite(hyb_handle *h, const SharedNodes &sh, int later) {
     const int last = h->cur;
     HIP_TRY(h, hipMemsetAsync(h->counters + kCntRecount, 0, (kCntSlots - kCntRecount) * 8, h->stream));
     int src = h->frozen, j0 = 0;
     for (int j = 0; j < sh.launches; ++j) {
-        const int dst = j == sh.launches - 1 ? last : h->spare(last);
+        const int dst = (sh.launches - 1 - j) & 1 ? h->spare(last) : last;
         LbmArgs a = h->lbm_args(src, dst);
-        a.counters = h->counters + kCntThrown;
-        HIP_TRY(h, launch_fused(h, a, j0, sh.take[j], h->stream, 0, 0));
         a.counters = h->counters + kCntRecount;
-        HIP_TRY(h, launch_fused(h, a, j0, sh.take[j], h->stream, 1, 0, &sh.hole[j]));
+        HIP_TRY(h, launch_fused(h, a, j0, sh.take[j], h->stream, 0, 0));
+        a.counters = h->counters + kCntFrame;
+        HIP_TRY(h, launch_fused(h, a, j0, sh.take[j], h->stream, 2, 0, &sh.hole[j]));
         src = dst;
         j0 += sh.take[j];
     }
-    unsigned long long cnt[2];
+    unsigned long long cnt[kCntSlots - kCntRecount];
     HIP_TRY(h, hipMemcpyAsync(cnt, h->counters + kCntRecount, sizeof(cnt), hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
-    h->shared_nonfinite += (unsigned long long)later * cnt[kCntNonfinite];
+    h->shared_nonfinite += (unsigned long long)later * (cnt[kCntNonfinite] - cnt[kCntFrame - kCntRecount + kCntNonfinite]);
     return HYB_OK;
 }
 
@@ -1785,7 +1829,7 @@ int hyb_step_record(hyb_handle *h, int passes, void *tape) {
     // the passes after the first record the frame that their interface values
     // reach; u of the nodes inside it is the first pass's
     const SharedNodes sh =
-        passes > 1 && reverse_reads_u_only(h) && !h->dissolve_ws ? shared_nodes(h) : SharedNodes();
+        passes > 1 && reverse_reads_u_only(h) && !h->dissolve_ws ? shared_nodes(h, true) : SharedNodes();
     for (int attempt = 0; attempt < 2; ++attempt) {
         h->cur = h->frozen;
         h->jsub = 0;
@@ -1852,7 +1896,7 @@ int hyb_step_record(hyb_handle *h, int passes, void *tape) {
         h->last_krylov_iters = h->solve_cap;
     }
     if (rc == HYB_OK) {
-        h->rec_step_inner = sh.launches > 0 ? sh.hole[sh.launches - 1] : NodeRect{0, -1, 0, -1};
+        h->rec_step_inner = sh.launches > 0 ? sh.common : NodeRect{0, -1, 0, -1};
         // the solid flags the commit left (the converted nodes are those
         // solid before and fluid after)
         if (h->dissolve_ws)

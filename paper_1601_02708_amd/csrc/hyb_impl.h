@@ -39,8 +39,8 @@ struct NodeRect {
 };
 
 // Device error counters (uint64 slots in the workspace).  kCntRecount: a second
-// set of the first two and a third to throw away (count_shared_nonfinite).
-enum Counter { kCntInfeasible = 0, kCntNonfinite = 1, kCntRecount = 2, kCntThrown = 4, kCntSlots = 8 };
+// and a third set of the first two (count_shared_nonfinite).
+enum Counter { kCntInfeasible = 0, kCntNonfinite = 1, kCntRecount = 2, kCntFrame = 4, kCntSlots = 8 };
 
 // Scalars of the coarse BiCGSTAB shared between its kernels.
 struct KrylovState {
@@ -110,6 +110,8 @@ struct LbmArgs {
     // nullptr: not tracked
     double *flux;
     int flux_first;
+    // whole 64 x 8 tiles inside it leave flux alone (multi-step launches)
+    NodeRect flux_kept = {0, -1, 0, -1};
     // two-step launches: when set, the first fine step's results of the
     // owned nodes are also stored here (a recording forward keeps every
     // fine state); nullptr: not stored
@@ -179,7 +181,7 @@ hipError_t launch_lbm_step2(const LbmArgs &a, int prec, hipStream_t s, int part 
                             int ring = 1, const NodeRect *hole = nullptr);
 // K = 3, 4 or 5 fine steps in one launch (Dirichlet closure on every slot;
 // with the surface reaction of dissolving solids, and its link fluxes into
-// a.flux, whole-patch launches only): a.src holds f*(j), a.dst receives
+// a.flux, parts 0 and 2 only): a.src holds f*(j), a.dst receives
 // f*(j+K); u^p at a.lam .. a.lam5.  With a.u_out (FP64 and FP32, whole-patch
 // launches, K = 2 too) every step's u is stored a.u_step bytes apart.  Parts as launch_lbm_step2, the depth-0
 // rectangle being the tiles whose ring of `ring` >= K-1 nodes stays clear

@@ -401,6 +401,13 @@ __device__ __forceinline__ void tile_of(const TileMap &m, int t, int &tx, int &t
     ty = m.iy1 + 1 + t / m.tiles_x;
 }
 
+// where the tile at (x0, y0) sums its link fluxes (nullptr: not at all)
+template <int TW, int TH>
+__device__ __forceinline__ double *tile_flux(const LbmArgs &a, int x0, int y0) {
+    const NodeRect &r = a.flux_kept;
+    return x0 >= r.x0 && x0 + TW - 1 <= r.x1 && y0 >= r.y0 && y0 + TH - 1 <= r.y1 ? nullptr : a.flux;
+}
+
 // Body of the two-step sweep.  FLUX (dissolving solids): bounce-back
 // values carry the surface reaction, and every owned solid node with fluid
 // neighbours adds the link fluxes of both fine steps to a.flux (step j+1
@@ -561,7 +568,8 @@ __device__ __forceinline__ void sweep2_body(const LbmArgs &a, const TileMap &map
     // neighbours) and its running flux sum
     S g1[FLUX ? ROUNDS2 : 1][kQ];
     double fl2[FLUX ? ROUNDS2 : 1];
-    if constexpr (FLUX) {
+    double *const flux = FLUX ? tile_flux<TW, TH>(a, x0, y0) : nullptr;
+    if (FLUX && flux) {
 #pragma unroll
         for (int k = 0; k < ROUNDS2; ++k) {
             if (!(m2[k] & kMaskSolid) || !(m2[k] & 0x1FEu)) continue;
@@ -572,7 +580,7 @@ __device__ __forceinline__ void sweep2_body(const LbmArgs &a, const TileMap &map
                 const unsigned at = kOpp[q] * SP + static_cast<unsigned>(kCx[q] + kCy[q] * P);
                 g1[k][q] = Buf<S>::load(fsrc, (n + at) * sz, 0);
             }
-            fl2[k] = (a.flux_first || !a.flux) ? 0.0 : a.flux[n];
+            fl2[k] = a.flux_first ? 0.0 : flux[n];
         }
     }
     __syncthreads();
@@ -582,7 +590,7 @@ __device__ __forceinline__ void sweep2_body(const LbmArgs &a, const TileMap &map
     for (int k = 0; k < ROUNDS2; ++k) {
         if (m2[k] & kMaskSolid) {
             if constexpr (FLUX) {
-                if ((m2[k] & 0x1FEu) && a.flux) {
+                if ((m2[k] & 0x1FEu) && flux) {
                     // sum over q of kappa_s (w_q c_sat - f*_opp(q)(x + e_q)),
                     // in q order, for step j+1 then step j+2
                     const int idx = threadIdx.x + NT * k;
@@ -596,7 +604,7 @@ __device__ __forceinline__ void sweep2_body(const LbmArgs &a, const TileMap &map
                             const T x1 = base[kOpp[q] * (H1 * W1) + kCy[q] * W1 + kCx[q]];
                             s2 += a.kappa_s * (kW[q] * a.c_sat - double(x1));
                         }
-                    a.flux[(y0 + r) * P + x0 + c] = (fl2[k] + s1) + s2;
+                    flux[(y0 + r) * P + x0 + c] = (fl2[k] + s1) + s2;
                 }
             }
             continue;
@@ -642,10 +650,10 @@ __global__ void __launch_bounds__(NT) lbm_sweep2_kernel(LbmArgs a, TileMap map) 
     sweep2_body<S, TW, TH, NT, PART, false>(a, map);
 }
 
-// whole-patch two-step launch with the surface reaction of dissolving solids
-template <typename S, int TW, int TH, int NT>
+// two-step launch with the surface reaction of dissolving solids
+template <typename S, int TW, int TH, int NT, int PART>
 __global__ void __launch_bounds__(NT) lbm_sweep2_flux_kernel(LbmArgs a, TileMap map) {
-    sweep2_body<S, TW, TH, NT, 0, true>(a, map);
+    sweep2_body<S, TW, TH, NT, PART, true>(a, map);
 }
 
 // whole-patch two-step launch that also stores the intermediate state (a.mid)
@@ -748,7 +756,7 @@ __device__ __forceinline__ void later_stages(const LbmArgs &a, typename Pop<S>::
                                              const int (&rr)[Region<TW, TH, NT, RING>::ROUNDS],
                                              const int (&cc)[Region<TW, TH, NT, RING>::ROUNDS],
                                              const unsigned (&mo)[TW * TH / NT], double (&acc)[TW * TH / NT],
-                                             Tally &tally) {
+                                             double *flux, Tally &tally) {
     typedef typename Pop<S>::T T;
     typedef Region<TW, TH, NT, RING> R;
     constexpr int W0 = TW + 2 * G, H0 = TH + 2 * G, PL = H0 * W0;
@@ -798,7 +806,7 @@ __device__ __forceinline__ void later_stages(const LbmArgs &a, typename Pop<S>::
             for (int q = 0; q < kQ; ++q) Buf<S>::store_nt(Pop<S>::st(h[k][q], q, a), fdst, n * sz, q * SP * sz);
         }
     }
-    if constexpr (FLUX) {
+    if (FLUX && flux) {
         // link fluxes of this step at the owned solid nodes, in q order, from
         // the step's input (still in LDS: the write-back comes after the
         // barrier below)
@@ -815,7 +823,7 @@ __device__ __forceinline__ void later_stages(const LbmArgs &a, typename Pop<S>::
                     s += a.kappa_s * (kW[q] * a.c_sat - double(base[kOpp[q] * PL + kCy[q] * W0 + kCx[q]]));
             acc[k] += s;
             if constexpr (RING == 0) {
-                if (a.flux) a.flux[(y0 + idx / TW) * P + x0 + idx % TW] = acc[k];
+                flux[(y0 + idx / TW) * P + x0 + idx % TW] = acc[k];
             }
         }
     }
@@ -834,7 +842,7 @@ __device__ __forceinline__ void later_stages(const LbmArgs &a, typename Pop<S>::
         }
         __syncthreads();
         later_stages<S, TW, TH, NT, G, RING - 1, FLUX, REC, EDGE>(a, L0, x0, y0, fdst, mrs, vxr, vyr, m2, vx2, vy2,
-                                                                 rr2, cc2, mo, acc, tally);
+                                                                 rr2, cc2, mo, acc, flux, tally);
     }
 }
 
@@ -874,7 +882,8 @@ __device__ __forceinline__ void sweepk_body(const LbmArgs &a, const TileMap &map
     constexpr int RO = TW * TH / NT;
     unsigned mo[RO];
     double acc[RO];
-    if constexpr (FLUX) {
+    double *const flux = FLUX ? tile_flux<TW, TH>(a, x0, y0) : nullptr;
+    if (FLUX && flux) {
 #pragma unroll
         for (int k = 0; k < RO; ++k) {
             const int idx = threadIdx.x + NT * k;
@@ -897,7 +906,7 @@ __device__ __forceinline__ void sweepk_body(const LbmArgs &a, const TileMap &map
                     s += a.kappa_s *
                          (kW[q] * a.c_sat - double(Pop<S>::ld(Buf<S>::load(fsrc, (n + at) * sz, 0), kOpp[q], a)));
                 }
-            acc[k] = ((a.flux_first || !a.flux) ? 0.0 : a.flux[n]) + s;
+            acc[k] = (a.flux_first ? 0.0 : flux[n]) + s;
         }
     }
 
@@ -991,7 +1000,7 @@ __device__ __forceinline__ void sweepk_body(const LbmArgs &a, const TileMap &map
         region_fields<TW, TH, NT, G - 1>(N, P, x0, y0, mrs, vxr, vyr, m1, vx2, vy2, r1, c1);
         __syncthreads();
         later_stages<S, TW, TH, NT, G, G - 1, FLUX, REC, EDGE>(a, &lds[0][0][0], x0, y0, fdst, mrs, vxr, vyr, m1, vx2,
-                                                               vy2, r1, c1, mo, acc, tally);
+                                                               vy2, r1, c1, mo, acc, flux, tally);
     };
     if (edge) stages(std::true_type{});
     else stages(std::false_type{});
@@ -1013,10 +1022,10 @@ __global__ void __launch_bounds__(NT) lbm_sweep5_kernel(LbmArgs a, TileMap map) 
     sweepk_body<S, TW, TH, NT, PART, 5>(a, map);
 }
 
-// whole-patch K-step launch with the surface reaction of dissolving solids
-template <typename S, int TW, int TH, int NT, int K>
+// K-step launch with the surface reaction of dissolving solids
+template <typename S, int TW, int TH, int NT, int PART, int K>
 __global__ void __launch_bounds__(NT) lbm_sweepk_flux_kernel(LbmArgs a, TileMap map) {
-    sweepk_body<S, TW, TH, NT, 0, K, true>(a, map);
+    sweepk_body<S, TW, TH, NT, PART, K, true>(a, map);
 }
 
 // K steps (2 .. 5) that also store every step's u for the reverse mode, whose
@@ -1175,12 +1184,14 @@ hipError_t step2_impl(const LbmArgs &a, int part, int depth, int ring, const Nod
     m.count = m.part == 0 ? all : m.part == 1 ? inner : all - inner;
     if (m.count == 0) return hipSuccess;
     if (a.flux || a.kappa_s != 0.0) {
-        // dissolving solids: whole-patch launches only
-        if (m.part != 0) return hipErrorInvalidValue;
+        // dissolving solids: whole-patch launches, and frames with nothing recorded
+        if (m.part == 1 || (m.part != 0 && a.mid)) return hipErrorInvalidValue;
         if (a.mid)
             hipLaunchKernelGGL((lbm_sweep2_flux_rec_kernel<S, TW, TH, NT>), dim3(m.count), dim3(NT), 0, s, a, m);
+        else if (m.part == 0)
+            hipLaunchKernelGGL((lbm_sweep2_flux_kernel<S, TW, TH, NT, 0>), dim3(m.count), dim3(NT), 0, s, a, m);
         else
-            hipLaunchKernelGGL((lbm_sweep2_flux_kernel<S, TW, TH, NT>), dim3(m.count), dim3(NT), 0, s, a, m);
+            hipLaunchKernelGGL((lbm_sweep2_flux_kernel<S, TW, TH, NT, 2>), dim3(m.count), dim3(NT), 0, s, a, m);
         return hipGetLastError();
     }
     if (a.mid) {
@@ -1252,11 +1263,14 @@ hipError_t stepk_impl(const LbmArgs &a, int prec, int part, int depth, int ring,
         if (m.count == 0) return hipSuccess;
     }
     if (a.flux || a.kappa_s != 0.0) {
-        // dissolving solids: whole-patch launches only
-        if (m.part != 0) return hipErrorInvalidValue;
-        if constexpr (K >= 3)
-            hipLaunchKernelGGL((lbm_sweepk_flux_kernel<S, TW, TH, NT, K>), dim3(m.count), dim3(NT), 0, s, a, m);
-        else return hipErrorInvalidValue;
+        // dissolving solids: whole-patch launches and frames
+        if (K < 3 || m.part == 1) return hipErrorInvalidValue;
+        if constexpr (K >= 3) {
+            if (m.part == 0)
+                hipLaunchKernelGGL((lbm_sweepk_flux_kernel<S, TW, TH, NT, 0, K>), dim3(m.count), dim3(NT), 0, s, a, m);
+            else
+                hipLaunchKernelGGL((lbm_sweepk_flux_kernel<S, TW, TH, NT, 2, K>), dim3(m.count), dim3(NT), 0, s, a, m);
+        }
         return hipGetLastError();
     }
     if (a.u_out) {
