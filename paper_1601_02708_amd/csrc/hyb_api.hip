@@ -391,7 +391,7 @@ struct hyb_handle {
         a.N = N;
         a.pitch = lay.pitch;
         a.plane = lay.plane;
-        a.bc_kind = kinds_set ? bc_kind : nullptr;
+        a.bc_kind = any_neumann ? bc_kind : nullptr;
         a.bc_a = bc_a;
         a.bc_b = bc_b;
         a.lam = 0.0;
@@ -810,9 +810,11 @@ namespace {
 
 // the two-step kernel addresses a population buffer with 32-bit byte
 // offsets, so it serves buffers below 4 GiB (N up to about 11500 in FP64)
+bool small_buffers(const hyb_handle *h) {
+    return 9.0 * (double)h->lay.plane * (double)storage_bytes(h->prec) < 4294967295.0;
+}
 bool use_two_step(const hyb_handle *h) {
-    const bool small_buf = 9.0 * (double)h->lay.plane * (double)storage_bytes(h->prec) < 4294967295.0;
-    return !h->any_neumann && !h->wall_on && h->steps_per_launch >= 2 && small_buf;
+    return !h->any_neumann && !h->wall_on && h->steps_per_launch >= 2 && small_buffers(h);
 }
 
 // Most fine steps one launch of the forward sub-stepping takes: the
@@ -820,6 +822,14 @@ bool use_two_step(const hyb_handle *h) {
 int fuse_steps(const hyb_handle *h) {
     if (!use_two_step(h)) return 1;
     return h->steps_per_launch;
+}
+
+// The same for a plain sub-stepping call, which also takes patches with Neumann
+// slots by several steps a launch (1025^2 FP64, an outlet, five steps: 105 us as
+// 3 + 2 against 214 as single steps, each with a perimeter kernel behind it).
+int substep_fuse(const hyb_handle *h) {
+    const bool outlet = h->any_neumann && !h->wall_on && !h->dissolve_on && small_buffers(h);
+    return outlet ? h->steps_per_launch : fuse_steps(h);
 }
 
 // Fine steps of the next launch when `rem` steps of the call remain, never
@@ -935,7 +945,7 @@ hipError_t launch_fused(const hyb_handle *h, LbmArgs a, int j0, int take, hipStr
     a.lam3 = (double)(j0 + 3) / (double)h->eta;
     a.lam4 = (double)(j0 + 4) / (double)h->eta;
     a.lam5 = (double)(j0 + 5) / (double)h->eta;
-    if (take >= 3 || a.u_out) return launch_lbm_stepk(a, h->prec, take, s, part, depth, pass_ring(h), hole);
+    if (take >= 3 || a.u_out || a.bc_kind) return launch_lbm_stepk(a, h->prec, take, s, part, depth, pass_ring(h), hole);
     return launch_lbm_step2(a, h->prec, s, part, depth, pass_ring(h), hole);
 }
 
@@ -1115,7 +1125,7 @@ int substeps_impl(hyb_handle *h, int n_sub, int restart, int first_dst, int deep
     // it)
     const bool timed = h->timing && h->N > 2 && n_sub > 0;
     const bool general = h->any_neumann || h->wall_on;
-    const int fuse = fuse_steps(h);
+    const int fuse = substep_fuse(h);
     hipEvent_t g0 = nullptr, g1 = nullptr;
     size_t gslot = 0;
     int launch = 0;
@@ -1137,7 +1147,7 @@ int substeps_impl(hyb_handle *h, int n_sub, int restart, int first_dst, int deep
         // the side stream's deep tiles this launch depends on
         if (deep > 0 && launch >= 1 && launch <= deep)
             HIP_TRY(h, hipStreamWaitEvent(h->stream, h->ev_deep[launch - 1], 0));
-        if (timed && !general && !g0 && !split_now) {
+        if (timed && (!general || fuse > 1) && !g0 && !split_now) {
             HIP_TRY(h, h->take_event_pair(&g0, &g1));
             gslot = h->ev_used - 1;
             HIP_TRY(h, hipEventRecord(g0, h->stream));
@@ -1146,7 +1156,7 @@ int substeps_impl(hyb_handle *h, int n_sub, int restart, int first_dst, int deep
             HIP_TRY(h, launch_fused(h, a, h->jsub, take, h->stream, split_now ? 2 : 0, split_now ? launch : 0));
         } else {
             hipEvent_t e0 = nullptr, e1 = nullptr;
-            if (timed && general) {
+            if (timed && general && fuse == 1) {
                 HIP_TRY(h, h->take_event_pair(&e0, &e1));
                 h->ev_launches[h->ev_used - 1] = 1;
             }

@@ -70,8 +70,7 @@ __device__ __forceinline__ void solid_link_flux(const LbmArgs &a, const S *__res
     a.flux[n] = a.flux_first ? s : a.flux[n] + s;
 }
 
-__device__ int closure_neumann(double (&f)[kQ], unsigned unknown, double nx, double ny, double qp,
-                               const double (&own)[kQ]);
+__device__ int closure_neumann(double (&f)[kQ], unsigned unknown, double nx, double ny, double qp);
 
 // Interior node (1 <= i, j <= N-2): every upstream node is inside the
 // patch.  The nine pulls are issued before the flag word is known;
@@ -108,7 +107,10 @@ __device__ __forceinline__ void interior_node(const LbmArgs &a, const S *__restr
             fd[q] = double(f[q]);
             if (q > 0 && kCx[q] * nx + kCy[q] * ny < 0.0) unknown |= 1u << q;
         }
-        count_lanes(&a.counters[kCntInfeasible], closure_neumann(fd, unknown, nx, ny, 0.0, own));
+#pragma unroll
+        for (int q = 0; q < kQ; ++q)
+            if ((unknown >> q) & 1u) fd[q] = own[kOpp[q]];
+        count_lanes(&a.counters[kCntInfeasible], closure_neumann(fd, unknown, nx, ny, 0.0));
 #pragma unroll
         for (int q = 0; q < kQ; ++q) f[q] = T(fd[q]);
     } else if (m & 0x1FEu) {
@@ -189,7 +191,7 @@ __global__ void __launch_bounds__(256) lbm_bulk_kernel(LbmArgs a, int row_blocks
 }
 
 // ---------------------------------------------------------------------------
-// Maximum-entropy closures (Sec. 4.1.1), FP64, for the general perimeter.
+// Maximum-entropy closures (Sec. 4.1.1), FP64.
 //
 // Dirichlet, eq. (LBM_Dir): as dirichlet_close.
 //
@@ -203,25 +205,8 @@ __global__ void __launch_bounds__(256) lbm_bulk_kernel(LbmArgs a, int row_blocks
 // tangential ones at a corner, links a curved wall grazes) are bounced back
 // from the node's own post-collision value.
 // ---------------------------------------------------------------------------
-__device__ int closure_dirichlet(double (&f)[kQ], unsigned unknown, double up, int clamp) {
-    double known = 0.0, wsum = 0.0;
-#pragma unroll
-    for (int q = 0; q < kQ; ++q) {
-        if ((unknown >> q) & 1u) wsum += kW[q];
-        else known += f[q];
-    }
-    double R = up - known;
-    const int bad = R < 0.0;
-    if (bad && clamp) R = 0.0;
-    const double scale = R / wsum;
-#pragma unroll
-    for (int q = 0; q < kQ; ++q)
-        if ((unknown >> q) & 1u) f[q] = kW[q] * scale;
-    return bad;
-}
-
-__device__ int closure_neumann(double (&f)[kQ], unsigned unknown, double nx, double ny, double qp,
-                               const double (&own)[kQ]) {
+// (f comes in with own_opp(q), the node's own value, in the place of each unknown q)
+__device__ int closure_neumann(double (&f)[kQ], unsigned unknown, double nx, double ny, double qp) {
     unsigned out = 0;      // M-: unknowns with e.n < 0
     double flux_known = 0.0;
 #pragma unroll
@@ -229,7 +214,6 @@ __device__ int closure_neumann(double (&f)[kQ], unsigned unknown, double nx, dou
         const double dot = kCx[q] * nx + kCy[q] * ny;
         if ((unknown >> q) & 1u) {
             if (dot < 0.0) { out |= 1u << q; continue; }
-            f[q] = own[kOpp[q]];
         }
         flux_known += dot * f[q];
     }
@@ -278,6 +262,59 @@ __device__ int closure_neumann(double (&f)[kQ], unsigned unknown, double nx, dou
     return 0;
 }
 
+// The Neumann closure at perimeter node (i, j), in closed form.  On a flat edge all
+// s_i are 1, so the unknowns are w_i R' / sum w = 6 w_i R'.  At a corner they are
+// w_1 z (two, s = 1/sqrt 2) and w_5 e z^2 (s = sqrt 2), z = exp(-1 + g / sqrt 2),
+// and the condition is the quadratic w_5 e z^2 + w_1 z = R' / sqrt 2; own(q) is the
+// node's own value, for the two tangential unknowns there.  (Newton, with its
+// logarithms and exponentials, took 193 registers and 10.1 us for the 4096 nodes of
+// a 1025^2 patch.)
+template <typename T, typename Own>
+__device__ __forceinline__ bool close_outlet(T (&f)[kQ], unsigned unknown, int N, int i, int j, double qp, Own own) {
+    const int sx = i == 0 ? -1 : i == N - 1 ? 1 : 0, sy = j == 0 ? -1 : j == N - 1 ? 1 : 0;
+    const bool corner = sx != 0 && sy != 0;
+    double known = 0.0;                      // sum of (e.n) f over the known, n of length 1 or sqrt 2
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+        const int dot = kCx[q] * sx + kCy[q] * sy;
+        if ((unknown >> q) & 1u) {
+            if (dot == 0) f[q] = T(own(kOpp[q]));
+        } else {
+            known += dot * double(f[q]);
+        }
+    }
+    const double R = corner ? 0.5 * known - 0.70710678118654752 * qp : known - qp;
+    const bool bad = !(R > 0.0);
+    double axis, diag;                       // f of the unknowns by their direction
+    if (corner) {
+        const double e = 2.71828182845904524;
+        const double z = bad ? 0.0 : 2.0 * R / (kW[1] + sqrt(kW[1] * kW[1] + 4.0 * kW[5] * e * R));
+        axis = kW[1] * z;
+        diag = kW[5] * e * z * z;
+    } else {
+        const double z = bad ? 0.0 : 6.0 * R;
+        axis = kW[1] * z;
+        diag = kW[5] * z;
+    }
+#pragma unroll
+    for (int q = 1; q < kQ; ++q)
+        if (((unknown >> q) & 1u) && kCx[q] * sx + kCy[q] * sy < 0) f[q] = T(q < 5 ? axis : diag);
+    return bad;
+}
+
+// The closure of perimeter node (i, j), Dirichlet or (GEN) Neumann by its slot;
+// own(q): the node's own value before the step.
+template <typename T, bool GEN, typename Own>
+__device__ __forceinline__ bool close_slot(const LbmArgs &a, T (&f)[kQ], int i, int j, double lam, Own own) {
+    const unsigned unknown = outside_bits(a.N, i, j);
+    const int p = perimeter_slot(a.N, i, j);
+    if constexpr (GEN) {
+        if (a.bc_kind && a.bc_kind[p])
+            return close_outlet(f, unknown, a.N, i, j, mts_value(a.bc_a[p], a.bc_b[p], lam), own);
+    }
+    return dirichlet_close<T>(a, f, unknown, p, lam);
+}
+
 // perimeter nodes, Dirichlet or Neumann per slot: one thread per slot
 template <typename S>
 __global__ void __launch_bounds__(128) lbm_perimeter_kernel(LbmArgs a) {
@@ -295,41 +332,22 @@ __global__ void __launch_bounds__(128) lbm_perimeter_kernel(LbmArgs a) {
     const S *__restrict__ src = static_cast<const S *>(a.src);
     S *__restrict__ dst = static_cast<S *>(a.dst);
 
-    double f[kQ], own[kQ];
-    unsigned unknown = 0;
+    T f[kQ];
 #pragma unroll
     for (int q = 0; q < kQ; ++q) {
-        own[q] = double(Pop<S>::ld(src[q * plane + n], q, a));
         const int si = i - kCx[q], sj = j - kCy[q];
-        if (si < 0 || si >= N || sj < 0 || sj >= N) {
-            unknown |= 1u << q;
-            f[q] = 0.0;
-        } else if ((m >> q) & 1u) {
-            f[q] = double(reactive<T>(a, Pop<S>::ld(src[kOpp[q] * plane + n], kOpp[q], a), q));
-        } else {
-            f[q] = double(Pop<S>::ld(src[q * plane + sj * P + si], q, a));
-        }
+        if (si < 0 || si >= N || sj < 0 || sj >= N) f[q] = T(0);
+        else if ((m >> q) & 1u) f[q] = reactive<T>(a, Pop<S>::ld(src[kOpp[q] * plane + n], kOpp[q], a), q);
+        else f[q] = Pop<S>::ld(src[q * plane + sj * P + si], q, a);
     }
-    const int kind = a.bc_kind ? a.bc_kind[p] : 0;
-    const double value = (1.0 - a.lam) * a.bc_a[p] + a.lam * a.bc_b[p];
-    int bad;
-    if (kind == 0) {
-        bad = closure_dirichlet(f, unknown, value, a.clamp);
-    } else {
-        const int sx = (i == 0) ? -1 : (i == N - 1) ? 1 : 0;
-        const int sy = (j == 0) ? -1 : (j == N - 1) ? 1 : 0;
-        const double inv_norm = rsqrt(double(sx * sx + sy * sy));
-        bad = closure_neumann(f, unknown, sx * inv_norm, sy * inv_norm, value, own);
-    }
+    const bool bad = close_slot<T, true>(a, f, i, j, a.lam,
+                                         [&](int q) { return double(Pop<S>::ld(src[q * plane + n], q, a)); });
     count_lanes(&a.counters[kCntInfeasible], bad);
 
-    T g[kQ];
-#pragma unroll
-    for (int q = 0; q < kQ; ++q) g[q] = T(f[q]);
-    const T u = collide<T>(g, T(a.vx[n]), T(a.vy[n]), T(a.omega), node_k<T>(a, n));
+    const T u = collide<T>(f, T(a.vx[n]), T(a.vy[n]), T(a.omega), node_k<T>(a, n));
     count_lanes(&a.counters[kCntNonfinite], !finite_val(u));
 #pragma unroll
-    for (int q = 0; q < kQ; ++q) dst[q * plane + n] = Pop<S>::st(g[q], q, a);
+    for (int q = 0; q < kQ; ++q) dst[q * plane + n] = Pop<S>::st(f[q], q, a);
 }
 
 // ---------------------------------------------------------------------------
@@ -746,7 +764,7 @@ __device__ __forceinline__ void region_fields(int N, int P, int x0, int y0, cons
 // results to registers, the next region's fields fetched, barrier, results
 // written back in place, barrier, next stage.  RING = 0: the owned nodes,
 // stored to HBM.
-template <typename S, int TW, int TH, int NT, int G, int RING, bool FLUX, bool REC, bool EDGE>
+template <typename S, int TW, int TH, int NT, int G, int RING, bool FLUX, bool REC, bool GEN, bool EDGE>
 __device__ __forceinline__ void later_stages(const LbmArgs &a, typename Pop<S>::T *L0, int x0, int y0,
                                              const BufRsrc &fdst, const BufRsrc &mrs, const BufRsrc &vxr,
                                              const BufRsrc &vyr,
@@ -793,7 +811,7 @@ __device__ __forceinline__ void later_stages(const LbmArgs &a, typename Pop<S>::
                 if ((m[k] >> q) & 1u) h[k][q] = reactive<T>(a, h[k][q], q);
         }
         if (perim) {
-            const bool bad = dirichlet_close<T>(a, h[k], outside_bits(N, i, j), perimeter_slot(N, i, j), lam);
+            const bool bad = close_slot<T, GEN>(a, h[k], i, j, lam, [&](int q) { return double(base[q * PL]); });
             tally.bad += bad && owned;
         }
         const T u = collide<T>(h[k], T(vx[k]), T(vy[k]), omega, node_k<T>(a, static_cast<int>(n)));
@@ -841,15 +859,15 @@ __device__ __forceinline__ void later_stages(const LbmArgs &a, typename Pop<S>::
             for (int q = 0; q < kQ; ++q) L0[q * PL + (rr[k] + OFF) * W0 + (cc[k] + OFF)] = h[k][q];
         }
         __syncthreads();
-        later_stages<S, TW, TH, NT, G, RING - 1, FLUX, REC, EDGE>(a, L0, x0, y0, fdst, mrs, vxr, vyr, m2, vx2, vy2,
+        later_stages<S, TW, TH, NT, G, RING - 1, FLUX, REC, GEN, EDGE>(a, L0, x0, y0, fdst, mrs, vxr, vyr, m2, vx2, vy2,
                                                                  rr2, cc2, mo, acc, flux, tally);
     }
 }
 
-template <typename S, int TW, int TH, int NT, int PART, int K, bool FLUX = false, bool REC = false>
+template <typename S, int TW, int TH, int NT, int PART, int K, bool FLUX = false, bool REC = false, bool GEN = false>
 __device__ __forceinline__ void sweepk_body(const LbmArgs &a, const TileMap &map) {
     typedef typename Pop<S>::T T;
-    static_assert(K >= 3 || REC, "other two-step launches use sweep2_body");
+    static_assert(K >= 3 || REC || GEN, "other two-step launches use sweep2_body");
     static_assert((TW * TH) % NT == 0 && NT % TW == 0, "last stage: whole rows per round");
     constexpr int G = K - 1;
     typedef Region<TW, TH, NT, G> R0;
@@ -980,7 +998,9 @@ __device__ __forceinline__ void sweepk_body(const LbmArgs &a, const TileMap &map
                 else f[q] = ((m[k] >> q) & 1u) ? own : pulled;
             }
             if (EDGE && (i == 0 || j == 0 || i == N - 1 || j == N - 1)) {
-                const bool bad = dirichlet_close<T>(a, f, outside_bits(N, i, j), perimeter_slot(N, i, j), a.lam);
+                const bool bad = close_slot<T, GEN>(a, f, i, j, a.lam, [&](int q) {
+                    return double(Pop<S>::ld(Buf<S>::load(fsrc, (q * SP + n) * sz, 0), q, a));
+                });
                 tally.bad += bad && owned;
             }
             const T u = collide<T>(f, T(vx1[k]), T(vy1[k]), omega, node_k<T>(a, static_cast<int>(n)));
@@ -999,7 +1019,7 @@ __device__ __forceinline__ void sweepk_body(const LbmArgs &a, const TileMap &map
         int r1[R1::ROUNDS], c1[R1::ROUNDS];
         region_fields<TW, TH, NT, G - 1>(N, P, x0, y0, mrs, vxr, vyr, m1, vx2, vy2, r1, c1);
         __syncthreads();
-        later_stages<S, TW, TH, NT, G, G - 1, FLUX, REC, EDGE>(a, &lds[0][0][0], x0, y0, fdst, mrs, vxr, vyr, m1, vx2,
+        later_stages<S, TW, TH, NT, G, G - 1, FLUX, REC, GEN, EDGE>(a, &lds[0][0][0], x0, y0, fdst, mrs, vxr, vyr, m1, vx2,
                                                                vy2, r1, c1, mo, acc, flux, tally);
     };
     if (edge) stages(std::true_type{});
@@ -1026,6 +1046,13 @@ __global__ void __launch_bounds__(NT) lbm_sweep5_kernel(LbmArgs a, TileMap map) 
 template <typename S, int TW, int TH, int NT, int PART, int K>
 __global__ void __launch_bounds__(NT) lbm_sweepk_flux_kernel(LbmArgs a, TileMap map) {
     sweepk_body<S, TW, TH, NT, PART, K, true>(a, map);
+}
+
+// K steps (2 .. 5) on patches with Neumann slots: the edge tiles' copy takes the
+// closure of each perimeter node's slot.
+template <typename S, int TW, int TH, int NT, int PART, int K>
+__global__ void __launch_bounds__(NT) lbm_sweepk_outlet_kernel(LbmArgs a, TileMap map) {
+    sweepk_body<S, TW, TH, NT, PART, K, false, false, true>(a, map);
 }
 
 // K steps (2 .. 5) that also store every step's u for the reverse mode, whose
@@ -1273,6 +1300,12 @@ hipError_t stepk_impl(const LbmArgs &a, int prec, int part, int depth, int ring,
         }
         return hipGetLastError();
     }
+    if (a.bc_kind) {
+        if (a.u_out || m.part == 1) return hipErrorInvalidValue;
+        if (m.part == 0) hipLaunchKernelGGL((lbm_sweepk_outlet_kernel<S, TW, TH, NT, 0, K>), dim3(m.count), dim3(NT), 0, s, a, m);
+        else hipLaunchKernelGGL((lbm_sweepk_outlet_kernel<S, TW, TH, NT, 2, K>), dim3(m.count), dim3(NT), 0, s, a, m);
+        return hipGetLastError();
+    }
     if (a.u_out) {
         if constexpr (sizeof(S) >= 4) {
             if (m.part == 0) hipLaunchKernelGGL((lbm_sweepk_rec_kernel<S, TW, TH, NT, 0, K>), dim3(m.count), dim3(NT), 0, s, a, m);
@@ -1302,7 +1335,7 @@ hipError_t stepk_impl(const LbmArgs &a, int prec, int part, int depth, int ring,
 
 template <typename S>
 hipError_t stepk_dispatch(const LbmArgs &a, int prec, int K, int part, int depth, int ring, const NodeRect *hole, hipStream_t s) {
-    if (K == 2 && a.u_out) return stepk_impl<S, 2>(a, prec, part, depth, ring, hole, s);
+    if (K == 2 && (a.u_out || a.bc_kind)) return stepk_impl<S, 2>(a, prec, part, depth, ring, hole, s);
     if (K == 3) return stepk_impl<S, 3>(a, prec, part, depth, ring, hole, s);
     if (K == 4) return stepk_impl<S, 4>(a, prec, part, depth, ring, hole, s);
     if (K == 5) return stepk_impl<S, 5>(a, prec, part, depth, ring, hole, s);
