@@ -13,8 +13,12 @@
 // workgroups -- three rings of that vector and two to four partial sums -- goes
 // through global memory once per product.  Per solve (seven iterations, kernel
 // trace): M = 16 30 us against 110 us of kernels, M = 64 55 against 135, M = 128
-// beside a sweep 86 against 180.  A product's LDS reads (49 a row, 0.4 us) and
-// the round trip of the sums (about 2.5 us) are what is left.
+// beside a sweep 86 against 180; then 3.5 us less (M = 16) and 5.5 us less (M = 64,
+// 128) from a row pitch free of bank conflicts, barriers that do not wait for
+// published words and first loads asked for at once.  What is left, in cycles of a
+// phase: the product 1000-1600 (49 LDS reads a row), the sums 1500, and between
+// workgroups 2500-4500 from publishing a word to seeing it on another XCD; before
+// the first phase some 8000 for cold instructions, operands and coefficients.
 //
 // Between workgroups: every double is published as two 64-bit words, each half
 // of it under a 32-bit tag that names the launch and the phase, written and
@@ -31,7 +35,10 @@
 namespace hyb {
 namespace {
 
-constexpr int kT = kSolveTile, kF = kT + 2 * kCoarseHalo, kRows = kT * kT, kRing = kF * kF - kRows;
+// kX: row pitch of the vector in LDS, 17 modulo the 32 doubles of the banks, so that
+// the 17-node rows one wavefront reads follow each other through the banks (at a
+// pitch of 23 half the reads met in a bank: 1900 cycles a product against 1000)
+constexpr int kT = kSolveTile, kX = kT + 32, kF = kT + 2 * kCoarseHalo, kRows = kT * kT, kRing = kF * kF - kRows;
 constexpr int kLanes = 384, kWaves = kLanes / 64;
 constexpr int kSumWave = kWaves - 1;       // polls the partial sums (no ring node of its own)
 constexpr int kSpin = 1 << 22;
@@ -65,6 +72,14 @@ __device__ __forceinline__ bool collect(const Word *at, unsigned tag, double (&x
         __builtin_amdgcn_s_sleep(1);
     }
     return false;
+}
+
+// Barrier for what goes through LDS: published words are not waited for, which
+// __syncthreads would do (about 1200 cycles a product).
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 }
 
 // Sum over the wavefront, in lane 63: lane shifts within rows of sixteen, then
@@ -107,8 +122,10 @@ template <bool GIVEN>
 __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const double *__restrict__ given,
                                                               double *__restrict__ out, int tiles_x, int extrapolate,
                                                               int max_iter, double tol) {
-    __shared__ double X[kF * kF];
-    __shared__ double red[kWaves][4];
+    // (one of each for either product, so that a phase may write its own while
+    // others still read the other one's)
+    __shared__ double X[2][kF * kX];
+    __shared__ double red[2][kWaves][4];
     __shared__ double tot[4];
     __shared__ int lost;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -119,7 +136,7 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
     const bool row = tid < kRows && k0 + dk < m1 && l0 + dl < m1;
     const int node = row ? (l0 + dl) * m1 + k0 + dk : 0;
     const int pi = (node / m1 + kCoarseHalo) * c.S + (node % m1 + kCoarseHalo);
-    const int xi = (dl + kCoarseHalo) * kF + dk + kCoarseHalo;
+    const int xi = (dl + kCoarseHalo) * kX + dk + kCoarseHalo;
     const bool shown = row && nb > 1 && (dk < kCoarseHalo || dl < kCoarseHalo || dk >= kT - kCoarseHalo || dl >= kT - kCoarseHalo);
     // and its ring node
     int rk, rl;
@@ -134,7 +151,7 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
     }
     const int gk = k0 + rk - kCoarseHalo, gl = l0 + rl - kCoarseHalo;
     const bool ring = tid < kRing && nb > 1 && gk >= 0 && gl >= 0 && gk < m1 && gl < m1;
-    const int rnode = ring ? gl * m1 + gk : 0, ri = ring ? rl * kF + rk : 0;
+    const int rnode = ring ? gl * m1 + gk : 0, ri = ring ? rl * kX + rk : 0;
 
     // words: the tag base, the partial sums of both phases, two published vectors
     Word *const base_at = c.words;
@@ -143,46 +160,67 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
     unsigned tag = static_cast<unsigned>(__hip_atomic_load(base_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) + 1u;
 
     if (tid == 0) lost = 0;
-    for (int e = tid; e < kF * kF; e += kLanes) X[e] = 0.0;
+    for (int e = tid; e < 2 * kF * kX; e += kLanes) (&X[0][0])[e] = 0.0;
+    // What r0 needs is asked for first and the coefficients behind it, all at once:
+    // they are cold, and each wait in a row costs 1-2 us.
+    constexpr int NX = GIVEN ? 1 : 9;
+    double xn[NX], xg[NX], a9[NX], b9[NX];
+    int kind = -1;
+    if constexpr (GIVEN) {
+        xn[0] = given[pi];
+    } else {
+        kind = c.dkind[node];
+#pragma unroll
+        for (int o = 0; o < 9; ++o) {
+            const int p = pi + (o / 3 - 1) * c.S + (o % 3 - 1);
+            xn[o] = c.xn[p];
+            xg[o] = extrapolate ? c.xprev[p] : c.x1[p];
+            a9[o] = c.A9[(size_t)o * c.n + node];
+            b9[o] = c.B9[(size_t)o * c.n + node];
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
     double ap[kApW * kApW];
 #pragma unroll
     for (int o = 0; o < kApW * kApW; ++o) ap[o] = c.AP[(size_t)node * (kApW * kApW) + o];
+    __builtin_amdgcn_sched_barrier(0);
 
-    auto product = [&]() {
+    auto product = [&](const double *x) {
         double s[kApW];
 #pragma unroll
         for (int a = 0; a < kApW; ++a) {
             s[a] = 0.0;
 #pragma unroll
             for (int b = 0; b < kApW; ++b)
-                s[a] += ap[a * kApW + b] * X[(dl + a) * kF + dk + b];
+                s[a] += ap[a * kApW + b] * x[(dl + a) * kX + dk + b];
             // two stencil rows of reads in flight: more would not fit the
             // registers beside the coefficients
             if (a & 1) __builtin_amdgcn_sched_barrier(0);
         }
         return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + s[6]);
     };
-    // Partial sums of this workgroup into red (and to the others); ends behind a barrier.
-    auto give_sums = [&](auto &v, Word *at) {
+    // Partial sums of this workgroup into red[ph] (and to the others); ends behind a barrier.
+    auto give_sums = [&](auto &v, int ph) {
         constexpr int NV = sizeof(v) / sizeof(double);
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
             const double x = wave_total(v[k]);
-            if (lane == 63) red[wave][k] = x;
+            if (lane == 63) red[ph][wave][k] = x;
         }
-        __syncthreads();
+        lds_barrier();
         if (nb > 1 && tid < NV) {
             double x = 0.0;
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w) x += red[w][tid];
-            publish(at + (size_t)blockIdx.x * 8 + 2 * tid, x, tag);
+            for (int w = 0; w < kWaves; ++w) x += red[ph][w][tid];
+            publish(sums_at[ph] + (size_t)blockIdx.x * 8 + 2 * tid, x, tag);
         }
     };
-    // Sums over the mesh into tot: the same operations in every workgroup.
-    // Complete after the caller's next barrier.
-    auto take_sums = [&](auto &v, const Word *at) {
+    // Sums over the mesh into v: the same operations in every workgroup.  A lone
+    // one adds its wavefronts' sums in every lane, without a further barrier.
+    auto take_sums = [&](auto &v, int ph) {
         constexpr int NV = sizeof(v) / sizeof(double);
         if (nb > 1) {
+            const Word *at = sums_at[ph];
             if (wave == kSumWave) {
                 double x[NV];
 #pragma unroll
@@ -194,11 +232,16 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
                     if (lane == 63) tot[k] = y;
                 }
             }
-        } else if (tid < NV) {
-            double x = 0.0;
+            lds_barrier();
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w) x += red[w][tid];
-            tot[tid] = x;
+            for (int k = 0; k < NV; ++k) v[k] = tot[k];
+        } else {
+#pragma unroll
+            for (int k = 0; k < NV; ++k) {
+                v[k] = 0.0;
+#pragma unroll
+                for (int w = 0; w < kWaves; ++w) v[k] += red[ph][w][k];
+            }
         }
     };
 
@@ -208,30 +251,28 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
     if (row) {
         double b;
         if constexpr (GIVEN) {
-            r = given[pi];
+            r = xn[0];
             b = r;
         } else {
-            // the guess: x1 as it stands, or 2 xn - xprev
-            auto at = [&](int p) { return extrapolate ? 2.0 * c.xn[p] - c.xprev[p] : c.x1[p]; };
-            const int kind = c.dkind[node];
             double sa = 0.0, sb = 0.0;
 #pragma unroll
             for (int o = 0; o < 9; ++o) {
-                const int p = pi + (o / 3 - 1) * c.S + (o % 3 - 1);
-                const double x = at(p);
+                // the guess: x1 as it stands, or 2 xn - xprev
+                const double x = extrapolate ? 2.0 * xn[o] - xg[o] : xg[o];
                 if (o == 4) guess = x;
-                sa += c.A9[(size_t)o * c.n + node] * x;
-                sb += c.B9[(size_t)o * c.n + node] * c.xn[p];
+                sa += a9[o] * x;
+                sb += b9[o] * xn[o];
             }
-            b = kind == -1 ? sb : c.A9[(size_t)4 * c.n + node] * (kind == -2 ? c.outer_value : c.ufc[kind]);
+            b = kind == -1 ? sb : a9[4] * (kind == -2 ? c.outer_value : c.ufc[kind]);
             r = b - sa;
         }
         first[0] = b * b;
         first[1] = r * r;
         first[2] = shadow_hash(node) * r;
+        X[0][xi] = r;
         if (shown) publish(vec_at[0] + (size_t)4 * node, r, tag);
     }
-    give_sums(first, sums_at[0]);
+    give_sums(first, 0);
 
     double p = 0.0, v = 0.0, s = 0.0, t = 0.0, w = 0.0, z = 0.0, y = 0.0, rh = 0.0;
     double rho = 1.0, inv_rho = 1.0, alpha = 1.0, bnorm = 0.0, rnorm = 0.0;
@@ -244,62 +285,58 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
         if (k == 0) {
             double one[1] = {0.0};
             if (ring && !collect<1>(vec_at[0] + (size_t)4 * rnode, tag, one)) lost = 1;
-            take_sums(first, sums_at[0]);
-            if (row) X[xi] = r;
-            if (ring) X[ri] = one[0];
-            __syncthreads();
-            bnorm = sqrt(tot[0]);
-            const double gamma = sqrt(tot[1] / c.n);
-            rho = tot[1] + gamma * tot[2];
+            if (ring) X[0][ri] = one[0];
+            take_sums(first, 0);
+            bnorm = sqrt(first[0]);
+            const double gamma = sqrt(first[1] / c.n);
+            rho = first[1] + gamma * first[2];
             rh = r + gamma * shadow_hash(node);
         } else {
             double four[4];
             if (ring && !collect<2>(vec_at[0] + (size_t)4 * rnode, tag, ring_x)) lost = 1;
-            take_sums(four, sums_at[0]);
-            __syncthreads();
+            take_sums(four, 0);
             // (1 / omega and 1 / rho_{k-1} on their own: one division deep)
-            omega = tot[1] > 0.0 ? tot[0] / tot[1] : 0.0;
-            const double inv_omega = tot[1] / tot[0];
-            const double next = tot[2] - omega * tot[3];
+            omega = four[1] > 0.0 ? four[0] / four[1] : 0.0;
+            const double inv_omega = four[1] / four[0];
+            const double next = four[2] - omega * four[3];
             breakdown = omega == 0.0 || next == 0.0;
             beta = breakdown ? 0.0 : (next * inv_rho) * (alpha * inv_omega);
             rho = next;
             r = s - omega * t;
             y += alpha * p + omega * s;
-            if (row) X[xi] = r;
-            if (ring) X[ri] = ring_x[0] - omega * ring_x[1];
-            __syncthreads();
+            if (row) X[0][xi] = r;
+            if (ring) X[0][ri] = ring_x[0] - omega * ring_x[1];
+            lds_barrier();
         }
         if (lost) break;
         ++tag;
         double two[2] = {0.0, 0.0};
         if (row) {
-            w = product();
+            w = product(X[0]);
             p = r + beta * (p - omega * v);
             v = w + beta * (v - omega * z);
             two[0] = rh * v;
             two[1] = r * r;
+            X[1][xi] = v;
             if (shown) publish(vec_at[1] + (size_t)4 * node, v, tag);
         }
-        give_sums(two, sums_at[1]);
+        give_sums(two, 1);
         // ---- B(k): stop test, z = A P v, s, t ------------------------------
         double one[1] = {0.0};
         if (ring && !collect<1>(vec_at[1] + (size_t)4 * rnode, tag, one)) lost = 1;
-        take_sums(two, sums_at[1]);
-        if (row) X[xi] = v;
-        if (ring) X[ri] = one[0];
-        __syncthreads();
+        if (ring) X[1][ri] = one[0];
+        take_sums(two, 1);
         if (lost) break;
-        rnorm = sqrt(tot[1]);
+        rnorm = sqrt(two[1]);
         iters = k;
         converged = rnorm <= tol * (bnorm > 0.0 ? bnorm : 1.0);
         if (converged || breakdown || k >= max_iter || !(rnorm == rnorm)) break;
-        alpha = rho / tot[0];
+        alpha = rho / two[0];
         inv_rho = 1.0 / rho;
         ++tag;
         double four[4] = {0.0, 0.0, 0.0, 0.0};
         if (row) {
-            z = product();
+            z = product(X[1]);
             s = r - alpha * v;
             t = w - alpha * z;
             four[0] = t * s;
@@ -311,7 +348,7 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
                 publish(vec_at[0] + (size_t)4 * node + 2, t, tag);
             }
         }
-        give_sums(four, sums_at[0]);
+        give_sums(four, 0);
     }
 
     // ---- the result ---------------------------------------------------------
@@ -322,16 +359,16 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
         double one[1] = {0.0};
         if (shown) publish(vec_at[1] + (size_t)4 * node, y, tag);
         if (ring && !lost && !collect<1>(vec_at[1] + (size_t)4 * rnode, tag, one)) lost = 1;
-        __syncthreads();                   // every product's reads are done
-        if (row) X[xi] = y;
-        if (ring) X[ri] = one[0];
-        __syncthreads();
+        // (every read of X[0] came before the last sums)
+        if (row) X[0][xi] = y;
+        if (ring) X[0][ri] = one[0];
+        lds_barrier();
         if (row) {
             double acc = 0.0;
 #pragma unroll
             for (int o = 0; o < kSpaiW * kSpaiW; ++o)
                 acc += c.P[(size_t)o * c.n + node] *
-                       X[xi + (o / kSpaiW - kSpaiRadius) * kF + (o % kSpaiW - kSpaiRadius)];
+                       X[0][xi + (o / kSpaiW - kSpaiRadius) * kX + (o % kSpaiW - kSpaiRadius)];
             out[pi] = guess + acc;
         }
     }
