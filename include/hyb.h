@@ -183,9 +183,11 @@ int hyb_commit(hyb_handle *h);
 /* Algorithm 1 for one coarse step: max_schwarz times {F2C exchange, coarse
  * step, C2F exchange, eta fine steps from f*(t_n)}, then commit.  The passes
  * start from the same state and differ in the interface values only, which eta
- * fine steps carry eta nodes into the patch; with at most two multi-step
- * launches a pass (hyb_set_steps_per_launch) the passes after the first sweep
- * that frame and share the first one's state inside it.  States, counts and
+ * fine steps carry eta nodes into the patch; where a pass is at most eight
+ * multi-step launches (hyb_set_steps_per_launch) the passes after the
+ * first sweep that frame and share the first one's state inside it.  (Passes of
+ * more than three launches need a fourth population buffer for it, which ws_bytes
+ * includes when the default launch plan has that many.)  States, counts and
  * errors are those of the separate calls, bit for bit. */
 int hyb_step(hyb_handle *h, int max_schwarz);
 
@@ -281,18 +283,18 @@ int hyb_diagnostics_noalloc(hyb_handle *h, double *out);
  *   (n_sub + 4) population buffers (f_bytes each) and n_sub planes of the
  *   arithmetic type.
  * hyb_lbm_substeps_record: like hyb_lbm_substeps(h, n_sub, 1), recording
- *   the intermediate states f*(1) .. f*(n_sub - 1) and, without dissolving
- *   solids, u of each fine step's collision (the reversed steps read it for
- *   dJ/dk) in the caller's device tape (256-byte aligned, >= tape bytes);
- *   f*(0) and f*(n_sub) stay in the handle's committed and current buffers.
- *   1 <= n_sub <= eta.
+ *   what the reversed steps read in the caller's device tape (256-byte
+ *   aligned, >= tape bytes): u of each fine step's collision, and with
+ *   clamped closures or dissolving solids the intermediate states
+ *   f*(1) .. f*(n_sub - 1); f*(0) and f*(n_sub) stay in the handle's
+ *   committed and current buffers.  1 <= n_sub <= eta.
  * hyb_lbm_adjoint: tape and n_sub of the last record; the handle must be
  *   unchanged since (HYB_EINVAL after any call that steps, commits, or sets
  *   populations, interface values or rates); lam_in, lam_out: device FP64
  *   [9][N][N] (index (q*N + j)*N + i), lam_in = dJ/df*(n_sub) (kept),
  *   lam_out = dJ/df*(0) (may alias lam_in); grad_a, grad_b: device FP64
  *   [4(N-1)] and grad_k: device FP64 [N*N] or NULL, each ADDED to.  The
- *   tape's last three buffers are scratch.  Enqueued on the handle's stream;
+ *   tape's population buffers that hold no state are scratch.  Enqueued on the handle's stream;
  *   no synchronisation. */
 int hyb_adjoint_query(const hyb_handle *h, int n_sub, size_t *tape_bytes);
 int hyb_lbm_substeps_record(hyb_handle *h, int n_sub, void *tape);
@@ -313,11 +315,12 @@ int hyb_lbm_adjoint(hyb_handle *h, int n_sub, const void *tape, const double *la
  * mesh is required.
  *
  * hyb_step_adjoint_query: device bytes of the tape for `passes` >= 1.
- * hyb_step_record: hyb_step(h, passes) run with one- and two-step
- *   launches, recording the fine states (and, without dissolving solids, u
- *   of each fine step's collision), interface arrays and the state the
- *   transfers read in the caller's device tape (256-byte aligned); f*(t_n)
- *   and the step's end state stay in the handle's buffers.  Commits the step
+ * hyb_step_record: hyb_step(h, passes), recording what the reversed passes
+ *   read in the caller's device tape (256-byte aligned): u of each fine
+ *   step's collision (of the nodes that no interface value reaches once, for
+ *   every pass), the interface arrays, what the transfers read, and with
+ *   clamped closures or dissolving solids the fine states; f*(t_n) and the
+ *   step's end state stay in the handle's buffers.  Commits the step
  *   as hyb_step does (same errors; nothing is recorded on an error).
  * hyb_step_adjoint: for the last record (tape pointer of that call; the
  *   handle must be unchanged since, HYB_EINVAL after any call that steps,

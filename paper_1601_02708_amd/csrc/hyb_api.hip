@@ -848,7 +848,10 @@ int plan_take(int fuse, int rem) {
 // Whether the reversed steps read u of each collision and nothing else of the
 // states between a sweep's ends: closures clamped at 0 read the states near the
 // perimeter (dissolving solids, which read all, are the callers' matter).
-bool reverse_reads_u_only(const hyb_handle *h) { return use_two_step(h) && !h->clamp; }
+// The launch plan does not enter: a record and its reversal may have different ones.
+bool reverse_reads_u_only(const hyb_handle *h) {
+    return !h->any_neumann && !h->wall_on && small_buffers(h) && !h->clamp;
+}
 
 // Fewest nodes that the strips of the reversed steps take.  Ten reversed steps,
 // tiles alone against strips in a frame: 1000^2 FP64 266 / 300 us, FP32 155 / 192;

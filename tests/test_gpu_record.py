@@ -76,8 +76,10 @@ def test_recorded_passes_share_the_inner_nodes(precision, N, eta, spl, passes):
         res = []
         g.set_steps_per_launch(s)
         g.step_record(passes, tape)
-        g.set_steps_per_launch(2)
-        for sub in (None, torch.zeros((9, N, N), dtype=torch.float64, device=g.dev)):
+        # (the reversal under other launch plans than the record's)
+        zeros = torch.zeros((9, N, N), dtype=torch.float64, device=g.dev)
+        for reverse_spl, sub in ((2, None), (2, zeros), (1, None)):
+            g.set_steps_per_launch(reverse_spl)
             lf, ld = torch.from_numpy(lam_f).to(g.dev), torch.from_numpy(lam_d).to(g.dev)
             of, od, gk = torch.empty_like(lf), torch.empty_like(ld), torch.zeros_like(lf[0])
             g.step_adjoint(tape, lf, ld, of, od, gk, lam_sub=sub)
