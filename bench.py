@@ -76,10 +76,43 @@ def default_steps_per_launch(precision):
     return {"fp32": 5, "fp64": 4, "fp16s": 4}[precision]
 
 
-def sweep_kernel(elem_bytes, take):
-    """Symbol of the whole-patch launch (tile part 0) of the sweep that
-    takes `take` fine steps per launch."""
+def strip_nodes(N, ring):
+    """Nodes of the interior rectangle of whole 64 x 8 tiles whose ring of
+    `ring` nodes is clear of the perimeter; the library sends it to the strip
+    kernel from 1.5e6 nodes on."""
+    return max((N - 1 - ring - 64) // 64, 0) * 64 * max((N - 1 - ring - 8) // 8, 0) * 8
+
+
+def executed_updates(N, eta, passes, steps_per_launch):
+    """Lattice updates one coarse step executes (halos not counted).  Every
+    Schwarz pass asks for eta steps of N^2 nodes; passes after the first leave
+    the nodes that no interface value reaches as the first pass left them, and
+    sweep only the frame around whole 64 x 8 tiles of those (the library's
+    shared_nodes)."""
+    plan = launch_plan(eta, steps_per_launch)
+    first = eta * N * N
+    if steps_per_launch < 2 or min(plan) < 2 or len(plan) > 8 or (len(plan) > 3 and N < 4 * eta + 128):
+        return passes * first
+    x0, x1, y0, y1 = eta, N - 1 - eta, eta, N - 1 - eta
+    holes = []
+    for k in reversed(plan):
+        x0, x1, y0, y1 = -(-x0 // 64) * 64, (x1 + 1) // 64 * 64 - 1, -(-y0 // 8) * 8, (y1 + 1) // 8 * 8 - 1
+        if x1 < x0 or y1 < y0:
+            return passes * first
+        holes.insert(0, (x1 - x0 + 1) * (y1 - y0 + 1))
+        x0, x1, y0, y1 = x0 + k, x1 - k, y0 + k, y1 - k
+    if len(plan) == 3:
+        holes[2] = holes[0]
+    return first + (passes - 1) * sum(k * (N * N - h) for k, h in zip(plan, holes))
+
+
+def sweep_kernel(elem_bytes, take, N=0, k_field=False):
+    """Symbol of the kernel that sweeps the patch's inner nodes, `take` fine
+    steps per launch: strips on a large patch (a frame of tiles beside them),
+    else the whole-patch launch (tile part 0)."""
     t = {8: "double", 4: "float", 2: "_Float16"}[elem_bytes]
+    if take >= 3 and strip_nodes(N, take - 1) >= 1.5e6:
+        return f"lbm_stream_kernel<{t}, {take}, {'true' if k_field else 'false'}, false>"
     nt = 512 if elem_bytes == 8 or take >= 3 else 256
     if take >= 2:
         return f"lbm_sweep{take}_kernel<{t}, 64, 8, {nt}, 0>"
@@ -257,29 +290,35 @@ def adjoint_rate(problem, precision, reps=3):
             rec_ms += ev[0].elapsed_time(ev[1])
             adj_ms += ev[1].elapsed_time(ev[2])
     lups = eta * N * N * reps
-    # algorithmic bytes of one reversed fine step (reversed in pairs, two
-    # per launch of adj_step2_kernel, the cotangent between them on chip): per
-    # fluid node the cotangent read and the result written (9 values each),
+    # algorithmic bytes of one reversed fine step (several a launch, the
+    # cotangents between them on chip): per fluid node the cotangent read and the result written (9 values each),
     # the recorded u of the step's collision (one value, for dJ/dk), flags,
     # velocity and the FP64 dJ/dk read-modify-write; per solid node its flags
     # and the zeros written
     s = 8 if precision == "fp64" else 4
     nfl = int((problem.solid == 0).sum())
     step_bytes = nfl * (19 * s + 2 + 8 + 16) + (N * N - nfl) * (2 + 9 * s)
-    kernel = f"adj_step2_kernel<{'double, 64, 8, 512' if s == 8 else 'float, 64, 8, 256'}>"
+    t, kf = ("double" if s == 8 else "float"), ("true" if problem.k_field is not None else "false")
+    if strip_nodes(N, eta + 4) >= 1.5e6:
+        take = launch_plan(eta, 4 if s == 8 else 5)[-1]
+        kernel = f"adj_stream_kernel<{t}, {take}, {kf}, true>"
+    else:
+        take = launch_plan(eta, 3 if s == 8 else 5)[0]
+        kernel = f"adj_stepk_kernel<{t}, 64, 8, 512, {take}>"
     lim = load_limiter(problem.cfg.name, precision, kernel, kind="sq_adjoint")
     step_ms = adj_ms / (reps * eta)
     out = {"precision": precision, "value": round(lups / (adj_ms / 1e3) / 1e6, 1), "unit": "MLUPS",
            "ms_per_fine_step": round(step_ms, 4),
            "record_forward_mlups": round(lups / (rec_ms / 1e3) / 1e6, 1),
-           "roofline": {"kernel": kernel + " (two reversed steps per launch)",
+           "roofline": {"kernel": f"{kernel} ({take} reversed steps per launch)",
                         "bound": lim["bound"] if lim else "hbm", "limiter": lim["limiter"] if lim else None,
                         "algorithmic_bytes_per_step": int(step_bytes),
                         "achieved": round(step_bytes / (step_ms / 1e3) / 1e9, 1), "peak": HBM_PEAK_GBS,
                         "unit": "GB/s", "frac": round(step_bytes / (step_ms / 1e3) / 1e9 / HBM_PEAK_GBS, 4),
-                        "note": "time per reversed fine step of the whole call (the dense FP64 cotangent is "
-                                "read and written by the first and last reversed launches, no packing passes)"},
-           "note": "dJ/df*, dJ/da, dJ/db, dJ/dk over one coarse step's fine steps (tape of eta + 4 states and eta recorded u planes)"}
+                        "note": "time per reversed fine step of the whole call (where strips sweep the inner "
+                                "nodes, the frame of tiles around them and the copy of the dense FP64 cotangent "
+                                "to planes included)"},
+           "note": "dJ/df*, dJ/da, dJ/db, dJ/dk over one coarse step's fine steps (u of every step's collision recorded)"}
     g.close()
     return out
 
@@ -490,11 +529,16 @@ def dissolution_rate(steps=20, warmup=2, timing_steps=3, adjoint=True):
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1)
     sol, _, conv1 = g.dissolution_state()
+    # (a step's later passes sweep a frame only, so the launches timed are those
+    # of whole passes)
     g.kernel_timing(True)
     for _ in range(timing_steps):
-        g.step(cfg.max_iter)
+        g.lbm_substeps(cfg.eta, restart=1)
     kms, launches = g.kernel_time()
     g.kernel_timing(False)
+    g.lbm_substeps(0, restart=1)
+    for _ in range(timing_steps):
+        g.step(cfg.max_iter)
     sol2, _, conv2 = g.dissolution_state()
     adj = None
     if adjoint:
@@ -522,12 +566,14 @@ def dissolution_rate(steps=20, warmup=2, timing_steps=3, adjoint=True):
                          f"eta={cfg.eta}, {cfg.max_iter} Schwarz passes; surface reaction kappa_s={cfg.kappa_s} "
                          f"towards c_sat={cfg.c_sat}, solid masses U{list(cfg.mass_range)}"),
             "precision": "fp32", "value": round(lups / (ms / 1e3) / 1e6, 1), "unit": "MLUPS",
+            "updates_asked_per_step": cfg.max_iter * cfg.eta * N * N,
+            "updates_executed_per_step": executed_updates(N, cfg.eta, cfg.max_iter, default_steps_per_launch("fp32")),
             "ms_per_step": round(ms / steps, 4), "steps": steps, "warmup": warmup,
             "converted_in_timed_steps": int(conv1 - conv0), "converted_total": int(conv2),
             "solid_nodes_now": int(sol2.sum()),
-            "sweep_kernel": (f"lbm_sweepk_flux_kernel<float, 64, 8, 512, {plan[0]}> (launches {plan}, link fluxes at "
+            "sweep_kernel": (f"lbm_sweepk_flux_kernel<float, 64, 8, 512, 0, {plan[0]}> (launches {plan}, link fluxes at "
                              "solid nodes)" if plan[0] >= 3 else
-                             "lbm_sweep2_flux_kernel<float, 64, 8, 256> (two fine steps, link fluxes at solid nodes)"),
+                             "lbm_sweep2_flux_kernel<float, 64, 8, 256, 0> (two fine steps, link fluxes at solid nodes)"),
             "sweep_avg_launch_ms": round(avg, 5),
             "sweep_algorithmic_bytes_per_launch": int(launch_bytes),
             "sweep_achieved_gbs": round(launch_bytes / (avg / 1e3) / 1e9, 1),
@@ -699,7 +745,7 @@ def main():
     bbytes, nfl, nsol, per_fluid = sweep_bytes(problem, elem)
     spl = spl or default_steps_per_launch(args.precision)
     steps_launch, avg_kernel_ms, dom_n = dominant(kinds, cfg.eta, spl)
-    kname = sweep_kernel(elem, steps_launch)
+    kname = sweep_kernel(elem, steps_launch, N, problem.k_field is not None)
     # algorithmic bytes per launch = bytes per fluid lattice update x the
     # updates one launch performs (its fine steps over every fluid node)
     launch_bytes = bbytes * steps_launch
@@ -727,6 +773,12 @@ def main():
             "storage": {"fp64": "f64", "fp32": "f32", "fp16s": "f16 shifted"}[args.precision],
         },
         "mflups": round(value * fluid_frac, 1),
+        # value counts the updates Algorithm 1 asks for (passes x eta x N^2 a
+        # step); the passes after the first execute only those that differ
+        # from the first pass's, whose results they share bit for bit
+        "updates_asked_per_step": int(lups_step),
+        "updates_executed_per_step": int(executed_updates(N, cfg.eta, cfg.max_iter, spl)),
+        "mlups_executed": round(executed_updates(N, cfg.eta, cfg.max_iter, spl) * args.steps / (gpu_ms / 1e3) / 1e6, 1),
         "roofline": {
             "bound": lim["bound"] if lim else "hbm",
             "achieved": round(achieved, 1),
@@ -741,6 +793,8 @@ def main():
             "hbm_frac": None if traffic is None else round(traffic / (avg_kernel_ms / 1e3) / 1e9 / HBM_PEAK_GBS, 4),
             "limiter": lim["limiter"] if lim else None,
             "kernel": kname,
+            # (where strips sweep the inner nodes, avg_launch_ms covers the
+            # frame of tiles around them too)
             "fine_steps_per_launch": steps_launch,
             "fluid_updates_per_launch": int(nfl * steps_launch),
             "bytes_per_fluid_update": round(bbytes / nfl, 2),
@@ -769,7 +823,7 @@ def main():
             e2 = ELEM[other]
             b2, _, _, _ = sweep_bytes(problem, e2)
             take2, k2, _ = dominant(kinds2, cfg.eta, args.steps_per_launch or default_steps_per_launch(other))
-            kname2 = sweep_kernel(e2, take2)
+            kname2 = sweep_kernel(e2, take2, N, problem.k_field is not None)
             res[other] = {"value": round(lups_step * args.steps / (gpu_ms2 / 1e3) / 1e6, 1), "unit": "MLUPS",
                           "ms_per_step": round(gpu_ms2 / args.steps, 4), "overlap_depth": d2,
                           "sweep_kernel": kname2,

@@ -21,12 +21,14 @@ import statistics
 import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-# the source of a kernel and the header it is built with: a counter record
-# stays valid while neither changes (the reversed-step kernels live in
-# adjoint_kernels.hip, the sweeps in lbm_kernels.hip)
+# the source of a kernel and the headers it is built with: a counter record
+# stays valid while none of them changes
 def _srcs(kernel):
-    f = "adjoint_kernels.hip" if kernel.startswith("adj_") else "lbm_kernels.hip"
-    return [os.path.join(ROOT, "paper_1601_02708_amd", "csrc", n) for n in (f, "hyb_impl.h")]
+    strips = "_stream_" in kernel
+    f = {(True, True): "adjoint_stream.hip", (True, False): "adjoint_kernels.hip",
+         (False, True): "stream_kernels.hip", (False, False): "lbm_kernels.hip"}[kernel.startswith("adj_"), strips]
+    headers = ("hyb_impl.h", "lbm_device.h") + (("strip_device.h",) if strips else ())
+    return [os.path.join(ROOT, "paper_1601_02708_amd", "csrc", n) for n in (f,) + headers]
 
 
 def kernel_hash(kernel="lbm_sweep"):
@@ -65,8 +67,10 @@ def traffic(fetch_csv, write_csv, out_path, workload, precision, copy_mib, comma
     # two-step launch, else the single-step one
     mname = {"fp32": "f", "fp64": "d", "fp16s": "DF16_"}[precision]
     # demangled, or (where the demangler gives up, as for _Float16) mangled
-    sweep = [k for k in fetch if (f"{kernel}<" in k and f"<{tname}" in k and ", 0>" in k) or
-             (f"{kernel}I{mname}Li" in k and "ELi0EEEv" in k)]
+    # (strip kernels have no parts)
+    whole = "_stream_" in kernel
+    sweep = [k for k in fetch if (f"{kernel}<" in k and f"<{tname}" in k and (whole or ", 0>" in k)) or
+             (f"{kernel}I{mname}Li" in k and (whole or "ELi0EEEv" in k))]
     sweep = sweep or [k for k in fetch if "lbm_sweep2_kernel" in k and f"<{tname}" in k and ", 0>" in k]
     sweep = sweep or [k for k in fetch if "lbm_sweep_kernel" in k and f"<{tname}" in k]
     if not sweep:
@@ -116,8 +120,8 @@ def sq(out_path, workload, precision, kernel, commands, *csv_paths):
     tname = {"fp32": "float", "fp64": "double", "fp16s": "_Float16"}[precision]
     mname = {"fp32": "f", "fp64": "d", "fp16s": "DF16_"}[precision]
     # the whole-patch launch (tile part 0) of a sweep; the reversed-step
-    # kernels have no parts
-    whole = kernel.startswith("adj_")
+    # kernels and the strips have no parts
+    whole = kernel.startswith("adj_") or "_stream_" in kernel
     ks = [k for k in data if (f"{kernel}<{tname}" in k and (whole or ", 0>" in k)) or
           (kernel in k and f"I{mname}" in k and (whole or "Li0EEE" in k))]
     if not ks:
