@@ -938,7 +938,7 @@ int overlap_dmax(const hyb_handle *h) {
     return k;
 }
 
-// One multi-step launch of `take` fine steps (2, 3 or 4) from a.src to a.dst,
+// One multi-step launch of `take` fine steps (2 .. 5) from a.src to a.dst,
 // fine steps j0 + 1 .. j0 + take of the pass (interface weights (j0+1)/eta,
 // ...).
 hipError_t launch_fused(const hyb_handle *h, LbmArgs a, int j0, int take, hipStream_t s, int part, int depth,
@@ -1755,7 +1755,8 @@ int hyb_lbm_adjoint(hyb_handle *h, int n_sub, const void *tape, const double *la
 
 namespace {
 
-// Tape of hyb_step_record: f*(t_n), then eta fine states per pass; three
+// Tape of hyb_step_record: room for eta + 1 fine states per pass (kept where the
+// reversed steps read them; else scratch, and the sums the transfers need); three
 // adjoint fields; the interface arrays a and b of every pass; dJ/da, dJ/db;
 // four padded coarse vectors; dJ/du_fc; one solver result per pass; u of
 // every fine step's collision.

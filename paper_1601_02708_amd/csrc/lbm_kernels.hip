@@ -14,10 +14,11 @@
 //
 // Default path: several fine steps per launch, temporally blocked -- strips of
 // columns for large patches (stream_kernels.hip), else tiles in LDS
-// (lbm_sweep2_kernel .. lbm_sweep5_kernel).  Single-step kernels serve odd step counts
-// (lbm_sweep_kernel, perimeter Dirichlet slots in the same launch) and
-// handles with Neumann slots (lbm_bulk_kernel + lbm_perimeter_kernel, whose
-// FP64 Newton solve would otherwise lower the occupancy of the sweep).
+// (lbm_sweep2_kernel .. lbm_sweep5_kernel; lbm_sweepk_outlet_kernel with Neumann
+// slots).  Single-step kernels serve lone steps (lbm_sweep_kernel, perimeter
+// Dirichlet slots in the same launch) and handles with the closure at solid walls
+// (lbm_bulk_kernel, whose FP64 Newton solve would lower the occupancy of the
+// sweep, + lbm_perimeter_kernel).
 #include "lbm_device.h"
 
 #include <type_traits>
@@ -687,19 +688,17 @@ __global__ void __launch_bounds__(NT) lbm_sweep2_flux_rec_kernel(LbmArgs a, Tile
 }
 
 // ---------------------------------------------------------------------------
-// K fine steps per launch (K = 3, 4)
+// K fine steps per launch (K = 3 .. 5; 2 too where u is recorded or slots are Neumann)
 // ---------------------------------------------------------------------------
 // A workgroup owns a TW x TH tile.  Step j+1 runs on the tile grown by
 // G = K-1 rings, from HBM into LDS (as the two-step kernel's first half, with
 // wider rings); each next step runs on a region one ring narrower, from LDS,
 // its results held in registers across a barrier and written back over the
 // values they replace; step j+K runs on the owned nodes, from LDS, stored to
-// HBM.  Every node takes the single step's operations, and values pass
-// through the storage format between steps, so the result equals K single
-// steps up to how the compiler fuses multiply-adds in each kernel (FP64
-// states measured identical to the two-step launches', FP32 ones within a
-// few ulp).  The state crosses HBM once per K fine steps; the first
-// stage does (TW+2G)(TH+2G) / ((TW+2)(TH+2)) of the two-step kernel's
+// HBM.  Every node takes the single step's operations, so the result equals K
+// single steps, in FP64 and FP32 bit for bit (binary16 rounds once a launch).
+// The state crosses HBM once per K fine steps; the first stage does
+// (TW+2G)(TH+2G) / ((TW+2)(TH+2)) of the two-step kernel's
 // first-half work (1.24 at K = 3, 1.48 at K = 4 for 64 x 8).
 
 // interface weight of stage s (1-based) of a multi-step launch
@@ -1232,7 +1231,7 @@ hipError_t step2_impl(const LbmArgs &a, int part, int depth, int ring, const Nod
     return hipGetLastError();
 }
 
-// Tile of the multi-step sweeps (K = 3, 4): 64 x 8 owned nodes, 512 lanes
+// Tile of the multi-step sweeps: 64 x 8 owned nodes, 512 lanes
 // (one owned node per lane in the last stage); LDS holds 9 planes of
 // (TW+2K-2) x (TH+2K-2) values of the arithmetic type: 29.4 / 35.3 KB in
 // FP32, 58.8 / 70.6 KB in FP64.  Measured at pore2048 FP32 (4 + 3 + 3 per
