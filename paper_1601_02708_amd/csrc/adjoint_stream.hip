@@ -13,7 +13,7 @@
 // off the gradient once per launch.  Cotangents and gradients leave through LDS
 // as the forward rows do.
 //
-// Bound: FP64 by HBM, FP32 by VALU issue at three wavefronts a SIMD.  2048^2 FP32,
+// Bound: FP64 by HBM, FP32 by a row's latency at three wavefronts a SIMD.  2048^2 FP32,
 // five steps: 124 us (150 G node-steps a second), the tiles 290; pairs of steps in
 // tiles took 214 each.
 #include "strip_device.h"

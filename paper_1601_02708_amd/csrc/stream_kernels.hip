@@ -14,10 +14,9 @@
 // gathered and bounced back at once; 4, 7, 8 pull from row r+1 and bounce back
 // 2, 5, 6 of row r, which row r+1 pulls anyway.
 //
-// Bound: FP64 by HBM (the state read and written once, 2.6 GB at 4096^2 in
-// about 550 us: 4.7 TB/s of the 4.9 a large copy reaches), FP32 and binary16 by
-// VALU issue (about 80 instructions per node and step; a build without stores
-// took 250 us of FP32's 300).  Per four-step launch at 4096^2, porosity 0.6, with
+// Bound, four steps at 4096^2: FP64 and FP32 by HBM (counters: 2.67 GB in 538 us
+// and 1.48 GB in 285 us, 5.0 and 5.2 TB/s, where a large copy reaches 4.9; VALU 42%
+// and 57% of the issue slots), binary16 by VALU issue (92%).  Per four-step launch at 4096^2, porosity 0.6, with
 // the frame of tiles (about 28 us): FP64 582 us, FP32 323, binary16 228; the
 // LDS tiles, bound by latency at the occupancy their tile allows, took 757, 455
 // and 390.
