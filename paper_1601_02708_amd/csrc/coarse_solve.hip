@@ -184,6 +184,8 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
 #pragma unroll
     for (int o = 0; o < kApW * kApW; ++o) ap[o] = c.AP[(size_t)node * (kApW * kApW) + o];
     __builtin_amdgcn_sched_barrier(0);
+    // a word of X is cleared by another wavefront than the one that fills it below
+    lds_barrier();
 
     auto product = [&](const double *x) {
         double s[kApW];
