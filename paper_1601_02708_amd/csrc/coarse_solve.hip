@@ -25,8 +25,13 @@
 // polled with agent-scope relaxed atomics.  A word is one atomic access and
 // carries its own tag, so a reader needs no fence and no flag, and a word left
 // over from an earlier phase or launch is never taken for the expected one.
-// Every workgroup waits for every other's partial sums in every phase, so words
-// may be overwritten two phases later without further ordering.  A wait gives up
+// What orders the writing of a word over what it held: a workgroup gives its sums
+// of a phase after it has collected everything of the phase before, and goes on
+// only with everyone's sums.  So whoever has the sums of a phase may write what was
+// collected before they were given -- the words of the phase before -- but not what
+// is collected beside them: r0, s and t go through vec_at[0] and v through
+// vec_at[1] in turn, and y, published behind the last sums of B, whose v others
+// may still be waiting for, through vec_at[0].  A wait gives up
 // after kSpin polls (a workgroup that never becomes resident); the launch then
 // ends with converged = 0 and `lost` set, and the host repeats the step with the
 // kernels of coarse_kernels.hip.
@@ -363,8 +368,8 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
         if (row) out[pi] = y;
     } else {
         double one[1] = {0.0};
-        if (shown) publish(vec_at[1] + (size_t)4 * node, y, tag);
-        if (ring && !lost && !collect<1>(vec_at[1] + (size_t)4 * rnode, tag, one)) lost = 1;
+        if (shown) publish(vec_at[0] + (size_t)4 * node, y, tag);
+        if (ring && !lost && !collect<1>(vec_at[0] + (size_t)4 * rnode, tag, one)) lost = 1;
         // (every read of X[0] came before the last sums)
         if (row) X[0][xi] = y;
         if (ring) X[0][ri] = one[0];

@@ -55,3 +55,9 @@ def _same_in_every_order(got):
 @pytest.mark.parametrize("M", [8, 16])
 def test_wavefronts_of_a_workgroup(program, M):
     _same_in_every_order(_solves(program, M, 6))
+
+
+# several: a last tile one node wide, nine tiles
+@pytest.mark.parametrize("M", [17, 35])
+def test_workgroups(program, M):
+    _same_in_every_order(_solves(program, M, 6))
