@@ -164,8 +164,17 @@ int hyb_interface_exchange(hyb_handle *h, int direction);
  * data of the last HYB_F2C exchange (Algorithm 1, "advance the solution in
  * Omega_c").  Solved on the GPU by right-preconditioned BiCGSTAB (sparse
  * approximate inverse) in FP64 to ||r|| <= 1e-14 ||b||, at most max_iter
- * iterations (<= 0: 200).  Does not commit. */
+ * iterations (<= 0: 200).  Does not commit.
+ *
+ * Meshes of up to 135 elements a side are solved in one launch, whose workgroups
+ * wait for each other.  Should one of them not become resident, the others end
+ * after some seconds, one of them solves alone in the same launch, and the handle
+ * goes over to a launch per product.  hyb_set_solve_polls: how often a workgroup
+ * looks for a value of another's before that (0: never, so that every solve of
+ * more than one workgroup takes that way; < 0: the default); the next solve is
+ * one launch again.  For tests.  Synchronises. */
 int hyb_coarse_step(hyb_handle *h, int max_iter);
+int hyb_set_solve_polls(hyb_handle *h, int polls);
 
 /* n_sub fine steps (Sec. 4.1, eqs. LBE, Collision): pull streaming with
  * halfway bounce-back at solids, the maxent closure at the perimeter with
@@ -508,6 +517,7 @@ int hyb_group_create(const hyb_mesh *mesh, int n_patches, hyb_handle *const *pat
                      const double *vcoarse, double k, void *workspace, void *stream, hyb_group **out);
 int hyb_group_step(hyb_group *g, int max_schwarz);
 int hyb_group_coarse(hyb_group *g, double *out, int out_is_device);
+int hyb_group_set_solve_polls(hyb_group *g, int polls);      /* as hyb_set_solve_polls */
 void hyb_group_destroy(hyb_group *g);
 const char *hyb_group_last_error(const hyb_group *g);
 

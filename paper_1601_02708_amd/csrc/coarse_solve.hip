@@ -31,10 +31,16 @@
 // collected before they were given -- the words of the phase before -- but not what
 // is collected beside them: r0, s and t go through vec_at[0] and v through
 // vec_at[1] in turn, and y, published behind the last sums of B, whose v others
-// may still be waiting for, through vec_at[0].  A wait gives up
-// after kSpin polls (a workgroup that never becomes resident); the launch then
-// ends with converged = 0 and `lost` set, and the host repeats the step with the
-// kernels of coarse_kernels.hip.
+// may still be waiting for, through vec_at[0].
+//
+// A wait ends after c.polls polls (some seconds: a workgroup that cannot become
+// resident beside the others).  Whether the launch is given up is settled once for
+// all its workgroups: the first that gives up, or that has its part of the result,
+// says so in one word, and the others follow it.  Once a workgroup has its part,
+// everyone has given all that is still waited for, so a wait goes on; once one has
+// given up, none stores a result, and the last to end solves alone, from the same
+// inputs.  It sets `lost`, after which the host takes the kernels of
+// coarse_kernels.hip.
 #include "hyb_impl.h"
 
 namespace hyb {
@@ -46,7 +52,6 @@ namespace {
 constexpr int kT = kSolveTile, kX = kT + 32, kF = kT + 2 * kCoarseHalo, kRows = kT * kT, kRing = kF * kF - kRows;
 constexpr int kLanes = 384, kWaves = kLanes / 64;
 constexpr int kSumWave = kWaves - 1;       // polls the partial sums (no ring node of its own)
-constexpr int kSpin = 1 << 22;
 static_assert(kRows <= kLanes && kRing <= kSumWave * 64 && kSolveTiles <= 64, "one row, one ring node, one tile a lane");
 static_assert(kCoarseHalo == kApW / 2, "ring of the operator's radius");
 
@@ -58,10 +63,37 @@ __device__ __forceinline__ void publish(Word *at, double x, unsigned tag) {
     __hip_atomic_store(at + 1, t | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// the NV doubles at `at` once all carry the tag; false: given up
+__device__ __forceinline__ unsigned uniform(unsigned x) {
+    return static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(x)));
+}
+
+// How a launch ends: the word at `at` holds 2 launch + 1 once it is given up, 2 launch
+// once a workgroup has its part of the result, else an earlier launch's (`before`).
+struct Ending {
+    Word *at;
+    Word before, launch;
+    int polls;
+};
+
+// Settles it, unless another has: whether the launch is given up.
+__device__ __forceinline__ bool given_up(const Ending &e, bool lost) {
+    Word now = e.before;
+    if (now >> 1 != e.launch &&
+        __hip_atomic_compare_exchange_strong(e.at, &now, 2 * e.launch + (lost ? 1 : 0), __ATOMIC_RELAXED,
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        return lost;
+    return now & 1;
+}
+
+// the NV doubles at `at` once all carry the tag; false: the launch is given up
 template <int NV>
-__device__ __forceinline__ bool collect(const Word *at, unsigned tag, double (&x)[NV]) {
-    for (int n = 0; n < kSpin; ++n) {
+__device__ __forceinline__ bool collect(const Word *at, unsigned tag, double (&x)[NV], const Ending &e) {
+    for (unsigned n = 0;; ++n) {
+        if (n == static_cast<unsigned>(e.polls)) {
+            if (given_up(e, true)) return false;
+        } else if ((n & 1023u) == 1023u) {
+            if (__hip_atomic_load(e.at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 2 * e.launch + 1) return false;
+        }
         Word w[2 * NV];
 #pragma unroll
         for (int k = 0; k < 2 * NV; ++k) w[k] = __hip_atomic_load(at + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -76,7 +108,6 @@ __device__ __forceinline__ bool collect(const Word *at, unsigned tag, double (&x
         }
         __builtin_amdgcn_s_sleep(1);
     }
-    return false;
 }
 
 // Barrier for what goes through LDS: published words are not waited for, which
@@ -120,6 +151,119 @@ __device__ __forceinline__ double shadow_hash(int node) {
     return double(x) * (2.0 / 4294967296.0) - 1.0;
 }
 
+// The solve of a launch that was given up, by one workgroup: the recurrences of
+// coarse_kernels.hip on the vectors in global memory, every lane a row in kLanes.
+template <bool GIVEN>
+__device__ __forceinline__ void solve_alone(const CoarseDev &c, const double *given, double *out, int extrapolate,
+                                            int max_iter, double tol, double (*red)[4]) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, m1 = c.M + 1;
+    auto place = [&](int node) { return (node / m1 + kCoarseHalo) * c.S + node % m1 + kCoarseHalo; };
+    auto start = [&](int p) { return extrapolate ? 2.0 * c.xn[p] - c.xprev[p] : c.x1[p]; };
+    auto product = [&](const double *x, int node, int p) {
+        double a = 0.0;
+        for (int o = 0; o < kApW * kApW; ++o)
+            a += c.AP[(size_t)node * (kApW * kApW) + o] * x[p + (o / kApW - kCoarseHalo) * c.S + o % kApW - kCoarseHalo];
+        return a;
+    };
+    auto sum = [&](auto &v) {
+        constexpr int NV = sizeof(v) / sizeof(double);
+        __syncthreads();
+        for (int k = 0; k < NV; ++k) {
+            const double x = wave_total(v[k]);
+            if (lane == 63) red[wave][k] = x;
+        }
+        __syncthreads();
+        for (int k = 0; k < NV; ++k) {
+            v[k] = 0.0;
+            for (int w = 0; w < kWaves; ++w) v[k] += red[w][k];
+        }
+    };
+    double first[3] = {0.0, 0.0, 0.0};
+    for (int node = tid; node < c.n; node += kLanes) {
+        const int p = place(node);
+        double r, b = 0.0;
+        if (GIVEN) {
+            r = b = given[p];
+        } else {
+            double ax = 0.0;
+            for (int o = 0; o < 9; ++o) {
+                const int q = p + (o / 3 - 1) * c.S + o % 3 - 1;
+                ax += c.A9[(size_t)o * c.n + node] * start(q);
+                b += c.B9[(size_t)o * c.n + node] * c.xn[q];
+            }
+            const int kind = c.dkind[node];
+            if (kind != -1) b = c.A9[(size_t)4 * c.n + node] * (kind == -2 ? c.outer_value : c.ufc[kind]);
+            r = b - ax;
+        }
+        c.r[p] = r;
+        c.p[p] = c.v[p] = c.z[p] = c.y[p] = 0.0;
+        first[0] += b * b;
+        first[1] += r * r;
+        first[2] += shadow_hash(node) * r;
+    }
+    sum(first);
+    const double bnorm = sqrt(first[0]), scale = bnorm > 0.0 ? bnorm : 1.0, gamma = sqrt(first[1] / c.n);
+    double rho = first[1] + gamma * first[2], alpha = 1.0, omega = 0.0, beta = 0.0, rnorm;
+    bool breakdown = false;
+    int k = 0;
+    for (;; ++k) {
+        // r is there, and every lane's vectors (sum's barriers)
+        double two[2] = {0.0, 0.0};
+        for (int node = tid; node < c.n; node += kLanes) {
+            const int p = place(node);
+            const double r = c.r[p], w = product(c.r, node, p), v = c.v[p];
+            if (k == 0) c.rh[p] = r + gamma * shadow_hash(node);
+            c.p[p] = r + beta * (c.p[p] - omega * v);
+            c.w[p] = w;
+            c.v[p] = w + beta * (v - omega * c.z[p]);
+            two[0] += c.rh[p] * c.v[p];
+            two[1] += r * r;
+        }
+        sum(two);
+        rnorm = sqrt(two[1]);
+        if (rnorm <= tol * scale || breakdown || k >= max_iter || !(rnorm == rnorm)) break;
+        alpha = rho / two[0];
+        double four[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int node = tid; node < c.n; node += kLanes) {
+            const int p = place(node);
+            const double z = product(c.v, node, p), s = c.r[p] - alpha * c.v[p], t = c.w[p] - alpha * z;
+            c.z[p] = z;
+            c.s[p] = s;
+            c.t[p] = t;
+            four[0] += t * s;
+            four[1] += t * t;
+            four[2] += c.rh[p] * s;
+            four[3] += c.rh[p] * t;
+        }
+        sum(four);
+        omega = four[1] > 0.0 ? four[0] / four[1] : 0.0;
+        const double next = four[2] - omega * four[3];
+        breakdown = omega == 0.0 || next == 0.0;
+        beta = breakdown ? 0.0 : (next / rho) * (alpha / omega);
+        rho = next;
+        for (int node = tid; node < c.n; node += kLanes) {
+            const int p = place(node);
+            c.y[p] += alpha * c.p[p] + omega * c.s[p];
+            c.r[p] = c.s[p] - omega * c.t[p];
+        }
+        __syncthreads();
+    }
+    for (int node = tid; node < c.n; node += kLanes) {
+        const int p = place(node);
+        double x = GIVEN ? c.y[p] : start(p);
+        if (!GIVEN)
+            for (int o = 0; o < kSpaiW * kSpaiW; ++o)
+                x += c.P[(size_t)o * c.n + node] * c.y[p + (o / kSpaiW - kSpaiRadius) * c.S + o % kSpaiW - kSpaiRadius];
+        out[p] = x;
+    }
+    if (tid == 0) {
+        c.result->iters = k;
+        c.result->converged = rnorm <= tol * scale ? 1 : 0;
+        c.result->relres = rnorm / scale;
+        c.result->lost = 1;
+    }
+}
+
 // GIVEN: r0 is a given vector, the guess 0 and the result y itself (a solve
 // with c.AP); else r0 = b - A guess of the trapezoidal step, and the result
 // guess + P y.
@@ -132,7 +276,7 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
     __shared__ double X[2][kF * kX];
     __shared__ double red[2][kWaves][4];
     __shared__ double tot[4];
-    __shared__ int lost;
+    __shared__ int lost, arrived;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m1 = c.M + 1, nb = gridDim.x;
     const int k0 = (blockIdx.x % tiles_x) * kT, l0 = (blockIdx.x / tiles_x) * kT;
@@ -158,11 +302,13 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
     const bool ring = tid < kRing && nb > 1 && gk >= 0 && gl >= 0 && gk < m1 && gl < m1;
     const int rnode = ring ? gl * m1 + gk : 0, ri = ring ? rl * kX + rk : 0;
 
-    // words: the tag base, the partial sums of both phases, two published vectors
+    // words: the tag base, the launch's ending, who has given up, the partial sums of both phases, two published vectors
     Word *const base_at = c.words;
     Word *const sums_at[2] = {c.words + 16, c.words + 16 + kSolveTiles * 8};
     Word *const vec_at[2] = {c.words + 16 + kSolveTiles * 16, c.words + 16 + kSolveTiles * 16 + (size_t)4 * c.n};
-    unsigned tag = static_cast<unsigned>(__hip_atomic_load(base_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) + 1u;
+    Word *const arrived_at = c.words + 2;
+    const Word base = __hip_atomic_load(base_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const Word before = __hip_atomic_load(c.words + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     if (tid == 0) lost = 0;
     for (int e = tid; e < 2 * kF * kX; e += kLanes) (&X[0][0])[e] = 0.0;
@@ -191,6 +337,10 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
     __builtin_amdgcn_sched_barrier(0);
     // a word of X is cleared by another wavefront than the one that fills it below
     lds_barrier();
+    // (in scalar registers: the coefficients leave no others)
+    unsigned tag = uniform(static_cast<unsigned>(base)) + 1u;
+    const Word high = uniform(static_cast<unsigned>(before >> 32));
+    const Ending end{c.words + 1, high << 32 | uniform(static_cast<unsigned>(before)), tag, c.polls};
 
     auto product = [&](const double *x) {
         double s[kApW];
@@ -232,7 +382,7 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
                 double x[NV];
 #pragma unroll
                 for (int k = 0; k < NV; ++k) x[k] = 0.0;
-                if (lane < nb && !collect<NV>(at + (size_t)lane * 8, tag, x)) lost = 1;
+                if (lane < nb && !collect<NV>(at + (size_t)lane * 8, tag, x, end)) lost = 1;
 #pragma unroll
                 for (int k = 0; k < NV; ++k) {
                     const double y = wave_total(x[k]);
@@ -284,14 +434,14 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
     double p = 0.0, v = 0.0, s = 0.0, t = 0.0, w = 0.0, z = 0.0, y = 0.0, rh = 0.0;
     double rho = 1.0, inv_rho = 1.0, alpha = 1.0, bnorm = 0.0, rnorm = 0.0;
     int iters = 0;
-    bool converged = false;
+    bool converged = false, gone = false;
     for (int k = 0;; ++k) {
         // ---- A(k): finish iteration k-1, w = A P r, p, v = A P p ----------
         bool breakdown = false;
         double omega = 0.0, beta = 0.0, ring_x[2] = {0.0, 0.0};
         if (k == 0) {
             double one[1] = {0.0};
-            if (ring && !collect<1>(vec_at[0] + (size_t)4 * rnode, tag, one)) lost = 1;
+            if (ring && !collect<1>(vec_at[0] + (size_t)4 * rnode, tag, one, end)) lost = 1;
             if (ring) X[0][ri] = one[0];
             take_sums(first, 0);
             bnorm = sqrt(first[0]);
@@ -300,7 +450,7 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
             rh = r + gamma * shadow_hash(node);
         } else {
             double four[4];
-            if (ring && !collect<2>(vec_at[0] + (size_t)4 * rnode, tag, ring_x)) lost = 1;
+            if (ring && !collect<2>(vec_at[0] + (size_t)4 * rnode, tag, ring_x, end)) lost = 1;
             take_sums(four, 0);
             // (1 / omega and 1 / rho_{k-1} on their own: one division deep)
             omega = four[1] > 0.0 ? four[0] / four[1] : 0.0;
@@ -315,7 +465,8 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
             if (ring) X[0][ri] = ring_x[0] - omega * ring_x[1];
             lds_barrier();
         }
-        if (lost) break;
+        gone = lost;
+        if (gone) break;
         ++tag;
         double two[2] = {0.0, 0.0};
         if (row) {
@@ -330,10 +481,11 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
         give_sums(two, 1);
         // ---- B(k): stop test, z = A P v, s, t ------------------------------
         double one[1] = {0.0};
-        if (ring && !collect<1>(vec_at[1] + (size_t)4 * rnode, tag, one)) lost = 1;
+        if (ring && !collect<1>(vec_at[1] + (size_t)4 * rnode, tag, one, end)) lost = 1;
         if (ring) X[1][ri] = one[0];
         take_sums(two, 1);
-        if (lost) break;
+        gone = lost;
+        if (gone) break;
         rnorm = sqrt(two[1]);
         iters = k;
         // Stops at half the tolerance: which iteration first meets a tolerance this
@@ -364,17 +516,37 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
 
     // ---- the result ---------------------------------------------------------
     ++tag;
-    if constexpr (GIVEN) {
-        if (row) out[pi] = y;
-    } else {
+    // (a wavefront without ring nodes, beside those that wait for theirs)
+    if (nb > 1 && !gone && tid == kSumWave * 64 && given_up(end, false)) lost = 1;
+    if constexpr (!GIVEN) {
         double one[1] = {0.0};
         if (shown) publish(vec_at[0] + (size_t)4 * node, y, tag);
-        if (ring && !lost && !collect<1>(vec_at[0] + (size_t)4 * rnode, tag, one)) lost = 1;
+        if (ring && !gone && !collect<1>(vec_at[0] + (size_t)4 * rnode, tag, one, end)) lost = 1;
         // (every read of X[0] came before the last sums)
         if (row) X[0][xi] = y;
         if (ring) X[0][ri] = one[0];
-        lds_barrier();
-        if (row) {
+    }
+    lds_barrier();
+    if (lost) {
+        if (tid == 0)
+            arrived = static_cast<int>(__hip_atomic_fetch_add(arrived_at, Word(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        __syncthreads();
+        if (arrived != nb - 1) return;
+        if (tid == 0) {
+            // (a workgroup may be a phase ahead of this one)
+            __hip_atomic_store(arrived_at, Word(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(base_at, static_cast<Word>(tag + 4u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        // (the arguments read anew: kept from the start they would not fit the registers)
+        const CoarseDev *again = (const CoarseDev *)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(again));
+        solve_alone<GIVEN>(*again, given, out, extrapolate, max_iter, tol, red[0]);
+        return;
+    }
+    if (row) {
+        if constexpr (GIVEN) {
+            out[pi] = y;
+        } else {
             double acc = 0.0;
 #pragma unroll
             for (int o = 0; o < kSpaiW * kSpaiW; ++o)
@@ -385,9 +557,9 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
     }
     if (blockIdx.x == 0 && tid == 0) {
         c.result->iters = iters;
-        c.result->converged = converged && !lost ? 1 : 0;
+        c.result->converged = converged ? 1 : 0;
         c.result->relres = bnorm > 0.0 ? rnorm / bnorm : rnorm;
-        if (lost) c.result->lost = 1;      // sticks: a step has several solves
+        if (GIVEN) c.result->lost = 0;     // (else it sticks: a step has several solves)
         // (every workgroup has read the base: it took part in a later phase)
         __hip_atomic_store(base_at, static_cast<Word>(tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }

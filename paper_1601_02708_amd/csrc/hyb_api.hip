@@ -676,6 +676,7 @@ int hyb_create(const hyb_mesh *mesh, const hyb_lattice *lat, double D, const hyb
         c.partials = reinterpret_cast<double *>(h->ws + L.partials);
         c.state = reinterpret_cast<KrylovState *>(h->ws + L.barrier);
         c.words = reinterpret_cast<unsigned long long *>(h->ws + L.words);
+        c.polls = kSolvePolls;
         h->solve_one = coarse_solve_fits(mesh->M);
         c.result = h->kres;
         const std::vector<double> A9t = offset_major(ch.A9, L.n, 9), B9t = offset_major(ch.B9, L.n, 9);
@@ -1273,13 +1274,8 @@ int hyb_commit(hyb_handle *h) {
         return h->fail(HYB_ENONFINITE, "non-finite concentration in the fine subdomain; state not committed");
     }
     if (h->solved_this_step) h->last_krylov_iters = kr.iters;
-    if (h->solved_this_step && h->solve_one && kr.lost) {
-        // (never again on this handle: see coarse_solve.hip)
-        h->solve_one = false;
-        h->last_krylov_iters = h->solve_cap;
-        h->solve_budget = 0;
-        return h->fail(HYB_ENOCONV, "coarse solve: a workgroup did not become resident");
-    }
+    // (a launch that was given up cost seconds: not again on this handle)
+    if (h->solved_this_step && kr.lost) h->solve_one = false;
     if (h->solved_this_step && !kr.converged) {
         char buf[160];
         std::snprintf(buf, sizeof buf, "coarse solve did not converge (%d iterations, relres %.3e)", kr.iters,
@@ -2089,8 +2085,9 @@ int hyb_step_adjoint(hyb_handle *h, const void *tape, const double *lam_f, const
     HIP_TRY(h, hipMemcpyAsync(res.data(), kr, passes * sizeof(KrylovResult), hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
     for (int p = 0; p < passes; ++p)
+        if (h->solve_one && res[p].lost) h->solve_one = false;
+    for (int p = 0; p < passes; ++p)
         if (!res[p].converged) {
-            h->solve_one = false;
             char buf[160];
             std::snprintf(buf, sizeof buf, "transposed coarse solve of pass %d did not converge (%d iterations, relres %.3e)",
                           p, res[p].iters, res[p].relres);
@@ -2115,6 +2112,16 @@ int hyb_set_steps_per_launch(hyb_handle *h, int steps) {
     h->tune_idx = 0;
     h->tuned_depth = -1;
     h->tune_ms.clear();
+    return HYB_OK;
+}
+
+int hyb_set_solve_polls(hyb_handle *h, int polls) {
+    if (!h) return HYB_EINVAL;
+    if (!h->has_mesh) return h->fail(HYB_EINVAL, "no coarse mesh");
+    h->cd.polls = polls < 0 ? kSolvePolls : polls;
+    HIP_TRY(h, hipMemsetAsync(&h->kres->lost, 0, sizeof(int), h->stream));
+    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    h->solve_one = coarse_solve_fits(h->M);
     return HYB_OK;
 }
 
@@ -2563,6 +2570,7 @@ int hyb_group_create(const hyb_mesh *mesh, int n, hyb_handle *const *patches, do
     c.partials = reinterpret_cast<double *>(ws + L.partials);
     c.state = reinterpret_cast<KrylovState *>(ws + L.state);
     c.words = reinterpret_cast<unsigned long long *>(ws + L.words);
+    c.polls = kSolvePolls;
     g->solve_one = coarse_solve_fits(mesh->M);
     g->kres = reinterpret_cast<KrylovResult *>(ws + L.kres);
     c.result = g->kres;
@@ -2643,11 +2651,8 @@ int hyb_group_step(hyb_group *g, int max_schwarz) {
             return rc;
         if ((rc = hip(hipStreamSynchronize(g->stream), "synchronise")) != HYB_OK) return rc;
         g->last_iters = kr.iters;
-        if (kr.converged && !(g->solve_one && kr.lost)) break;
-        if (g->solve_one && kr.lost) {
-            g->solve_one = false;
-            g->budget = 0;
-        }
+        if (kr.lost) g->solve_one = false;       // as hyb_commit
+        if (kr.converged) break;
         if (g->budget >= g->cap || attempt == 1) {
             char buf[160];
             std::snprintf(buf, sizeof buf, "coarse solve did not converge (%d iterations, relres %.3e)", kr.iters,
@@ -2664,6 +2669,16 @@ int hyb_group_step(hyb_group *g, int max_schwarz) {
     g->cd.xn = g->cd.x1;
     g->cd.x1 = old_prev;
     g->solved = false;
+    return HYB_OK;
+}
+
+int hyb_group_set_solve_polls(hyb_group *g, int polls) {
+    if (!g) return HYB_EINVAL;
+    g->cd.polls = polls < 0 ? kSolvePolls : polls;
+    if (hipMemsetAsync(&g->kres->lost, 0, sizeof(int), g->stream) != hipSuccess ||
+        hipStreamSynchronize(g->stream) != hipSuccess)
+        return g->fail(HYB_EHIP, "solver state");
+    g->solve_one = coarse_solve_fits(g->M);
     return HYB_OK;
 }
 

@@ -58,7 +58,7 @@ struct KrylovResult {
     int iters;
     int converged;
     double relres;
-    int lost;                // a workgroup of the one-launch solve never showed up
+    int lost;                // a one-launch solve was given up and done by one workgroup
     unsigned pad1;
 };
 
@@ -286,11 +286,13 @@ struct CoarseDev {
     KrylovState *state;
     KrylovResult *result;
     unsigned long long *words;   // coarse_solve_words(n) words of the one-launch solve
+    int polls;               // after which a wait in it is given up
 };
 
 // The whole solve in one launch (coarse_solve.hip), for meshes that fit: from
 // c.x1 or, with extrapolate, from 2 xn - xprev; the solution in c.x1.
 constexpr int kSolveTile = 17, kSolveTiles = 64;
+constexpr int kSolvePolls = 1 << 22;     // some seconds
 bool coarse_solve_fits(int M);
 size_t coarse_solve_words(int n);
 hipError_t launch_coarse_solve_one(const CoarseDev &c, bool extrapolate, int max_iter, double tol, hipStream_t s);

@@ -104,6 +104,8 @@ SIGNATURES = {
     "hyb_group_create": (_i, [_P, _i, _P, _d, _P, _d, _P, _P, _P]),
     "hyb_group_step": (_i, [_P, _i]),
     "hyb_group_coarse": (_i, [_P, _P, _i]),
+    "hyb_set_solve_polls": (_i, [_P, _i]),
+    "hyb_group_set_solve_polls": (_i, [_P, _i]),
     "hyb_group_destroy": (None, [_P]),
     "hyb_group_last_error": (ctypes.c_char_p, [_P]),
     "hyb1d_query": (_i, [_P, _P, _P, _P, _P, _P]),
@@ -399,6 +401,10 @@ class Hybrid:
         if k.size != self.N * self.N:
             raise ValueError("k_field must have N*N entries")
         return self._check(load().hyb_set_reaction_field(self.h, _ptr(k)))
+
+    def set_solve_polls(self, polls):
+        """How long the one-launch coarse solve waits for a workgroup (tests)."""
+        return self._check(load().hyb_set_solve_polls(self.h, int(polls)))
 
     def set_outer_value(self, value):
         """Replace the Dirichlet value of the outer edges that are not natural."""
@@ -809,6 +815,11 @@ class HybridGroup:
 
     def step(self, max_schwarz):
         rc = load().hyb_group_step(self.g, int(max_schwarz))
+        if rc != HYB_OK:
+            raise HybError(rc, load().hyb_group_last_error(self.g).decode())
+
+    def set_solve_polls(self, polls):
+        rc = load().hyb_group_set_solve_polls(self.g, int(polls))
         if rc != HYB_OK:
             raise HybError(rc, load().hyb_group_last_error(self.g).decode())
 

@@ -58,6 +58,9 @@ struct Wave {
     int block, wave;
 };
 extern std::function<size_t(const std::vector<Wave> &)> policy;
+extern const void *arguments;        // the first of the kernel's
+template <typename First, typename... Rest>
+const void *first_of(const First &first, const Rest &...) { return &first; }
 
 }  // namespace emulated
 
@@ -90,8 +93,10 @@ inline bool emulated_cas(T *p, T *expected, T desired) {
 #define __builtin_amdgcn_s_sleep(n) emulated::wait(emulated::kPolled)
 #define __builtin_amdgcn_s_barrier() emulated::wait(emulated::kBarrier)
 #define __builtin_amdgcn_sched_barrier(n) ((void)0)
+#define __builtin_amdgcn_readfirstlane(x) (x)
+#define __builtin_amdgcn_kernarg_segment_ptr() (emulated::arguments)
 #define __syncthreads() emulated::wait(emulated::kBarrier)
 #define __builtin_amdgcn_update_dpp(old, x, ctrl, rows, banks, zero) emulated::from_lane(old, x, ctrl, rows)
 
 #define hipLaunchKernelGGL(kernel, grid, block, bytes, stream, ...) \
-    emulated::run_grid((grid).x, (block).x, [&] { kernel(__VA_ARGS__); })
+    (emulated::arguments = emulated::first_of(__VA_ARGS__), emulated::run_grid((grid).x, (block).x, [&] { kernel(__VA_ARGS__); }))

@@ -1,5 +1,6 @@
 // The one-launch coarse solve (coarse_solve.hip, included as KERNEL) on the CPU
-// under chosen orders of its wavefronts.  Prints a line per solve: the order, the
+// under chosen orders of its wavefronts; argv: elements a side, random orders, polls
+// of a wait before it is given up.  Prints a line per solve: the order, the
 // solve, converged, lost, iterations, the true residual over ||b||, a hash of the
 // solution.
 #include <cstdio>
@@ -38,6 +39,7 @@ namespace emulated {
 Lane *lane = nullptr;
 unsigned blocks = 0;
 long long stores = 0;
+const void *arguments = nullptr;
 std::function<size_t(const std::vector<Wave> &)> policy;
 
 static void *scheduler = nullptr;
@@ -264,8 +266,8 @@ static unsigned long long hash_of(const double *x, size_t n) {
 }
 
 int main(int argc, char **argv) {
-    if (argc < 3) return 2;
-    const int M = std::atoi(argv[1]), seeds = std::atoi(argv[2]);
+    if (argc < 4) return 2;
+    const int M = std::atoi(argv[1]), seeds = std::atoi(argv[2]), polls = std::atoi(argv[3]);
     const int side = (M + 1 + kSolveTile - 1) / kSolveTile, nb = side * side;
     struct Order {
         std::string name;
@@ -295,6 +297,7 @@ int main(int argc, char **argv) {
     for (int s = 0; s < seeds; ++s) orders.push_back({"random" + std::to_string(s), [&gen](const std::vector<emulated::Wave> &w) { return gen() % w.size(); }});
     for (const Order &o : orders) {
         Mesh m(M);
+        m.c.polls = polls;
         emulated::policy = o.pick;
         for (int solve = 0; solve < 3; ++solve) {
             const bool given = solve == 2;
