@@ -164,7 +164,9 @@ int hyb_interface_exchange(hyb_handle *h, int direction);
  * data of the last HYB_F2C exchange (Algorithm 1, "advance the solution in
  * Omega_c").  Solved on the GPU by right-preconditioned BiCGSTAB (sparse
  * approximate inverse) in FP64 to ||r|| <= 1e-14 ||b||, at most max_iter
- * iterations (<= 0: 200).  Does not commit.
+ * iterations (<= 0: 200).  Does not commit.  (Up to 135 elements a side, an iterate
+ * that lands above half of that gets one iteration more and stays the result if
+ * that is not better.)
  *
  * Meshes of up to 135 elements a side are solved in one launch, whose workgroups
  * wait for each other.  Should one of them not become resident, the others end

@@ -67,6 +67,12 @@ __device__ __forceinline__ unsigned uniform(unsigned x) {
     return static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(x)));
 }
 
+__device__ __forceinline__ double uniform(double x) {
+    const Word w = __builtin_bit_cast(Word, x);
+    const Word high = uniform(static_cast<unsigned>(w >> 32));
+    return __builtin_bit_cast(double, high << 32 | uniform(static_cast<unsigned>(w)));
+}
+
 // How a launch ends: the word at `at` holds 2 launch + 1 once it is given up, 2 launch
 // once a workgroup has its part of the result, else an earlier launch's (`before`).
 struct Ending {
@@ -337,7 +343,7 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
     __builtin_amdgcn_sched_barrier(0);
     // a word of X is cleared by another wavefront than the one that fills it below
     lds_barrier();
-    // (in scalar registers: the coefficients leave no others)
+    // (in scalar registers, as all that is the same in every lane: the coefficients leave no others)
     unsigned tag = uniform(static_cast<unsigned>(base)) + 1u;
     const Word high = uniform(static_cast<unsigned>(before >> 32));
     const Ending end{c.words + 1, high << 32 | uniform(static_cast<unsigned>(before)), tag, c.polls};
@@ -434,6 +440,7 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
     double p = 0.0, v = 0.0, s = 0.0, t = 0.0, w = 0.0, z = 0.0, y = 0.0, rh = 0.0;
     double rho = 1.0, inv_rho = 1.0, alpha = 1.0, bnorm = 0.0, rnorm = 0.0;
     int iters = 0;
+    double met = 0.0, y_met = 0.0;
     bool converged = false, gone = false;
     for (int k = 0;; ++k) {
         // ---- A(k): finish iteration k-1, w = A P r, p, v = A P p ----------
@@ -444,9 +451,9 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
             if (ring && !collect<1>(vec_at[0] + (size_t)4 * rnode, tag, one, end)) lost = 1;
             if (ring) X[0][ri] = one[0];
             take_sums(first, 0);
-            bnorm = sqrt(first[0]);
+            bnorm = uniform(sqrt(first[0]));
             const double gamma = sqrt(first[1] / c.n);
-            rho = first[1] + gamma * first[2];
+            rho = uniform(first[1] + gamma * first[2]);
             rh = r + gamma * shadow_hash(node);
         } else {
             double four[4];
@@ -458,7 +465,7 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
             const double next = four[2] - omega * four[3];
             breakdown = omega == 0.0 || next == 0.0;
             beta = breakdown ? 0.0 : (next * inv_rho) * (alpha * inv_omega);
-            rho = next;
+            rho = uniform(next);
             r = s - omega * t;
             y += alpha * p + omega * s;
             if (row) X[0][xi] = r;
@@ -488,14 +495,27 @@ __global__ void __launch_bounds__(kLanes) coarse_solve_kernel(CoarseDev c, const
         if (gone) break;
         rnorm = sqrt(two[1]);
         iters = k;
-        // Stops at half the tolerance: which iteration first meets a tolerance this
-        // near the rounding of r0 is a matter of the order of the sums, and one more
-        // (3-6 us) is needed in few solves, where it is worth a digit.
+        // An iterate that meets the tolerance by less than a factor of two gets one
+        // iteration more: which one first meets a tolerance this near the rounding
+        // of r0 is a matter of the order of the sums, and the next (3-6 us, in few
+        // solves) is worth a digit.  If it is not better, the first is the result.
         const double scale = bnorm > 0.0 ? bnorm : 1.0;
-        converged = rnorm <= tol * scale;
-        if (rnorm <= 0.5 * tol * scale || breakdown || k >= max_iter || !(rnorm == rnorm)) break;
-        alpha = rho / two[0];
-        inv_rho = 1.0 / rho;
+        if (converged || rnorm <= 0.5 * tol * scale || breakdown || k >= max_iter || !(rnorm == rnorm)) {
+            if (converged && !(rnorm <= met)) {
+                y = y_met;
+                rnorm = met;
+                iters = k - 1;
+            }
+            converged = rnorm <= tol * scale;
+            break;
+        }
+        if (rnorm <= tol * scale) {
+            converged = true;
+            met = uniform(rnorm);
+            y_met = y;
+        }
+        alpha = uniform(rho / two[0]);
+        inv_rho = uniform(1.0 / rho);
         ++tag;
         double four[4] = {0.0, 0.0, 0.0, 0.0};
         if (row) {

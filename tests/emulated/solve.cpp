@@ -1,8 +1,9 @@
 // The one-launch coarse solve (coarse_solve.hip, included as KERNEL) on the CPU
 // under chosen orders of its wavefronts; argv: elements a side, random orders, polls
-// of a wait before it is given up.  Prints a line per solve: the order, the
+// of a wait before it is given up, most iterations, tolerance, size of a part of the
+// matrix that is not symmetric.  Prints a line per solve: the order, the
 // solve, converged, lost, iterations, the true residual over ||b||, a hash of the
-// solution.
+// solution, the residual that the solve reports.
 #include <cstdio>
 #include <random>
 #include <string>
@@ -169,7 +170,7 @@ struct Mesh {
     double *base(int v) { return vec[v].data(); }
     int pad(int k, int l) const { return (l + kCoarseHalo) * S + k + kCoarseHalo; }
 
-    explicit Mesh(int M_) : M(M_), m1(M_ + 1), n(m1 * m1), S(m1 + 2 * kCoarseHalo) {
+    Mesh(int M_, double skew) : M(M_), m1(M_ + 1), n(m1 * m1), S(m1 + 2 * kCoarseHalo) {
         std::mt19937 gen(M);
         auto rnd = [&] { return gen() / 4294967296.0; };
         A9.assign(9 * (size_t)n, 0.0);
@@ -187,7 +188,7 @@ struct Mesh {
                 if (inner) dkind[node] = 0;
                 for (int o = 0; o < 9; ++o) {
                     if (!in(k + o % 3 - 1, l + o / 3 - 1)) continue;
-                    A9[(size_t)o * n + node] = o == 4 ? 1.0 + 0.5 * rnd() : edge || inner ? 0.0 : -0.1 * rnd();
+                    A9[(size_t)o * n + node] = o == 4 ? 1.0 + 0.5 * rnd() : edge || inner ? 0.0 : -0.1 * rnd() + (skew != 0.0 ? skew * (rnd() - 0.5) : 0.0);
                     B9[(size_t)o * n + node] = 0.2 * rnd();
                 }
                 for (int o = 0; o < 25; ++o)
@@ -267,6 +268,8 @@ static unsigned long long hash_of(const double *x, size_t n) {
 
 int main(int argc, char **argv) {
     if (argc < 4) return 2;
+    const int max_iter = argc > 4 ? std::atoi(argv[4]) : 200;
+    const double tol = argc > 5 ? std::atof(argv[5]) : 1e-14, skew = argc > 6 ? std::atof(argv[6]) : 0.0;
     const int M = std::atoi(argv[1]), seeds = std::atoi(argv[2]), polls = std::atoi(argv[3]);
     const int side = (M + 1 + kSolveTile - 1) / kSolveTile, nb = side * side;
     struct Order {
@@ -296,16 +299,17 @@ int main(int argc, char **argv) {
     std::mt19937 gen(1);
     for (int s = 0; s < seeds; ++s) orders.push_back({"random" + std::to_string(s), [&gen](const std::vector<emulated::Wave> &w) { return gen() % w.size(); }});
     for (const Order &o : orders) {
-        Mesh m(M);
+        Mesh m(M, skew);
         m.c.polls = polls;
         emulated::policy = o.pick;
         for (int solve = 0; solve < 3; ++solve) {
             const bool given = solve == 2;
             m.result.lost = 0;
-            if (given) launch_coarse_solve_given_one(m.c, m.rhs.data(), m.out.data(), 200, 1e-14, nullptr);
-            else launch_coarse_solve_one(m.c, solve == 0, 200, 1e-14, nullptr);
-            std::printf("%s %d %d %d %d %.3e %016llx\n", o.name.c_str(), solve, m.result.converged, m.result.lost,
-                        m.result.iters, m.residual(given), hash_of(given ? m.out.data() : m.c.x1, m.out.size()));
+            if (given) launch_coarse_solve_given_one(m.c, m.rhs.data(), m.out.data(), max_iter, tol, nullptr);
+            else launch_coarse_solve_one(m.c, solve == 0, max_iter, tol, nullptr);
+            std::printf("%s %d %d %d %d %.3e %016llx %.17e\n", o.name.c_str(), solve, m.result.converged, m.result.lost,
+                        m.result.iters, m.residual(given), hash_of(given ? m.out.data() : m.c.x1, m.out.size()),
+                        m.result.relres);
         }
     }
     return 0;
