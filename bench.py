@@ -302,7 +302,7 @@ def adjoint_rate(problem, precision, reps=3):
     t, kf = ("double" if s == 8 else "float"), ("true" if problem.k_field is not None else "false")
     if strip_nodes(N, eta + 4) >= 1.5e6:
         take = launch_plan(eta, 4 if s == 8 else 5)[-1]
-        kernel = f"adj_stream_kernel<{t}, {take}, {kf}, true>"
+        kernel = f"adj_stream_kernel<{t}, {take}, {kf}, true, false>"
     else:
         take = launch_plan(eta, 3 if s == 8 else 5)[0]
         kernel = f"adj_stepk_kernel<{t}, 64, 8, 512, {take}>"

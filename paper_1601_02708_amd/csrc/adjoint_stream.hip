@@ -11,7 +11,8 @@
 //
 // A node's dJ/dk terms, one a step, travel with its row in FP64 and are taken
 // off the gradient once per launch.  Cotangents and gradients leave through LDS
-// as the forward rows do.
+// as the forward rows do.  A launch that adds to the dense FP64 array is bound by
+// that array's traffic (2048^2 FP32, five steps: 203 us, one that overwrites it 136).
 //
 // Bound: FP64 by HBM, FP32 by a row's latency at three wavefronts a SIMD.  2048^2 FP32,
 // five steps: 124 us (150 G node-steps a second), the tiles 290; pairs of steps in
@@ -21,11 +22,13 @@
 namespace hyb {
 namespace {
 
-template <typename T, int K>
-constexpr int adjoint_waves_per_simd() { return sizeof(T) == 8 ? (K <= 2 ? 3 : 2) : (K <= 4 ? 4 : 3); }
+// ADD: the result is added to the dense array, whose row is fetched a row's time
+// before (a wavefront less at K = 4 for the registers)
+template <typename T, int K, bool ADD = false>
+constexpr int adjoint_waves_per_simd() { return sizeof(T) == 8 ? (K <= 2 ? 3 : 2) : (K <= (ADD ? 3 : 4) ? 4 : 3); }
 
-template <typename T, int K, bool KF, bool DENSE>
-__global__ void __launch_bounds__(64 * kStreamWaves, (adjoint_waves_per_simd<T, K>()))
+template <typename T, int K, bool KF, bool DENSE, bool ADD>
+__global__ void __launch_bounds__(64 * kStreamWaves, (adjoint_waves_per_simd<T, K, ADD>()))
     adj_stream_kernel(AdjSteps A, StreamMap map, NodeRect own_rect) {
     constexpr int OW = 64 - 2 * K;
     constexpr unsigned sz = sizeof(T);
@@ -144,6 +147,13 @@ __global__ void __launch_bounds__(64 * kStreamWaves, (adjoint_waves_per_simd<T, 
         vx[0] = -next.vx;                    // flipped directions
         vy[0] = -next.vy;
         if constexpr (KF) kn[0] = next.k;
+        double there[ADD ? kQ : 1];
+        if constexpr (ADD) {
+            if (col_on && r - K >= y0) {
+#pragma unroll
+                for (int q = 0; q < kQ; ++q) there[q] = A.out_dense[((size_t)q * N + r - K) * N + my_col];
+            }
+        }
         fetch(r + 1 < rend ? r + 1 : r, next);
         __builtin_amdgcn_sched_barrier(0);
         double term;
@@ -218,7 +228,7 @@ __global__ void __launch_bounds__(64 * kStreamWaves, (adjoint_waves_per_simd<T, 
 #pragma unroll
                     for (int q = 0; q < kQ; ++q) {
                         double *row = A.out_dense + ((size_t)q * N + j) * N;
-                        row[my_col] = out[q * GW + threadIdx.x];
+                        row[my_col] = ADD ? there[ADD ? q : 0] + out[q * GW + threadIdx.x] : out[q * GW + threadIdx.x];
                     }
                 }
             } else {
@@ -250,12 +260,21 @@ __global__ void __launch_bounds__(64 * kStreamWaves, (adjoint_waves_per_simd<T, 
 
 template <typename T, int K>
 hipError_t strips_impl(const AdjSteps &A, const NodeRect &nodes, const NodeRect &own, hipStream_t s) {
+    const dim3 block(64 * kStreamWaves);
+    if constexpr (sizeof(T) == 4) {
+        if (A.accumulate) {
+            const StreamMap m = stream_map(nodes, K, adjoint_waves_per_simd<T, K, true>());
+            if (A.a.kfield) hipLaunchKernelGGL((adj_stream_kernel<T, K, true, true, true>), dim3(m.count), block, 0, s, A, m, own);
+            else hipLaunchKernelGGL((adj_stream_kernel<T, K, false, true, true>), dim3(m.count), block, 0, s, A, m, own);
+            return hipGetLastError();
+        }
+    }
     const StreamMap m = stream_map(nodes, K, adjoint_waves_per_simd<T, K>());
-    const dim3 grid(m.count), block(64 * kStreamWaves);
-    if (A.a.kfield && A.out_dense) hipLaunchKernelGGL((adj_stream_kernel<T, K, true, true>), grid, block, 0, s, A, m, own);
-    else if (A.a.kfield) hipLaunchKernelGGL((adj_stream_kernel<T, K, true, false>), grid, block, 0, s, A, m, own);
-    else if (A.out_dense) hipLaunchKernelGGL((adj_stream_kernel<T, K, false, true>), grid, block, 0, s, A, m, own);
-    else hipLaunchKernelGGL((adj_stream_kernel<T, K, false, false>), grid, block, 0, s, A, m, own);
+    const dim3 grid(m.count);
+    if (A.a.kfield && A.out_dense) hipLaunchKernelGGL((adj_stream_kernel<T, K, true, true, false>), grid, block, 0, s, A, m, own);
+    else if (A.a.kfield) hipLaunchKernelGGL((adj_stream_kernel<T, K, true, false, false>), grid, block, 0, s, A, m, own);
+    else if (A.out_dense) hipLaunchKernelGGL((adj_stream_kernel<T, K, false, true, false>), grid, block, 0, s, A, m, own);
+    else hipLaunchKernelGGL((adj_stream_kernel<T, K, false, false, false>), grid, block, 0, s, A, m, own);
     return hipGetLastError();
 }
 
@@ -264,7 +283,7 @@ hipError_t strips_impl(const AdjSteps &A, const NodeRect &nodes, const NodeRect 
 hipError_t launch_adjoint_strips(const AdjSteps &A, int prec, const NodeRect &nodes, const NodeRect &own,
                                  hipStream_t s) {
     const int K = A.K, chunk = prec == HYB_FP64 ? 2 : 4;
-    if (A.a.clamp || A.a.kappa_s != 0.0 || A.inj || A.accumulate || A.lam_dense || !A.lam) return hipErrorInvalidValue;
+    if (A.a.clamp || A.a.kappa_s != 0.0 || A.inj || (A.accumulate && (!A.out_dense || prec != HYB_FP32)) || A.lam_dense || !A.lam) return hipErrorInvalidValue;
     if (A.grad_k && !A.a.u_rec) return hipErrorInvalidValue;
     if (nodes.x1 < nodes.x0 || nodes.y1 < nodes.y0) return hipSuccess;
     // no pull reaches a perimeter node's row or column

@@ -867,7 +867,7 @@ constexpr int kReverseTileSteps64 = 3;
 // tiles that no launch's halo connects with the perimeter (n + 4: the strips'
 // first column is rounded down to 16 bytes).  Every Schwarz pass has the same
 // reversed steps there, u of the collisions included, so the passes' cotangents
-// are added up and swept once.  Around them a frame of tiles, pass by pass.
+// may be added up and swept once.  Around them a frame of tiles, pass by pass.
 NodeRect reverse_deep(const hyb_handle *h, int n) {
     const NodeRect none{0, -1, 0, -1};
     // (pairs leave an odd count's last step alone, and strips take two or more)
@@ -1986,11 +1986,14 @@ int hyb_step_adjoint(hyb_handle *h, const void *tape, const double *lam_f, const
     ct.AP = h->apt;
     const int budget = std::min(200, std::max(16, 2 * h->last_krylov_iters + 6));
     // reversed steps that read no state: several a launch; on a large patch the
-    // inner nodes of all passes in one sweep of strips, from the sum of the
-    // passes' cotangents (deep_lam)
+    // inner nodes in sweeps of strips.  FP64: one for all passes, from the sum of the
+    // passes' cotangents (deep_lam).  FP32: each pass's own, whose images are added
+    // in FP64 (a sum in planes of 32 bits would lose what is small beside lam_f;
+    // gradient of a step at 2048^2, two passes of ten steps: 1822 us, with one sweep
+    // 1490).
     const bool u_only = reverse_reads_u_only(h) && !dissolving;
     const NodeRect deep = u_only && !inj && dense_in ? reverse_deep(h, h->eta) : NodeRect{0, -1, 0, -1};
-    const bool split = deep.x1 >= deep.x0;
+    const bool split = deep.x1 >= deep.x0, apart = split && h->prec == HYB_FP32;
     void *deep_lam = split ? base + T.states : nullptr;
     if (split) HIP_TRY(h, launch_adjoint_pack(a, h->prec, lam_f, deep_lam, true, h->stream));
     for (int p = passes - 1; p >= 0; --p) {
@@ -2013,10 +2016,17 @@ int hyb_step_adjoint(hyb_handle *h, const void *tape, const double *lam_f, const
             A.lam_dense = dense_in && p == passes - 1 ? lam_f : nullptr;
             A.out_dense = lam_f_out;
             A.accumulate = p != passes - 1;
+            if (apart) {
+                // (before the frame, which sweeps through lcur)
+                AdjSteps D = A;
+                D.lam = p == passes - 1 ? deep_lam : lcur;
+                D.lam_dense = nullptr;
+                HIP_TRY(h, reverse_steps(h, D, h->eta, uplane(0, 1), uplane(0, 1), deep_lam, nu, &deep, true));
+            }
             A.inner = p > 0 ? h->rec_step_inner : NodeRect{0, -1, 0, -1};
             HIP_TRY(h, reverse_steps(h, A, h->eta, uplane(p, 1), uplane(0, 1), lcur, lnext, split ? &deep : nullptr,
                                      false));
-            if (split && p == 0) {
+            if (split && !apart && p == 0) {
                 A.lam = deep_lam;
                 A.lam_dense = nullptr;
                 A.accumulate = false;
@@ -2066,7 +2076,7 @@ int hyb_step_adjoint(hyb_handle *h, const void *tape, const double *lam_f, const
         // (from the second pass on its sums over q at the nodes read, which the
         // record kept; with dissolving solids the state itself)
         const void *read = p == 0 ? state(0, 0) : dissolving ? state(p - 1, h->eta) : nullptr;
-        if (p > 0 && split)
+        if (p > 0 && split && !apart)
             HIP_TRY(h, launch_clear_tiles(a, h->prec, lcur, NodeRect{deep.x0 + h->eta, deep.x1 - h->eta, deep.y0 + h->eta,
                                                                      deep.y1 - h->eta}, h->stream));
         else if (p > 0) HIP_TRY(h, hipMemsetAsync(lcur, 0, fb, h->stream));
@@ -2078,7 +2088,7 @@ int hyb_step_adjoint(hyb_handle *h, const void *tape, const double *lam_f, const
                                                     to_dense, grad_k, h->stream));
         else
             HIP_TRY(h, launch_f2c_transpose(a, h->prec, h->f2cT_node, h->f2cT_ptr, h->f2cT_c, h->f2cT_w, h->f2cT_n,
-                                            lam_ufc, read, sums(p), p > 0 ? deep_lam : nullptr, to_pitched, to_dense, grad_k, h->stream));
+                                            lam_ufc, read, sums(p), p > 0 && !apart ? deep_lam : nullptr, to_pitched, to_dense, grad_k, h->stream));
     }
     HIP_TRY(h, launch_coarse_repad(h->cd, lam_dn, lam_d_out, true, h->stream));
     std::vector<KrylovResult> res(passes);

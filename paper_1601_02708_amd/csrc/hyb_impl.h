@@ -244,7 +244,8 @@ struct AdjSteps {
 hipError_t launch_adjoint_steps(const AdjSteps &A, int prec, hipStream_t s);
 // The same, K = 2 .. 5 (FP64: 2 .. 4), on a rectangle of nodes more than K from
 // the perimeter, x0 a multiple of 16 bytes (adjoint_stream.hip): pitched cotangent,
-// no injection, no accumulation; gradients of the nodes inside `own` only.
+// no injection, accumulation with HYB_FP32 in the dense array only; gradients of the
+// nodes inside `own` only.
 hipError_t launch_adjoint_strips(const AdjSteps &A, int prec, const NodeRect &nodes, const NodeRect &own,
                                  hipStream_t s);
 // zero populations in the tiles that do not lie inside hole
