@@ -420,11 +420,14 @@ __device__ __forceinline__ void tile_of(const TileMap &m, int t, int &tx, int &t
     ty = m.iy1 + 1 + t / m.tiles_x;
 }
 
-// where the tile at (x0, y0) sums its link fluxes (nullptr: not at all)
+// where the tile at (x0, y0) sums its link fluxes (nullptr: not at all).  No
+// short-circuit: as a chain of branches, with the pointer spilled, clang 22 lost the
+// branch that takes it (the flux kernels then summed nothing).
 template <int TW, int TH>
 __device__ __forceinline__ double *tile_flux(const LbmArgs &a, int x0, int y0) {
     const NodeRect &r = a.flux_kept;
-    return x0 >= r.x0 && x0 + TW - 1 <= r.x1 && y0 >= r.y0 && y0 + TH - 1 <= r.y1 ? nullptr : a.flux;
+    const bool kept = (x0 >= r.x0) & (x0 + TW - 1 <= r.x1) & (y0 >= r.y0) & (y0 + TH - 1 <= r.y1);
+    return kept ? nullptr : a.flux;
 }
 
 // Body of the two-step sweep.  FLUX (dissolving solids): bounce-back
