@@ -440,7 +440,8 @@ int hyb_kernel_time(hyb_handle *h, double *total_ms, int64_t *launches);
  * hyb_set_solids: replace the geometry and masses (host u8 / FP64 [N*N],
  *   e.g. a checkpoint taken with hyb_dissolution_state): only nodes solid at
  *   hyb_create may be solid (HYB_EINVAL otherwise); the flag words are
- *   rebuilt; only between coarse steps.  Synchronises.
+ *   rebuilt; only between coarse steps.  A node that it opens holds what was
+ *   set there (hyb_set_populations), else stored zeros.  Synchronises.
  * Reverse mode: the fine-step adjoint carries the link factor 1 - kappa_s
  * (the recorded steps also sum the link fluxes).  hyb_step_record records
  * the step's flag words and the solids left by its commit; hyb_step_adjoint

@@ -402,6 +402,7 @@ struct hyb_handle {
         for (int q = 0; q < kQ; ++q) a.hs_wc[kWClass[q]] = (float)kW[q] * hs_cref;
         a.kappa_s = dissolve_on ? kappa_s : 0.0;
         a.c_sat = c_sat;
+        a.keep_solid = dissolve_ws ? 1 : 0;
         a.flux = nullptr;
         a.flux_first = 0;
         a.flux_kept = NodeRect{0, -1, 0, -1};

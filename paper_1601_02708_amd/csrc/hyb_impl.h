@@ -104,6 +104,9 @@ struct LbmArgs {
     // bounce-back value relaxes towards w_q c_sat at rate kappa_s (0: off)
     double kappa_s;
     double c_sat;
+    // solids may be opened (hyb_set_solids): a sweep leaves what is stored at
+    // solid nodes as it is
+    int keep_solid;
     // dissolving solids: flux[n] (pitched, FP64) at every solid node with a
     // fluid neighbour receives the mass its reactive links move into the
     // fluid during the step (overwritten when flux_first, else added to);

@@ -1249,7 +1249,8 @@ template <typename S> struct Tile3 { static constexpr int TW = 64, TH = 8, NT = 
 // rectangles leave their bands short.  Measured per four-step launch, frame
 // included, tiles against strips: 1200^2 FP64 70.5 / 75.2 us, FP32 45.7 / 50.0,
 // binary16 43.8 / 47.8; 1501^2 FP64 110.6 / 100.7; 1800^2 FP32 87.0 / 76.1;
-// 4096^2 FP64 757 / 582, FP32 455 / 323, binary16 390 / 228.
+// 4096^2 FP64 757 / 582, FP32 455 / 323, binary16 390 / 228.  Strips store whole
+// rows, solid nodes among them, so they serve solids that stay solid.
 bool stream_pays(const NodeRect &r) {
     return (double)(r.x1 - r.x0 + 1) * (double)(r.y1 - r.y0 + 1) >= 1.5e6;
 }
@@ -1284,7 +1285,7 @@ hipError_t stepk_impl(const LbmArgs &a, int prec, int part, int depth, int ring,
     if (m.count == 0) return hipSuccess;
     if (a.mid || (a.u_out && (a.flux || a.kappa_s != 0.0))) return hipErrorInvalidValue;
     const NodeRect deep{m.ix0 * TW, (m.ix1 + 1) * TW - 1, m.iy0 * TH, (m.iy1 + 1) * TH - 1};
-    if (K >= 3 && m.part != 2 && has_rect && !hole && !(a.flux || a.kappa_s != 0.0) && stream_pays(deep)) {
+    if (K >= 3 && m.part != 2 && has_rect && !hole && !(a.flux || a.kappa_s != 0.0) && !a.keep_solid && stream_pays(deep)) {
         const hipError_t e = launch_lbm_stream(a, prec, K, deep, s);
         if (e != hipSuccess || m.part == 1) return e;
         m.part = 2;

@@ -284,7 +284,7 @@ hipError_t stream_steps(const LbmArgs &a, int K, const NodeRect &nodes, hipStrea
 }  // namespace
 
 hipError_t launch_lbm_stream(const LbmArgs &a, int prec, int K, const NodeRect &nodes, hipStream_t s) {
-    if (a.flux || a.kappa_s != 0.0 || a.mid) return hipErrorInvalidValue;
+    if (a.flux || a.kappa_s != 0.0 || a.keep_solid || a.mid) return hipErrorInvalidValue;
     if (nodes.x1 < nodes.x0 || nodes.y1 < nodes.y0) return hipSuccess;
     // every pull of every step stays inside the patch and off its perimeter nodes
     if (nodes.x0 < K || nodes.y0 < K || nodes.x1 > a.N - 1 - K || nodes.y1 > a.N - 1 - K) return hipErrorInvalidValue;
