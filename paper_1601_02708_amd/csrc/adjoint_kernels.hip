@@ -518,10 +518,11 @@ __global__ void __launch_bounds__(NT) adj_stepk_kernel(AdjSteps A, FrameMap map)
     int tx, ty;
     frame_tile(map, xcd_tile(blockIdx.x, map.count), tx, ty);
     const int x0 = tx * TW, y0 = ty * TH, N = A.a.N;
-    const bool adds = !(tx >= map.qx0 && tx <= map.qx1 && ty >= map.qy0 && ty <= map.qy1);
+    // (bitwise: see tile_flux of the forward sweeps)
+    const bool adds = !((tx >= map.qx0) & (tx <= map.qx1) & (ty >= map.qy0) & (ty <= map.qy1));
     const bool edge = x0 - K <= 0 || y0 - K <= 0 || x0 + TW + K - 1 >= N - 1 || y0 + TH + K - 1 >= N - 1;
     const NodeRect &in = A.inner;
-    const bool inner = x0 >= in.x0 && x0 + TW - 1 <= in.x1 && y0 >= in.y0 && y0 + TH - 1 <= in.y1;
+    const bool inner = (x0 >= in.x0) & (x0 + TW - 1 <= in.x1) & (y0 >= in.y0) & (y0 + TH - 1 <= in.y1);
     const char *u_rec = static_cast<const char *>(inner ? A.u_inner : A.a.u_rec);
     if (edge) reversed_stages<T, TW, TH, NT, K, K, true>(A, u_rec, nus, kst, x0, y0, adds);
     else reversed_stages<T, TW, TH, NT, K, K, false>(A, u_rec, nus, kst, x0, y0, adds);
