@@ -411,6 +411,14 @@ struct hyb_handle {
         a.wall_ny = wall_on ? wall_ny : nullptr;
         return a;
     }
+    // a buffer whose contents nobody reads any more: neither the committed nor the
+    // current state, nor the start of a recorded step that may still be reversed
+    int unread() const {
+        const bool kept = rec_step_tape && rec_step_gen == gen;
+        for (int b = 0; b < 3; ++b)
+            if (b != frozen && b != cur && !(kept && b == rec_step_f0)) return b;
+        return -1;
+    }
     // buffer that is neither the committed state nor `a`
     int spare(int a) const {
         for (int b = 0; b < 3; ++b)
@@ -1405,7 +1413,7 @@ int hyb_concentration(hyb_handle *h, int which, double *out, int out_is_device) 
     if (!h || !out) return HYB_EINVAL;
     if (which == HYB_FINE) {
         const size_t bytes = (size_t)h->N * h->N * 8;
-        double *dev = out_is_device ? out : static_cast<double *>(h->f[h->spare(h->cur == h->frozen ? -1 : h->cur)]);
+        double *dev = out_is_device ? out : static_cast<double *>(h->f[h->unread()]);
         LbmArgs a = h->lbm_args(h->cur, -1);
         HIP_TRY(h, launch_concentration(a, dev, h->prec, h->stream));
         if (!out_is_device) HIP_TRY(h, hipMemcpyAsync(out, dev, bytes, hipMemcpyDeviceToHost, h->stream));
