@@ -107,6 +107,27 @@ def executed_updates(N, eta, passes, steps_per_launch):
     return first + (passes - 1) * sum(k * (N * N - h) for k, h in zip(plan, holes))
 
 
+def step_rates(cfg, steps_per_launch, steps, gpu_ms):
+    """MLUPS of `steps` coarse steps: `value` counts the lattice updates that are
+    executed, `mlups_asked` those that Algorithm 1 names (passes x eta x N^2 a
+    step), whose shared part the passes after the first do not repeat."""
+    asked = cfg.max_iter * cfg.eta * cfg.N ** 2
+    done = executed_updates(cfg.N, cfg.eta, cfg.max_iter, steps_per_launch)
+    rate = lambda updates: round(updates * steps / (gpu_ms / 1e3) / 1e6, 1)  # noqa: E731
+    return {"value": rate(done), "mlups_asked": rate(asked), "updates_executed_per_step": int(done),
+            "updates_asked_per_step": int(asked)}
+
+
+def hbm_limiter(lim, traffic, launch_ms):
+    """The counters' reading of a launch, or HBM where its traffic moves at the
+    rate of a large copy (the sequencer's counters see waits, not what they wait
+    for)."""
+    if traffic is not None and traffic / (launch_ms / 1e3) / 1e9 >= 0.9 * COPY_GBS:
+        return {"bound": "hbm", "limiter": "HBM: the launch moves its traffic at nine tenths of a large copy's rate "
+                                           "or more"}
+    return lim
+
+
 def sweep_kernel(elem_bytes, take, N=0, k_field=False):
     """Symbol of the kernel that sweeps the patch's inner nodes, `take` fine
     steps per launch: strips on a large patch (a frame of tiles beside them),
@@ -327,8 +348,9 @@ def adjoint_rate(problem, precision, reps=3):
 def step_adjoint_rate(problem, precision, reps=3):
     """Reverse mode of one whole coarse step (hyb_step_record, then
     hyb_step_adjoint: every Schwarz pass's fine steps, transfers and coarse
-    solve transposed); MLUPS over the step's lattice updates (passes x eta x
-    all nodes) for the adjoint and for the recording forward."""
+    solve transposed); MLUPS over the step's lattice updates as asked (passes x
+    eta x all nodes, although passes share nodes) for the adjoint and for the
+    recording forward."""
     import torch
     from paper_1601_02708_amd import hyb
     g = hyb.Hybrid.from_problem(problem, precision=precision, device="cuda:0")
@@ -357,7 +379,7 @@ def step_adjoint_rate(problem, precision, reps=3):
     res = {"precision": precision, "value": round(lups / (adj_ms / 1e3) / 1e6, 1), "unit": "MLUPS",
            "ms_per_coarse_step": round(adj_ms / reps, 4),
            "record_forward_mlups": round(lups / (rec_ms / 1e3) / 1e6, 1),
-           "tape_bytes": int(tape.numel()),
+           "tape_bytes": int(tape.numel()), "updates": "as asked: passes x eta x N^2, though passes share nodes",
            "note": "dJ/df*(t_n), dJ/dd^n, dJ/dk through one coarse step of Algorithm 1 "
                    "(fine steps, transfers and the transposed coarse solve of every Schwarz pass)"}
     g.close()
@@ -559,16 +581,16 @@ def dissolution_rate(steps=20, warmup=2, timing_steps=3, adjoint=True):
     k_avg = cfg.eta / len(plan)             # fine steps per launch (uniform at eta = 20: 5)
     launch_bytes = k_avg * (nfl * (18 * 4 + 8 + 2) + (N * N - nfl) * 2 + 4 * (N - 1) * 16) + surface * 16
     avg = kms / max(launches, 1)
-    lups = steps * cfg.max_iter * cfg.eta * N * N
+    rates = step_rates(cfg, default_steps_per_launch("fp32"), steps, ms)
     g.close()
     out_adj = {} if adj is None else {"adjoint_fp32": adj}
     return {"workload": (f"{cfg.name}: {N}^2 D2Q9 lattice, random disks (porosity {p.porosity:.4f}), 8-mode "
                          f"stream-function velocity max 0.05, D={cfg.D}, k={cfg.k}, {cfg.M}^2 Q1 SUPG mesh, "
                          f"eta={cfg.eta}, {cfg.max_iter} Schwarz passes; surface reaction kappa_s={cfg.kappa_s} "
                          f"towards c_sat={cfg.c_sat}, solid masses U{list(cfg.mass_range)}"),
-            "precision": "fp32", "value": round(lups / (ms / 1e3) / 1e6, 1), "unit": "MLUPS",
-            "updates_asked_per_step": cfg.max_iter * cfg.eta * N * N,
-            "updates_executed_per_step": executed_updates(N, cfg.eta, cfg.max_iter, default_steps_per_launch("fp32")),
+            "precision": "fp32", "value": rates["value"], "unit": "MLUPS", "mlups_asked": rates["mlups_asked"],
+            "updates_asked_per_step": rates["updates_asked_per_step"],
+            "updates_executed_per_step": rates["updates_executed_per_step"],
             "ms_per_step": round(ms / steps, 4), "steps": steps, "warmup": warmup,
             "converted_in_timed_steps": int(conv1 - conv0), "converted_total": int(conv2),
             "solid_nodes_now": int(sol2.sum()),
@@ -731,7 +753,6 @@ def main():
     cfg = configs.CONFIGS[args.workload]
     problem = configs.build_problem(cfg)
     N = cfg.N
-    lups_step = cfg.max_iter * cfg.eta * N * N
     fluid_frac = float((problem.solid == 0).mean())
     elem = ELEM[args.precision]
     print(f"[bench] {cfg.name} {args.precision}: {args.warmup} warmup + {args.steps} timed coarse steps",
@@ -742,9 +763,9 @@ def main():
     g, wall, gpu_ms, kms, launches, st, _, kinds = run_gpu(problem, args.precision, args.steps, args.warmup,
                                                            spl, depth, args.timing_steps)
     ms_step = gpu_ms / args.steps
-    value = lups_step * args.steps / (gpu_ms / 1e3) / 1e6
     bbytes, nfl, nsol, per_fluid = sweep_bytes(problem, elem)
     spl = spl or default_steps_per_launch(args.precision)
+    rates = step_rates(cfg, spl, args.steps, gpu_ms)
     steps_launch, avg_kernel_ms, dom_n = dominant(kinds, cfg.eta, spl)
     kname = sweep_kernel(elem, steps_launch, N, problem.k_field is not None)
     # algorithmic bytes per launch = bytes per fluid lattice update x the
@@ -752,14 +773,10 @@ def main():
     launch_bytes = bbytes * steps_launch
     achieved = launch_bytes / (avg_kernel_ms / 1e3) / 1e9
     traffic = load_traffic(cfg.name, args.precision, kname)
-    lim = load_limiter(cfg.name, args.precision, kname)
-    if traffic is not None and traffic / (avg_kernel_ms / 1e3) / 1e9 >= 0.9 * COPY_GBS:
-        # the sequencer's counters see waits, not what they wait for
-        lim = {"bound": "hbm", "limiter": "HBM: the launch moves its traffic at the rate of a large copy; " +
-               (lim["limiter"] if lim else "")}
+    lim = hbm_limiter(load_limiter(cfg.name, args.precision, kname), traffic, avg_kernel_ms)
     res = {
         "metric": METRIC,
-        "value": round(value, 1),
+        "value": rates["value"],
         "unit": "MLUPS",
         "n_gpus": 1,
         "steps": args.steps,
@@ -777,13 +794,14 @@ def main():
             "lattice": N, "mesh": cfg.M, "eta": cfg.eta, "schwarz": cfg.max_iter, "precision": args.precision,
             "storage": {"fp64": "f64", "fp32": "f32", "fp16s": "f16 shifted"}[args.precision],
         },
-        "mflups": round(value * fluid_frac, 1),
-        # value counts the updates Algorithm 1 asks for (passes x eta x N^2 a
-        # step); the passes after the first execute only those that differ
-        # from the first pass's, whose results they share bit for bit
-        "updates_asked_per_step": int(lups_step),
-        "updates_executed_per_step": int(executed_updates(N, cfg.eta, cfg.max_iter, spl)),
-        "mlups_executed": round(executed_updates(N, cfg.eta, cfg.max_iter, spl) * args.steps / (gpu_ms / 1e3) / 1e6, 1),
+        "mflups": round(rates["value"] * fluid_frac, 1),
+        # value counts the updates executed: the passes after the first sweep only
+        # the nodes that differ from the first pass's and share the others bit for
+        # bit (mlups_asked counts passes x eta x N^2 a step, as records made while
+        # every pass swept the whole patch)
+        "mlups_asked": rates["mlups_asked"],
+        "updates_asked_per_step": rates["updates_asked_per_step"],
+        "updates_executed_per_step": rates["updates_executed_per_step"],
         "roofline": {
             "bound": lim["bound"] if lim else "hbm",
             "achieved": round(achieved, 1),
@@ -829,7 +847,8 @@ def main():
             b2, _, _, _ = sweep_bytes(problem, e2)
             take2, k2, _ = dominant(kinds2, cfg.eta, args.steps_per_launch or default_steps_per_launch(other))
             kname2 = sweep_kernel(e2, take2, N, problem.k_field is not None)
-            res[other] = {"value": round(lups_step * args.steps / (gpu_ms2 / 1e3) / 1e6, 1), "unit": "MLUPS",
+            rates2 = step_rates(cfg, args.steps_per_launch or default_steps_per_launch(other), args.steps, gpu_ms2)
+            res[other] = {"value": rates2["value"], "unit": "MLUPS", "mlups_asked": rates2["mlups_asked"],
                           "ms_per_step": round(gpu_ms2 / args.steps, 4), "overlap_depth": d2,
                           "sweep_kernel": kname2,
                           "sweep_achieved_gbs": round(b2 * take2 / (k2 / 1e3) / 1e9, 1),
