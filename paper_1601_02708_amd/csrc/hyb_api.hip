@@ -210,9 +210,11 @@ Layout make_layout(const hyb_mesh *mesh, const hyb_lattice *lat, bool has_kfield
         }
         // passes of more than three launches share nodes by way of a fourth
         // state (shared_nodes), where the patch is large enough to have any
+        // (hyb_query without eta: room for any)
+        const int eta = lat->eta < 1 ? 3 * default_steps(lat->precision) + 1 : lat->eta;
         int launches = 0;
-        for (int rem = lat->eta; rem > 0; ++launches) rem -= plan_take(default_steps(lat->precision), rem);
-        L.extra_state = launches > 3 && launches <= 8 && N >= 4 * lat->eta + 128 && !lat->wall_closure;
+        for (int rem = eta; rem > 0 && launches <= 8; ++launches) rem -= plan_take(default_steps(lat->precision), rem);
+        L.extra_state = launches > 3 && launches <= 8 && N >= 4 * eta + 128 && !lat->wall_closure;
         if (L.extra_state) L.f_extra = take(L.f_bytes);
     }
     L.total = off;
