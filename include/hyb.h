@@ -376,7 +376,7 @@ int hyb_set_overlap(hyb_handle *h, int depth);
 
 /* Most fine steps per lattice-sweep launch (1 to 5; default 5 for HYB_FP32,
  * 4 for HYB_FP64 and HYB_FP16S storage, the fastest measured for each).  With 2 or
- * more, while every perimeter slot is Dirichlet, hyb_lbm_substeps takes fine
+ * more, hyb_lbm_substeps takes fine
  * steps in temporally blocked launches (the state between the steps of one
  * launch stays on chip), never leaving a lone single step where it can be
  * avoided: with 2, in pairs; with 3, in threes, a remainder of 4 taken as
@@ -384,25 +384,25 @@ int hyb_set_overlap(hyb_handle *h, int depth);
  * 6 starting with a three (eta = 10: 4 + 3 + 3); with 5, in fives,
  * remainders of 6, 7, 8 and 9 as 3 + 3, 4 + 3, 4 + 4 and 5 + 4 (eta = 10:
  * 5 + 5).  A remaining single step, and
- * every step when some slot is Neumann, the wall closure is on, or a
+ * every step when the wall closure is on, when solids dissolve beside Neumann
+ * slots, or when a
  * population buffer reaches 4 GiB (the multi-step kernels use 32-bit byte
- * offsets), uses the single-step sweep.  Results agree with the single-step
- * path to rounding (same operations per node; pairs give its bits, and
- * three- to five-step launches FP64 states identical to pairs' and FP32
- * ones within a few ulp, from the compiler's fusing of multiply-adds; FP16
+ * offsets), uses the single-step sweep.  HYB_FP64 and HYB_FP32 states are the
+ * same bits under every plan; FP16
  * shifted storage rounds to binary16 once per launch instead of once per
- * step).  With 2 or more, hyb_lbm_adjoint and hyb_step_adjoint also reverse
- * fine steps in pairs, one launch each (same bits as single reversed
- * steps).  Returns HYB_EINVAL for other values.  Takes effect at the next
+ * step.  hyb_lbm_adjoint and hyb_step_adjoint also reverse up to this many
+ * fine steps a launch (HYB_FP64 at most four; pairs with clamped closures or
+ * dissolving solids): the same cotangents, bit for bit, and dJ/dk to the
+ * rounding of its sum.  Returns HYB_EINVAL for other values.  Takes effect at the next
  * hyb_lbm_substeps or adjoint call and restarts the overlap tuning of
  * HYB_OVERLAP_AUTO. */
 int hyb_set_steps_per_launch(hyb_handle *h, int steps);
 
 /* Measurement: while enabled, every hyb_lbm_substeps call records HIP
  * events on the handle's stream around its lattice-sweep kernels: one pair
- * around the whole batch when all perimeter slots are Dirichlet (only sweep
- * kernels are launched, back to back), else one pair around each
- * interior-node kernel.  hyb_kernel_time returns the summed elapsed
+ * around the whole batch where fine steps go several to a launch or all
+ * perimeter slots are Dirichlet (a lone last step with Neumann slots brings its
+ * perimeter kernel into it), else one pair around each interior-node kernel.  hyb_kernel_time returns the summed elapsed
  * milliseconds and the number of sweep launches they cover since the last
  * call, and synchronises. */
 int hyb_kernel_timing(hyb_handle *h, int enable);

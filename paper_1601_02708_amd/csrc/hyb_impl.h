@@ -182,7 +182,8 @@ hipError_t launch_lbm_step(const LbmArgs &a, int prec, bool general_perimeter, h
 // hole: part 1 takes the tiles inside it, part 2 the others.
 hipError_t launch_lbm_step2(const LbmArgs &a, int prec, hipStream_t s, int part = 0, int depth = 0,
                             int ring = 1, const NodeRect *hole = nullptr);
-// K = 3, 4 or 5 fine steps in one launch (Dirichlet closure on every slot;
+// K = 3, 4 or 5 fine steps in one launch (with a.bc_kind the closure of each
+// slot, K = 2 too, else Dirichlet on every slot;
 // with the surface reaction of dissolving solids, and its link fluxes into
 // a.flux, parts 0 and 2 only): a.src holds f*(j), a.dst receives
 // f*(j+K); u^p at a.lam .. a.lam5.  With a.u_out (FP64 and FP32, whole-patch
